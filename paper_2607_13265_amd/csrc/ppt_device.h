@@ -298,6 +298,20 @@ DEV T gval(const T* p, size_t i) {
     return r;
 }
 
+// Reads at a wave-uniform index of memory that no kernel writes while this one runs (tables of the scene
+// and the plan): scalar loads, whose values take no vector registers.
+#define PPT_CONST __attribute__((address_space(4)))
+template <class T>
+DEV T cval(const T* p, int i) {
+    static_assert(sizeof(T) % 4 == 0, "records of 32-bit words");
+    T r;
+    const PPT_CONST uint32_t* src = (const PPT_CONST uint32_t*)(uintptr_t)(p + i);
+    uint32_t* dst = (uint32_t*)&r;
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(T) / 4); ++k) dst[k] = src[k];
+    return r;
+}
+
 // the four texels of a bilinear lookup (element offsets) and their weights
 struct Bilin { int i[4]; float w[4]; };
 
@@ -740,30 +754,34 @@ struct Counters { uint32_t nodes, prims, shadow, verts; };
 
 DEV bool is_delta(int t) { return t == MAT_DIELECTRIC || t == MAT_SHEET; }
 
-// Surface data of a hit (identical whether the hit comes from traversal or from a record).
-DEV void surface(const DevWorld& W, const Hit& h, v3 o, v3 d, Vtx& x) {
-    const float4* pr = W.prims + 3 * h.prim;
+// Surface data at a point of primitive prim: a triangle's from its barycentrics (u, v), a sphere's
+// from the point ps itself (identical whether they come from traversal or from a record).
+DEV void surface_at(const DevWorld& W, int prim, float hu, float hv, v3 ps, Vtx& x) {
+    const float4* pr = W.prims + 3 * prim;
     // the kind is in the third word and the material in the second: one round trip for the record
     const float4 A = ldg4(pr, 0), B = ldg4(pr, 1), C = ldg4(pr, 2);
     x.orig = __float_as_int(A.w);
-    x.prim = h.prim;
+    x.prim = prim;
     x.mat = __float_as_int(B.w);
     x.tri = __float_as_int(C.w) == 0;
     if (x.tri) {
         v3 e1 = mk(B.x, B.y, B.z), e2 = mk(C.x, C.y, C.z);
-        x.p = mk(A.x, A.y, A.z) + e1 * h.u + e2 * h.v;
+        x.p = mk(A.x, A.y, A.z) + e1 * hu + e2 * hv;
         x.ng = normalize(cross(e1, e2));
         const float* t = W.tri_uv + 6 * (size_t)x.orig;
-        float b0 = 1.0f - h.u - h.v;
-        x.u = b0 * gval(t, 0) + h.u * gval(t, 2) + h.v * gval(t, 4);
-        x.v = b0 * gval(t, 1) + h.u * gval(t, 3) + h.v * gval(t, 5);
+        float b0 = 1.0f - hu - hv;
+        x.u = b0 * gval(t, 0) + hu * gval(t, 2) + hv * gval(t, 4);
+        x.v = b0 * gval(t, 1) + hu * gval(t, 3) + hv * gval(t, 5);
     } else {
-        x.p = o + d * h.t;
+        x.p = ps;
         v3 nout = normalize(x.p - mk(A.x, A.y, A.z));
         x.ng = B.x < 0.0f ? -nout : nout;
         x.u = 0.5f + atan2f(nout.z, nout.x) * (0.5f / PI_F);
         x.v = acosf(fminf(fmaxf(nout.y, -1.0f), 1.0f)) * (1.0f / PI_F);
     }
+}
+DEV void surface(const DevWorld& W, const Hit& h, v3 o, v3 d, Vtx& x) {
+    surface_at(W, h.prim, h.u, h.v, o + d * h.t, x);
 }
 
 // Tangent frame of a triangle hit at its outward geometric normal ng: the tangent follows
@@ -843,10 +861,11 @@ constexpr int NEE_NONE = 0, NEE_VISIBLE = 1, NEE_OCCLUDED = 2, NEE_ZERO = 3, NEE
 // describe the shadow ray; the caller resolves it (a shadow-ray kernel, or a recorded flag).
 // EXT: the extended material features (normal maps, specular maps, circularly polarized
 // emitters) are compiled in; kernels of scenes without them skip that code.
+// last: the path is known to end here, so its continuation (lobe NONE) is not sampled again.
 template <bool EXT>
 DEV void vertex_setup(const DevWorld& W, const Call& K, uint32_t view_id, uint64_t seed, uint32_t pix, uint32_t smp,
                       int b, int max_depth, uint32_t flags, bool prev_delta, v3 d, Vtx& x, v3& so, v3& sd,
-                      float& stmax) {
+                      float& stmax, bool last = false) {
     const DevMaterial m = gval(W.mats, (size_t)x.mat);
     x.wo = -d;
     x.front = dot(x.ng, x.wo) > 0.0f;
@@ -895,6 +914,7 @@ DEV void vertex_setup(const DevWorld& W, const Call& K, uint32_t view_id, uint64
             x.nee_geom = cos_y * L.area * (float)nl / dist2;
         }
     }
+    if (last) return;
     switch (m.type) {
         case MAT_LAMBERT:
             x.lobe = sample_diffuse(x.ns, ua[1], ua[2], x.wi, x.pdf);
@@ -1128,18 +1148,20 @@ DEV v3 spec_frames_grad(v3 k_in, v3 n_inc, v3 k_out, float gci, float gsi, float
 // FULL (conventional reverse sweep, scenes without the light-stage features): Ln is the general
 // adjoint of the weight, 3 row-major 4x4 blocks, instead of the suffix whose outer product with a
 // gives it.
-template <bool GRAD, bool EXT, bool FULL = false>
+// WONLY: the weight alone (no emission and no next-event part; Eemit and Enee are not written).
+template <bool GRAD, bool EXT, bool FULL = false, bool WONLY = false>
 DEV void eval_vertex(const DevWorld& W, const Call& K, const Vtx& x, WC& w, float* Eemit, float* Enee, const float* a,
                      const float* Ln) {
     static_assert(!(FULL && EXT), "the general weight adjoint is not implemented with the light-stage features");
     const DevMaterial m = gval(W.mats, (size_t)x.mat);
     const bool nm = EXT && x.nmap;
+    if (!WONLY)
 #pragma unroll
-    for (int i = 0; i < 12; ++i) { Eemit[i] = 0.0f; Enee[i] = 0.0f; }
+        for (int i = 0; i < 12; ++i) { Eemit[i] = 0.0f; Enee[i] = 0.0f; }
     GradVtx gv;
     if (GRAD) gv.zero();
     w.kind = 0;
-    if (x.emit) {
+    if (!WONLY && x.emit) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             float le = K.p(m.emit_slot, m.emit_off + c);
@@ -1149,7 +1171,7 @@ DEV void eval_vertex(const DevWorld& W, const Call& K, const Vtx& x, WC& w, floa
         }
     }
     // next-event estimation: E_c += f_c (e0 + circ e3) * cos_x * geom * Le_c
-    if (x.nee == NEE_VISIBLE || x.nee == NEE_PENDING) {
+    if (!WONLY && (x.nee == NEE_VISIBLE || x.nee == NEE_PENDING)) {
         const DevLight L = gval(W.lights, (size_t)x.light);
         float cx = dot(x.ns, x.wl);
         float gs = cx * x.nee_geom;
@@ -1362,12 +1384,12 @@ DEV void analyzer_apply(int sensor, float theta, int a, const float* v, float* o
     else { C = 0.0f; S = -1.0f; q = 0.5f * (v[0] - v[3]); }  // QWP(0), polarizer at -45 deg: left-circular
     o[0] = q; o[1] = C * q; o[2] = S * q; o[3] = 0.0f;
 }
-// row delta^T A_a
-DEV void analyzer_row(int sensor, float theta, int a, const float* dl, float* r) {
+// row delta^T A_a; (C2, S2) = (cos 2 theta, sin 2 theta) of a linear polarizer
+DEV void analyzer_row(int sensor, float C2, float S2, int a, const float* dl, float* r) {
     if (sensor == SENSOR_NONE) { r[0] = dl[0]; r[1] = dl[1]; r[2] = dl[2]; r[3] = dl[3]; return; }
     float C, S;
     int kind = 0;
-    if (sensor == SENSOR_POLARIZER) { C = cosf(2.0f * theta); S = sinf(2.0f * theta); }
+    if (sensor == SENSOR_POLARIZER) { C = C2; S = S2; }
     else if (a == 0) { C = 1.0f; S = 0.0f; }
     else if (a == 1) { C = 0.0f; S = 1.0f; }
     else if (a == 2) { C = -1.0f; S = 0.0f; }
@@ -1376,9 +1398,8 @@ DEV void analyzer_row(int sensor, float theta, int a, const float* dl, float* r)
     if (kind == 0) { r[0] = q; r[1] = C * q; r[2] = S * q; r[3] = 0.0f; }
     else { r[0] = q; r[1] = 0.0f; r[2] = 0.0f; r[3] = S * q; }  // circular analyzers: q(v) = (v0 + S v3) / 2
 }
-// delta^T (dP(theta)/dtheta) v
-DEV float polarizer_dtheta(float theta, const float* dl, const float* v) {
-    float C = cosf(2.0f * theta), S = sinf(2.0f * theta);
+// delta^T (dP(theta)/dtheta) v, (C, S) = (cos 2 theta, sin 2 theta)
+DEV float polarizer_dtheta(float C, float S, const float* dl, const float* v) {
     float r0 = -S * dl[1] + C * dl[2];
     float r1 = -S * dl[0] - 2.0f * C * S * dl[1] + (C * C - S * S) * dl[2];
     float r2 = C * dl[0] + (C * C - S * S) * dl[1] + 2.0f * C * S * dl[2];

@@ -20,7 +20,7 @@ hipError_t launch_fill_f32(float* p, int64_t n, hipStream_t s);
 hipError_t launch_fill_f64(double* p, int64_t n, hipStream_t s);
 hipError_t launch_finalize(const CallTable* tab, const double* gacc, int n_slots, int64_t max_numel, hipStream_t s);
 hipError_t launch_rng(uint64_t seed, const uint32_t* ctr, uint32_t* out, int64_t n, hipStream_t s);
-hipError_t launch_chunk(WArgs a, int mode, const LaunchGrid& G, hipStream_t s, const LaunchMarker& M);
+hipError_t launch_chunk(WArgs a, const PathState& S2, int mode, const LaunchGrid& G, hipStream_t s, const LaunchMarker& M);
 hipError_t occupancy_grid(int cu, int stack_cap, LaunchGrid* G);
 hipError_t noalloc_scratch(void** ptr);
 }  // namespace ppt
@@ -508,7 +508,7 @@ static int convert_world(ppt_scene* sc, const uint8_t*& p, const uint8_t* end, W
 struct WsLayout {
     size_t table, stats, counts, gacc, total;
     int lds_nd = 0, lds_nf = 0;
-    size_t ray, shd, acc, cache, hits, ckpt, q0, q1, sq, hq, hf, nv, nv_bytes;
+    size_t ray, shd, acc, vtx, row, dq, cache, hits, ckpt, q0, q1, sq, hq, hf, nv, nv_bytes;
     size_t ray2, shd2, acc2, q0_2, q1_2, sq2, hq2, hf2, counts2;  // P-RB sub-path state
     int64_t gacc_n;
 };
@@ -518,7 +518,13 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // linear-polarizer sensor and the scene has none of the light-stage features.
 static bool rank_one(const ppt_plan* p) { return p->all_polarizer && !p->scene->has_ext; }
 
-static WsLayout ws_layout(const ppt_plan* p, int op, int32_t Qslots) {
+// The backward runs as the cached reverse walk (no checkpoints, none of the comparators, and a scene
+// without the light-stage features).
+static bool cached_adjoint(const ppt_plan* p) {
+    return p->ckpt == 0 && p->adjoint == PPT_ADJOINT_CACHED && !p->scene->has_ext;
+}
+
+static WsLayout ws_layout(const ppt_plan* p, int op, int32_t Qslots, bool packed = false) {
     WsLayout L{};
     const size_t Q = (size_t)Qslots;
     size_t at = 0;
@@ -527,14 +533,23 @@ static WsLayout ws_layout(const ppt_plan* p, int op, int32_t Qslots) {
     L.stats = take(sizeof(Stats));
     L.counts = take(32);
     L.ray = take(RAY_F4 * 16 * Q);
-    L.shd = take(op == 0 && rank_one(p) ? 0 : SHD_F4 * 16 * Q);
+    const bool adj = op == 1 && cached_adjoint(p);
+    L.shd = take(op == 0 && rank_one(p) ? 0 : (adj ? SHD1_F4 : SHD_F4) * 16 * Q);
     const bool tape = op == 1 && p->adjoint == PPT_ADJOINT_TAPE;  // (forward accumulator + per-vertex tape)
     L.acc = take(op == 0 || tape ? ACC_F4 * 16 * Q : 0);
     L.nv_bytes = (op == 0 && rank_one(p)) || op == 1 ? Q : 0;  // vertex counts (rank-one render, backward)
     L.nv = take(L.nv_bytes);
     const bool hybrid = op == 1 && p->ckpt > 0;
     const size_t records = hybrid ? (size_t)std::min(p->ckpt, p->max_depth) : (size_t)p->max_depth;
-    L.cache = take(op == 1 ? records * (tape ? TAPE_F4 : CACHE_F4) * 16 * Q : 0);
+    // the cached backward's vertex records and adjoint rows: within the 128 bytes per vertex that the
+    // workspace's stated size reserves, or just as large as they are (packed)
+    const size_t vtx_bytes = adj ? (size_t)p->max_depth * VTX_F4 * 16 * Q : 0;
+    const size_t row_bytes = adj ? (size_t)(p->max_depth - 1) * (rank_one(p) ? ROW1_F4 : ROW_F4) * 16 * Q : 0;
+    static_assert(VTX_F4 + ROW_F4 <= CACHE_F4 && VTX_F4 + ROW1_F4 <= CACHE_F4, "fit in the reserved records");
+    L.vtx = take(!adj ? 0 : packed ? vtx_bytes + row_bytes : records * CACHE_F4 * 16 * Q);
+    L.row = L.vtx + vtx_bytes;
+    L.dq = take(adj ? 4 * Q : 0);
+    L.cache = take(op == 1 && !adj ? records * (tape ? TAPE_F4 : CACHE_F4) * 16 * Q : 0);
     L.hits = take(hybrid ? (size_t)p->max_depth * 16 * Q : 0);
     L.ckpt = take(hybrid ? (size_t)((p->max_depth + p->ckpt - 1) / p->ckpt) * CKPT_F4 * 16 * Q : 0);
     L.q0 = take(4 * Q); L.q1 = take(4 * Q); L.sq = take(4 * Q); L.hq = take(4 * Q); L.hf = take(Q);
@@ -568,6 +583,9 @@ static PathState path_state(void* ws, const WsLayout& L) {
     S.shd = (float4*)(w + L.shd);
     S.acc = (float4*)(w + L.acc);
     S.nv = L.nv_bytes ? (uint8_t*)(w + L.nv) : nullptr;
+    S.vtx = (float4*)(w + L.vtx);
+    S.row = (float4*)(w + L.row);
+    S.dqueue = (int*)(w + L.dq);
     S.cache = (float4*)(w + L.cache);
     S.hits = (float4*)(w + L.hits);
     S.ckpt = (float4*)(w + L.ckpt);
@@ -695,6 +713,9 @@ int ppt_plan_create(const ppt_scene* sc, const ppt_view* views, int32_t n_views,
         D.view_id = V.view_id;
         D.out_off = out_off;
         D.path_off = path_off;
+        D.inv_spp = 1.0 / (double)V.spp;
+        D.inv_cw = 1.0 / (double)std::max(V.crop_w, 1);  // (an empty view has no paths)
+        D.inv_w = 1.0 / (double)V.width;
         out_off += (int64_t)D.n_analyzers * V.crop_w * V.crop_h * 12;
         path_off += (int64_t)V.crop_w * V.crop_h * V.spp;
         P->dviews.push_back(D);
@@ -846,13 +867,14 @@ static LaunchMarker marker(const ppt_plan* p, int op) {
 }
 
 // every chunk of a.Q paths (the plan's chunk size unless the caller's memory holds less)
-static int run_chunks(const ppt_plan* p, WArgs a, int mode, hipStream_t s, const LaunchMarker& M) {
+// (S2: P-RB's sub-path state)
+static int run_chunks(const ppt_plan* p, WArgs a, const PathState& S2, int mode, hipStream_t s, const LaunchMarker& M) {
     const int64_t n_chunks = std::max<int64_t>(1, (p->num_paths + a.Q - 1) / a.Q);
     for (int64_t c = 0; c < n_chunks; ++c) {
         a.g0 = c * a.Q;
         a.n_chunk = (int32_t)std::min<int64_t>(a.Q, p->num_paths - a.g0);
         if (a.n_chunk <= 0) break;
-        HIP_TRY(launch_chunk(a, mode, p->grid, s, M), mode == 0 ? "render launch" : "backward launch");
+        HIP_TRY(launch_chunk(a, S2, mode, p->grid, s, M), mode == 0 ? "render launch" : "backward launch");
     }
     return PPT_OK;
 }
@@ -874,7 +896,7 @@ static int render_impl(const ppt_plan* p, const float* const* params, int32_t n_
     M(KF_OTHER, s);
     HIP_TRY(launch_setup(t, a.table, (Stats*)((char*)ws + L.stats), p->stats, s), "setup launch");
     if (out) HIP_TRY(launch_fill_f32(out, p->image_numel, s), "clear launch");
-    if ((rc = run_chunks(p, a, 0, s, M))) return rc;
+    if ((rc = run_chunks(p, a, PathState{}, 0, s, M))) return rc;
     M(-1, s);
     return PPT_OK;
 }
@@ -916,14 +938,13 @@ static int backward_impl(const ppt_plan* p, const float* const* params, int32_t 
     a.pprb = p->adjoint == PPT_ADJOINT_PPRB;
     a.tape = p->adjoint == PPT_ADJOINT_TAPE;
     a.prb = p->adjoint == PPT_ADJOINT_PRB;
-    if (a.prb) a.S2 = path_state2(ws, L);
     a.pprb_sigma = p->pprb_sigma;
     const LaunchMarker M = op_timer >= 0 ? marker(p, op_timer) : LaunchMarker{nullptr, nullptr};
     if (op_timer >= 0 && p->timing) p->timer[op_timer].begin();
     M(KF_OTHER, s);
     HIP_TRY(launch_setup(t, a.table, (Stats*)((char*)ws + L.stats), stats, s), "setup launch");
     HIP_TRY(launch_fill_f64(a.gacc, L.gacc_n, s), "clear launch");
-    if ((rc = run_chunks(p, a, 1, s, M))) return rc;
+    if ((rc = run_chunks(p, a, a.prb ? path_state2(ws, L) : PathState{}, 1, s, M))) return rc;
     M(KF_OTHER, s);
     HIP_TRY(launch_finalize(a.table, a.gacc, n_params, mx, s), "finalize launch");
     M(-1, s);
@@ -944,22 +965,22 @@ int ppt_backward_noalloc(const ppt_plan* p, const float* const* params, int32_t 
     // the largest chunk (a multiple of the wavefront size, at most the plan's) whose records and
     // the gradient accumulators fit in the fixed scratch
     const size_t cap = NOALLOC_SCRATCH_BYTES;
-    if (ws_layout(p, 1, WAVE).total > cap) {
+    if (ws_layout(p, 1, WAVE, true).total > cap) {
         char msg[200];
         std::snprintf(msg, sizeof msg,
                       "the fixed scratch (%zu bytes) cannot hold the gradient accumulators and one %d-path chunk "
-                      "at depth %d (%zu bytes needed)", cap, WAVE, p->max_depth, ws_layout(p, 1, WAVE).total);
+                      "at depth %d (%zu bytes needed)", cap, WAVE, p->max_depth, ws_layout(p, 1, WAVE, true).total);
         return fail(PPT_EUNSUPPORTED, msg);
     }
     int64_t lo = 1, hi = std::max<int64_t>(1, p->Q / WAVE);  // in wavefronts
     while (lo < hi) {
         const int64_t mid = (lo + hi + 1) / 2;
-        if (ws_layout(p, 1, (int32_t)(mid * WAVE)).total <= cap) lo = mid; else hi = mid - 1;
+        if (ws_layout(p, 1, (int32_t)(mid * WAVE), true).total <= cap) lo = mid; else hi = mid - 1;
     }
     const int32_t Q = (int32_t)(lo * WAVE);
     void* ws = nullptr;
     HIP_TRY(noalloc_scratch(&ws), "scratch address lookup");
-    WsLayout L = ws_layout(p, 1, Q);
+    WsLayout L = ws_layout(p, 1, Q, true);
     return backward_impl(p, params, n_params, seed, d_stokes, grads, ws, L, Q, false, -1, stream);
 }
 

@@ -32,7 +32,14 @@ constexpr int STACK = 64;       // BVH traversal stack entries per lane
 //   next-event part included as if visible   [3] y without that part (restored for an occluded
 //   sample); the shadow ray in a dense 32-byte record behind the chunk's rank-one records, [0] origin,
 //   tmax   [1] direction, info; no shadow record
-//   cache record (backward), one per (vertex b, slot), CACHE_F4 = 8 vectors (128 B):
+//   vertex record (cached backward), one per (vertex b, slot), VTX_F4 = 2 vectors (32 B):
+//     [0] prim | (previous vertex delta) << 26, then u v - (a triangle) or the hit point (a sphere)
+//     [1] incoming direction, visibility word (0; 1 written by traversal for an occluded light sample)
+//   adjoint row (cached backward), one per (vertex b > 1, slot): ROW_F4 = 3 vectors (48 B), the 3 x 4 rows a_b,
+//     or in a batch of linear polarizers ROW1_F4 = 2 vectors (32 B): [0] rho [1] sc (3), a_b,c = sc_c rho.
+//     Shadow rays of the cached backward: dense 32-byte records (SHD1_F4).  The suffix L[2] beyond a path's
+//     first vertex: the first 48 bytes of its ray record, after the bounces
+//   cache record (comparators, and the backward with light-stage features), one per (vertex b, slot), CACHE_F4 = 8 vectors (128 B):
 //     [0] rgb0 rgb1 rgb2 A   [1] B C D Cin   [2] Sin Cout Sout hitword   [3] u-or-t v - -
 //     [4..6] E_b (12 words; with the next-event part as if visible when a light sample is pending, set
 //     back to E_b by the shadow-ray traversal if occluded), overwritten by the fold with the suffix radiance beyond the vertex,
@@ -51,6 +58,7 @@ constexpr int STACK = 64;       // BVH traversal stack entries per lane
 //     throughput beta_b (shared 4x4)   [12] its RGB scales, previous vertex delta   [13..14] the ray into
 //     the vertex (o, d)
 constexpr int RAY_F4 = 4, SHD_F4 = 8, ACC_F4 = 8, R1_F4 = 4, CACHE_F4 = 8, CKPT_F4 = 5, TAPE_F4 = 15;
+constexpr int SHD1_F4 = 2, VTX_F4 = 2, ROW_F4 = 3, ROW1_F4 = 2;
 
 enum MatType : int32_t { MAT_LAMBERT = 0, MAT_DIELECTRIC = 1, MAT_GGX_DIELECTRIC = 2, MAT_GGX_CONDUCTOR = 3,
                          MAT_SHEET = 4, MAT_EMITTER = 5, MAT_BLEND = 6 };
@@ -106,6 +114,7 @@ struct DevView {
     uint32_t view_id, pad;
     int64_t out_off;             // float offset of this view in the output image
     int64_t path_off;            // index of its first path (view, crop row, crop column, sample)
+    double inv_spp, inv_cw, inv_w;  // 1 / spp, 1 / crop_w, 1 / width: divisors of path and pixel indices
 };
 
 // Per-call device table written by the setup kernel (kernel arguments cannot be indexed
@@ -146,7 +155,11 @@ struct PathState {
     float4* acc;    // [Q][ACC_F4] (render)
     uint8_t* nv;    // [Q] vertices of the path: the first traversal writes 0 or 1, the backward's shading
                     // kernels the count; read by the rank-one pixel reduction (has the path a radiance
-                    // record) and by the fold, so that neither reads a ray record (NULL: not kept)
+                    // record), the fold and the first-vertex kernel, so that none reads a ray record (NULL:
+                    // not kept)
+    float4* vtx;    // [max_depth][Q][VTX_F4] vertex records (cached backward)
+    float4* row;    // [max_depth - 1][Q][ROW_F4 or ROW1_F4] adjoint rows of the vertices after the first
+    int* dqueue;    // paths of two or more vertices (cached backward)
     float4* cache;  // [max_depth or k][Q][CACHE_F4] (backward; per block scratch in the hybrid replay)
     float4* hits;   // [max_depth][Q] hit records (hybrid replay)
     float4* ckpt;   // [ceil(max_depth / k)][Q][CKPT_F4] checkpoint records (hybrid replay)
@@ -156,8 +169,8 @@ struct PathState {
     int* hqueue;    // queue of the rays of this bounce that hit a surface (input of the shading kernel)
     uint8_t* hflag; // [Q] outcome of the slot's last closest-hit ray: 0 miss, 1 hit, 2 no ray (masked path)
     int* counts;    // 8 ints: [0], [1] sizes of queue0, queue1; [2] size of the shadow queue; [3] size of
-                    // the replay queue; [4], [5] work counters of the replay and traversal kernels; [6]
-                    // unused; [7] size of the hit queue
+                    // the replay queue; [4], [5], [6] work counters of the replay, traversal and first-vertex
+                    // kernels; [7] size of the hit queue
 };
 
 struct WArgs {
@@ -184,12 +197,13 @@ struct WArgs {
     unsigned long long* hyb_stats;  // NULL or 3 counters of the rule's branches
     int32_t tape;           // backward by the conventional-AD baseline (stored tape, reverse sweep)
     int32_t prb;            // backward by the P-RB comparator (independent suffix estimates)
-    PathState S2;           // P-RB: state of the sub-paths
     int32_t pprb;           // backward by the noise-regularised P-PRB comparator (Sec. 4.2)
     float pprb_sigma;       // its noise deviation
     int32_t ext;            // the scene uses normal maps, specular maps or circular emitters
     int32_t r1;             // render by the rank-one record (every view has a linear-polarizer sensor, no ext)
-    int32_t r1adj;          // cached backward of such a batch: the replay start record's rank-one form
+    int32_t adj;            // cached backward (no checkpoints, no comparator)
+    int32_t r1adj;          // cached backward of such a batch: adjoint rows in rank-one form
+    int32_t keep_deep;      // this bounce's hit queue is kept (in S.dqueue, its size in counts[3])
     float* out;             // render output
     const float* dout;      // backward: dL/dStokes
     double* gacc;           // backward: FP64 gradient accumulators

@@ -98,7 +98,8 @@ struct WaveFetch {
     bool exhausted;
     DEV explicit WaveFetch(int n) {
         const int waves = fetch_blocks(n) * (BLOCK / WAVE);
-        const int w = blockIdx.x * (BLOCK / WAVE) + (int)(threadIdx.x / WAVE);
+        // (readfirstlane: the wavefront's number, known uniform, keeps the fetch state in scalar registers)
+        const int w = blockIdx.x * (BLOCK / WAVE) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
         int sb = (n + waves - 1) / waves;
         sb = sb < FETCH_MIN ? FETCH_MIN : (sb > FETCH_BATCH ? FETCH_BATCH : sb);
         stat = waves * sb;
@@ -132,41 +133,81 @@ struct WaveFetch {
     DEV bool more() const { return !exhausted || c < cend; }  // wave-uniform
 };
 
-// view of a global path index (binary search over the views' first path indices)
-DEV int find_view(const DevView* views, int n_views, int64_t g) {
-    int lo = 0, hi = n_views - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (gval(views, (size_t)mid).path_off <= g) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-// Path keys of a global path index.  The lanes of a wavefront mostly hold consecutive paths, so
-// the view of a wave-uniform first index g_first is looked up once and a lane searches only when
-// its path lies outside [g_first, end of that view).  The index within a view fits 32 bits (checked
-// when the plan is made).
-struct PathId { int v, px, py, lx, ly; uint32_t smp, pix, view_id; };
-DEV void path_keys(const DevView& V, int64_t g, PathId& r) {
-    const uint32_t local = (uint32_t)(g - V.path_off);
-    const uint32_t spp = (uint32_t)V.spp, cw = (uint32_t)V.crop_w;
-    const uint32_t pl = local / spp;
-    r.smp = local - pl * spp;
-    r.ly = (int)(pl / cw);
-    r.lx = (int)(pl - (uint32_t)r.ly * cw);
-    r.px = V.crop_x0 + r.lx;
-    r.py = V.crop_y0 + r.ly;
-    r.pix = (uint32_t)(r.py * V.width + r.px);
-    r.view_id = V.view_id;
-}
-DEV PathId path_id(const DevView* views, int n_views, int64_t g, int64_t g_first) {
+// Path keys of a global path index of view V.  The index within a view fits 32 bits (checked when the
+// plan is made).
+struct PathId { int lx, ly; uint32_t smp, pix; };
+// n / d for n < 2^31 and inv = 1 / d in double: (n + 1/2) / d lies at least 1 / (2 d) from an integer and the
+// product is off by less than 2^-21 / d, so the quotient is exact (4 instructions instead of the about 25 of
+// a 32-bit division).
+DEV uint32_t div_by(uint32_t n, double inv) { return (uint32_t)(((double)n + 0.5) * inv); }
+DEV PathId path_keys(const DevView& V, int64_t g) {
     PathId r;
-    const int v0 = __builtin_amdgcn_readfirstlane(find_view(views, n_views, g_first));
-    r.v = v0;
-    const int64_t end0 = v0 + 1 < n_views ? gval(views, (size_t)(v0 + 1)).path_off : INT64_MAX;
-    if (g >= end0 || g < g_first) r.v = find_view(views, n_views, g);
-    const DevView V = gval(views, (size_t)r.v);
-    path_keys(V, g, r);
+    const uint32_t local = (uint32_t)(g - V.path_off);
+    const uint32_t pl = div_by(local, V.inv_spp);
+    r.smp = local - pl * (uint32_t)V.spp;
+    r.ly = (int)div_by(pl, V.inv_cw);
+    r.lx = (int)(pl - (uint32_t)r.ly * (uint32_t)V.crop_w);
+    r.pix = (uint32_t)((V.crop_y0 + r.ly) * V.width + V.crop_x0 + r.lx);
     return r;
+}
+// The view of a wavefront's paths.  The lanes mostly hold consecutive paths of one view, and go on in
+// that view, so the view found last is kept (v and its paths [lo, hi), wave-uniform, in scalar
+// registers), and a new one is searched (binary, by scalar loads) only when a path lies outside it.
+// A search per wavefront and step by vector loads was a chain of log2(views) round trips: the
+// first-vertex kernel of the 128-view batch spent half of its time in it.
+struct ViewRange { int v = 0; int64_t lo = 0, hi = 0; };
+DEV int64_t read_lane64(int64_t x, int lane) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)x >> 32), lane);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+DEV void view_at(const WArgs& A, int64_t g, ViewRange& R) {  // g wave-uniform
+    if (g >= R.lo && g < R.hi) return;
+    int lo = 0, hi = A.n_views - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (cval(&A.views[mid].path_off, 0) <= g) lo = mid; else hi = mid - 1;
+    }
+    R.v = lo;
+    R.lo = cval(&A.views[lo].path_off, 0);
+    R.hi = lo + 1 < A.n_views ? cval(&A.views[lo + 1].path_off, 0) : INT64_MAX;
+}
+// The view of path g of an active lane: the wavefront's, or its own where its path lies in another one.
+// Every lane of the wavefront calls find(), then an active lane view().
+DEV void view_find(const WArgs& A, ViewRange& R, bool active, int64_t g) {
+    const uint64_t m = __ballot(active);
+    if (m != 0ull) view_at(A, read_lane64(g, __ffsll((long long)m) - 1), R);
+}
+DEV DevView view_of(const WArgs& A, const ViewRange& R, int64_t g, int& v) {
+    DevView V = cval(A.views, R.v);
+    v = R.v;
+    if (g < R.lo || g >= R.hi) {
+        int lo = 0, hi = A.n_views - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (gval(&A.views[mid].path_off, 0) <= g) lo = mid; else hi = mid - 1;
+        }
+        v = lo;
+        V = gval(A.views, (size_t)lo);
+    }
+    return V;
+}
+// f(v, V) for the active lanes, view by view: v and V are the wave-uniform view of the lanes that run it
+// (one pass unless the lanes' paths g span views).  Every lane of the wavefront calls it, so that the
+// range stays in scalar registers.
+template <class F>
+DEV void for_views(const WArgs& A, ViewRange& R, bool active, int64_t g, F f) {
+    bool todo = active;
+    while (true) {
+        const uint64_t m = __ballot(todo);
+        if (m == 0ull) break;
+        view_at(A, read_lane64(g, __ffsll((long long)m) - 1), R);
+        if (todo && g >= R.lo && g < R.hi) {
+            const DevView V = cval(A.views, R.v);
+            f(R.v, V);
+            todo = false;
+        }
+    }
 }
 
 // The call table (parameter pointers, gradient routing) is read for every parameter access; a
@@ -185,18 +226,18 @@ DEV float4* r1_rec(const PathState& S, int i) { return S.acc + (size_t)i * R1_F4
 // the rank-one render's shadow rays: a dense 32-byte record per slot behind the rank-one records
 DEV float4* r1_shd(const PathState& S, int Q, int i) { return S.acc + (size_t)Q * R1_F4 + (size_t)i * 2; }
 static_assert(R1_F4 + 2 <= ACC_F4, "the rank-one records and their shadow rays fit in the accumulator array");
-// The cached replay's start record in its rank-one form (every view a linear-polarizer sensor): the
-// adjoint rows are s_c r with one row r shared by the channels, so the record is 64 bytes, two to a
-// line, in the shadow-record array: [0] camera-ray direction, info  [1] pix, smp, r1, r2  [2] s_c
-// (r0 = 1, r3 = 0).
-DEV float4* rst_rec(const PathState& S, int i) { return S.shd + (size_t)i * 4; }
-static_assert(2 + 3 <= SHD_F4 && 4 <= SHD_F4,
-              "the dense shadow rays, emitting E_b and rank-one start records fit in the shadow-record array");
-// The cached backward's bounces use the shadow-record array as two dense arrays (the fold later
-// writes whole 128-byte records there): a 32-byte shadow ray per slot, four to a cache line, and
-// the 48-byte E_b of an emitting vertex behind them.
-DEV float4* shd1_rec(const PathState& S, int i) { return S.shd + (size_t)i * 2; }
+// The comparators' bounces (P-PRB, P-RB) use the shadow-record array as two dense arrays (the fold
+// later writes whole 128-byte records there): a 32-byte shadow ray per slot, four to a cache line,
+// and the 48-byte E_b of an emitting vertex behind them.  The cached backward keeps the shadow rays alone.
+static_assert(2 + 3 <= SHD_F4, "the dense shadow rays and the emitting E_b fit in the shadow-record array");
+DEV float4* shd1_rec(const PathState& S, int i) { return S.shd + (size_t)i * SHD1_F4; }
 DEV float4* emit1_rec(const PathState& S, int Q, int i) { return S.shd + (size_t)Q * 2 + (size_t)i * 3; }
+// cached backward: a vertex's record, and the adjoint row of a vertex after the first (b0 >= 1)
+DEV float4* vtx_rec(const PathState& S, int Q, int b0, int i) { return S.vtx + ((size_t)b0 * Q + i) * VTX_F4; }
+template <bool R1>
+DEV float4* row_rec(const PathState& S, int Q, int b0, int i) {
+    return S.row + ((size_t)(b0 - 1) * Q + i) * (R1 ? ROW1_F4 : ROW_F4);
+}
 DEV float4* cache_rec(const PathState& S, int Q, int b0, int i) {  // b0: 0-based vertex index
     return S.cache + ((size_t)b0 * Q + i) * CACHE_F4;
 }
@@ -225,6 +266,7 @@ DEV void ray_set(float4* R, v3 o, v3 d, float Cs = 0.0f, float Ss = 0.0f) {
     R[1] = f4(d.y, d.z, Cs, Ss);
 }
 
+constexpr int VTX_PREV_DELTA = 1 << 26;  // (vertex record: beside the primitive)
 constexpr int INFO_DEAD = 1 << 9;
 constexpr int INFO_EMIT = 1 << 10;  // (a cached-backward shadow ray's vertex emits: its E_b is kept)
 DEV int info_make(int nverts, bool prev_delta, int view) { return nverts | (prev_delta ? 256 : 0) | (view << 12); }
@@ -278,33 +320,23 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STAT
     Trav T;
     bool alive = false, any = false;
     int slot = -1, info = 0;
+    ViewRange range;  // (camera rays)
     while (true) {
         const int idx = F.take(!alive, n, &S.counts[5]);
-        if (idx >= 0) {
-            any = idx < ns;
-            if (SMODE >= 0 && any) {
-                slot = S.squeue[idx];
-                // the shadow ray and its vertex's info word in one record (no read of the ray
-                // record, whose line would be fetched for its 16-byte key word)
-                const float4* H = SMODE == 4 ? r1_shd(S, Q, slot) : SMODE == 1 ? shd1_rec(S, slot) : shd_rec(S, slot);
-                const float4 s0 = H[0], s1 = H[1];
-                info = __float_as_int(s1.w);
-                trav_begin(T, world_of(A, info >> 12),
-                           mk(s0.x, s0.y, s0.z), mk(s1.x, s1.y, s1.z), s0.w);
-                alive = true;
-                ++cnt.c[ST_SHADOW_RAYS];
-            } else if (SMODE == -2) {
-                // the camera ray of path slot, generated here (its record is written when the ray
-                // is finished; a masked path's keys at once, and it is not traversed)
+        if constexpr (SMODE == -2) {
+            // the camera ray of path slot, generated here (its record is written when the ray is
+            // finished; a masked path's keys at once, and it is not traversed)
+            const int64_t g = A.g0 + idx;
+            view_find(A, range, idx >= 0, g);
+            if (idx >= 0) {
                 slot = idx;
-                const int64_t g = A.g0 + idx;
-                const int64_t g_first = A.g0 + __builtin_amdgcn_readfirstlane(idx);
-                const PathId id = path_id(A.views, A.n_views, g, g_first);
-                const DevView V = gval(A.views, (size_t)id.v);
+                int v;
+                const DevView V = view_of(A, range, g, v);
                 const bool live = !(A.mask && !A.mask[g]);
+                const PathId id = path_keys(V, g);
                 v3 o, d;
-                camera_ray(V, id.px, id.py, id.smp, A.seed, o, d);
-                info = info_make(0, false, id.v) | (live ? 0 : INFO_DEAD);
+                camera_ray(V, V.crop_x0 + id.lx, V.crop_y0 + id.ly, id.smp, A.seed, o, d);
+                info = info_make(0, false, v) | (live ? 0 : INFO_DEAD);
                 trav_begin(T, world_of(A, V), o, d, 3.0e38f);
                 alive = live;
                 if (A.sig) A.sig[g] = live ? 1469598103934665603ull : 0ull;
@@ -317,6 +349,20 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STAT
                     S.hflag[slot] = 2;
                     if (S.nv) S.nv[slot] = 0;  // (no vertex)
                 }
+            }
+        } else if (idx >= 0) {
+            any = idx < ns;
+            if (SMODE >= 0 && any) {
+                slot = S.squeue[idx];
+                // the shadow ray and its vertex's info word in one record (no read of the ray
+                // record, whose line would be fetched for its 16-byte key word)
+                const float4* H = SMODE == 4 ? r1_shd(S, Q, slot) : SMODE == 1 || SMODE == 5 ? shd1_rec(S, slot) : shd_rec(S, slot);
+                const float4 s0 = H[0], s1 = H[1];
+                info = __float_as_int(s1.w);
+                trav_begin(T, world_of(A, info >> 12),
+                           mk(s0.x, s0.y, s0.z), mk(s1.x, s1.y, s1.z), s0.w);
+                alive = true;
+                ++cnt.c[ST_SHADOW_RAYS];
             } else {
                 slot = A.first ? idx : q[idx - ns];
                 const float4* R = ray_rec(S, slot);
@@ -343,7 +389,34 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STAT
                 cnt.c[ST_NODES] += nn; cnt.c[ST_PRIMS] += np;
             }
         }
-        if (done) {
+        if constexpr (SMODE == -2) {
+            // the camera ray's record: the whole record for a hit (ray, sensor rotation, hit,
+            // keys), the keys alone for a ray that escaped (nothing else of it is read); the
+            // keys again from the slot and the view
+            const int64_t g = A.g0 + slot;
+            view_find(A, range, done, g);
+            if (done) {
+                alive = false;
+                int v;
+                const DevView V = view_of(A, range, g, v);
+                float4* R = ray_rec(S, slot);
+                const PathId id = path_keys(V, g);
+                if (T.h.prim >= 0) {
+                    // rotation from the canonical frame of the light arriving along -d to the
+                    // sensor frame, kept in the record's spare words for the pixel reduction
+                    const v3 kc = -T.d;
+                    float Cs, Ss;
+                    rot_cs(kc, canon_x(kc), normalize(ld3(V.r) - kc * dot(ld3(V.r), kc)), Cs, Ss);
+                    ray_set(R, T.o, T.d, Cs, Ss);
+                    R[2] = f4(T.tb, T.h.u, T.h.v, __int_as_float(T.h.prim));
+                }
+                R[3] = f4(__int_as_float(info), __uint_as_float(id.pix), __uint_as_float(id.smp),
+                          __uint_as_float(V.view_id));
+                S.hflag[slot] = T.h.prim >= 0 ? 1 : 0;
+                // whether the path has a vertex (the shading kernels of the backward then count them)
+                if (S.nv) S.nv[slot] = T.h.prim >= 0 ? 1 : 0;
+            }
+        } else if (done) {
             alive = false;
             if (SMODE == 4 && any) {
                 // rank-one render: the path's radiance words already hold the next-event part
@@ -353,6 +426,9 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STAT
                     AC[2] = AC[3];
                 }
                 if (A.sig) sig_add(A.sig[A.g0 + slot], (uint32_t)(T.h.prim >= 0 ? NEE_OCCLUDED : NEE_VISIBLE));
+            } else if (SMODE == 5 && any) {
+                // cached backward: the vertex's record reads visible; an occluded sample marks it
+                if (T.h.prim >= 0) vtx_rec(S, Q, (info & 255) - 1, slot)[1].w = __int_as_float(1);
             } else if (SMODE >= 0 && any) {
                 const bool occ = T.h.prim >= 0;
                 const float4* H = shd_rec(S, slot);
@@ -399,28 +475,6 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STAT
                     *hwp = __int_as_float((int)hw);
                 }
                 if (A.sig) sig_add(A.sig[A.g0 + slot], (uint32_t)(occ ? NEE_OCCLUDED : NEE_VISIBLE));
-            } else if (SMODE == -2) {
-                // the camera ray's record: the whole record for a hit (ray, sensor rotation, hit,
-                // keys), the keys alone for a ray that escaped (nothing else of it is read); the
-                // keys again from the slot and the view in the info word
-                float4* R = ray_rec(S, slot);
-                const DevView V = gval(A.views, (size_t)(info >> 12));
-                PathId id;
-                path_keys(V, A.g0 + slot, id);
-                if (T.h.prim >= 0) {
-                    // rotation from the canonical frame of the light arriving along -d to the
-                    // sensor frame, kept in the record's spare words for the pixel reduction
-                    const v3 kc = -T.d;
-                    float Cs, Ss;
-                    rot_cs(kc, canon_x(kc), normalize(ld3(V.r) - kc * dot(ld3(V.r), kc)), Cs, Ss);
-                    ray_set(R, T.o, T.d, Cs, Ss);
-                    R[2] = f4(T.tb, T.h.u, T.h.v, __int_as_float(T.h.prim));
-                }
-                R[3] = f4(__int_as_float(info), __uint_as_float(id.pix), __uint_as_float(id.smp),
-                          __uint_as_float(V.view_id));
-                S.hflag[slot] = T.h.prim >= 0 ? 1 : 0;
-                // whether the path has a vertex (the shading kernels of the backward then count them)
-                if (S.nv) S.nv[slot] = T.h.prim >= 0 ? 1 : 0;
             } else {
                 float4* R = ray_rec(S, slot);
                 // the hit in one aligned 16-byte store (a hit's distance is the final tb); a miss
@@ -466,15 +520,68 @@ __global__ void __launch_bounds__(BLOCK) k_compact(WArgs A) {
     bq_flush(qh, &S.counts[7], S.hqueue, true);
 }
 
+// ============================================================================ sensor adjoint
+// dL/dI of a pixel (analyzer a, per sample) and the adjoint rows at the camera ray it gives:
+// a_c = (sum_a delta_a,c^T A_a / spp) R_s, R_s the rotation (Cs, Ss) into the sensor frame.
+DEV int64_t pixel_offset(const DevView& V, uint32_t pix) {  // (of its first analyzer, in the image)
+    const int py = (int)div_by(pix, V.inv_w), px = (int)(pix - (uint32_t)py * (uint32_t)V.width);
+    return V.out_off + ((int64_t)(py - V.crop_y0) * V.crop_w + (px - V.crop_x0)) * 12;
+}
+// (C2, S2) = (cos 2 theta, sin 2 theta) of a linear polarizer
+DEV void sensor_rows(const WArgs& A, const DevView& V, int64_t px_off, float C2, float S2, float Cs, float Ss, float* av) {
+    const float inv = 1.0f / (float)V.spp;
+    const int64_t astride = (int64_t)V.crop_w * V.crop_h * 12;
+    const float* dp = A.dout + px_off;
+    float asens[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) asens[k] = 0.0f;
+    for (int a = 0; a < V.n_analyzers; ++a) {
+        float dl[12];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) dl[k] = gval(dp, (size_t)(a * astride + k)) * inv;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            float r4[4];
+            analyzer_row(V.sensor, C2, S2, a, dl + 4 * c, r4);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) asens[4 * c + k] += r4[k];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const float a1 = asens[4 * c + 1], a2 = asens[4 * c + 2];
+        av[4 * c] = asens[4 * c];
+        av[4 * c + 1] = Cs * a1 - Ss * a2;
+        av[4 * c + 2] = Ss * a1 + Cs * a2;
+        av[4 * c + 3] = asens[4 * c + 3];
+    }
+}
+// The same in rank-one form for a linear polarizer, whose analyzer row is q' = (1, C, S, 0): a_c = sc_c rho
+// with one row rho shared by the channels.
+DEV void sensor_row1(const WArgs& A, const DevView& V, int64_t px_off, float C2, float S2, float Cs, float Ss, float* rho,
+                     float* sc) {
+    const float inv = 1.0f / (float)V.spp;
+    const float* dp = A.dout + px_off;
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+        sc[c] = 0.5f * (gval(dp, 4 * c) * inv + C2 * (gval(dp, 4 * c + 1) * inv) + S2 * (gval(dp, 4 * c + 2) * inv));
+    rho[0] = 1.0f;
+    rho[1] = Cs * C2 - Ss * S2;
+    rho[2] = Ss * C2 + Cs * S2;
+    rho[3] = 0.0f;
+}
+
 // ============================================================================ shading
 template <int MODE, bool EXT>
 // (four waves per SIMD where the registers then fit without spills)
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MODE == 1 && EXT ? 1 : 4, 8))) k_shade(WArgs A) {
+    constexpr bool ADJ = MODE == 5 || MODE == 6;  // cached backward: adjoint rows carried forward
     PathState& S = A.S;
     const int Q = A.Q;
     Call K{A.table, nullptr};
     int* qout = A.qin ? S.queue0 : S.queue1;
     const int n = S.counts[7];
+    if (ADJ && A.keep_deep && blockIdx.x == 0 && threadIdx.x == 0) S.counts[3] = n;
     __shared__ BlockQueue qn, qs;
     __shared__ CallTable tab;
     table_to_lds(&tab, A.table);
@@ -503,7 +610,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MODE
             {  // every queued ray hit a surface
                 int b = nb + 1;
                 ++cnt.c[ST_VERTICES];
-                if (MODE == 1 || MODE == 2 || MODE == 3) S.nv[slot] = (uint8_t)b;  // (the fold reads these)
+                if (MODE == 1 || MODE == 2 || MODE == 3 || ADJ) S.nv[slot] = (uint8_t)b;  // (the fold reads these)
                 Vtx x;
                 surface(W, h, o, d, x);
                 v3 so, sd;
@@ -524,7 +631,8 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MODE
                 WC w;
                 w.kind = 0;
                 float Ee[12], En[12];
-                if (MODE != 2) eval_vertex<false, EXT>(W, K, x, w, Ee, En, nullptr, nullptr);
+                if (ADJ) eval_vertex<false, EXT, false, true>(W, K, x, w, nullptr, nullptr, nullptr, nullptr);
+                else if (MODE != 2) eval_vertex<false, EXT>(W, K, x, w, Ee, En, nullptr, nullptr);
                 cont = x.lobe != LOBE_NONE && x.lobe != LOBE_INVALID;
                 shadow = x.nee == NEE_PENDING;
                 float4* H = shd_rec(S, slot);
@@ -674,6 +782,61 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MODE
                         for (int k = 0; k < 4; ++k) AC[k] = f4(beta[4 * k], beta[4 * k + 1], beta[4 * k + 2], beta[4 * k + 3]);
                         AC[4] = f4(brgb[0] * w.rgb[0], brgb[1] * w.rgb[1], brgb[2] * w.rgb[2], 0.0f);
                     }
+                } else if (ADJ) {
+                    // cached backward: what the reverse walk needs to evaluate the vertex again (32 bytes:
+                    // hit, incoming direction, visibility word), and the adjoint row of the next vertex,
+                    // a <- a W_b, started here from dL/dI (the first vertex's row is made again from it)
+                    float4* VR = vtx_rec(S, Q, b - 1, slot);
+                    VR[0] = f4(__int_as_float(h.prim | (prev_delta ? VTX_PREV_DELTA : 0)), x.tri ? h.u : x.p.x,
+                               x.tri ? h.v : x.p.y, x.p.z);
+                    VR[1] = f4(d.x, d.y, d.z, 0.0f);
+                    if (cont) {
+                        float C2 = 1.0f, S2 = 0.0f;
+                        DevView V;
+                        if (nb == 0) {
+                            V = gval(A.views, (size_t)v);
+                            if (V.sensor == SENSOR_POLARIZER) {
+                                const float th = K.p(V.theta_slot, V.theta_off);
+                                C2 = cosf(2.0f * th);
+                                S2 = sinf(2.0f * th);
+                            }
+                        }
+                        if (MODE == 6) {
+                            float rho[4], sc[3];
+                            if (nb == 0) {
+                                sensor_row1(A, V, pixel_offset(V, pix), C2, S2, r1.z, r1.w, rho, sc);
+                            } else {
+                                const float4* RR = row_rec<true>(S, Q, b - 1, slot);
+                                const float4 a0 = RR[0], a1 = RR[1];
+                                rho[0] = a0.x; rho[1] = a0.y; rho[2] = a0.z; rho[3] = a0.w;
+                                sc[0] = a1.x; sc[1] = a1.y; sc[2] = a1.z;
+                            }
+                            if (w.kind == 1) {
+                                rho[1] = rho[2] = rho[3] = 0.0f;
+                            } else {
+                                WC ws = w;
+                                ws.rgb[0] = 1.0f;
+                                float o4[4];
+                                w_row(ws, 0, rho, o4);
+                                rho[0] = o4[0]; rho[1] = o4[1]; rho[2] = o4[2]; rho[3] = o4[3];
+                            }
+                            float4* RW = row_rec<true>(S, Q, b, slot);
+                            RW[0] = f4(rho[0], rho[1], rho[2], rho[3]);
+                            RW[1] = f4(sc[0] * w.rgb[0], sc[1] * w.rgb[1], sc[2] * w.rgb[2], 0.0f);
+                        } else {
+                            float av[12], an[12];
+                            if (nb == 0) sensor_rows(A, V, pixel_offset(V, pix), C2, S2, r1.z, r1.w, av);
+                            else ld12(row_rec<false>(S, Q, b - 1, slot), av);
+#pragma unroll
+                            for (int c = 0; c < 3; ++c) w_row(w, c, av + 4 * c, an + 4 * c);
+                            st12(row_rec<false>(S, Q, b, slot), an);
+                        }
+                    }
+                    if (shadow) {  // the shadow ray in its dense 32-byte record
+                        float4* H1 = shd1_rec(S, slot);
+                        H1[0] = f4(so.x, so.y, so.z, stmax);
+                        H1[1] = f4(sd.x, sd.y, sd.z, __int_as_float(info_shd));
+                    }
                 } else {  // MODE 1
                     float4* C = cache_rec(S, A.Q, b - 1, slot);
                     const bool sphere = !x.tri;
@@ -702,7 +865,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MODE
                     // visible (traversal rewrites it for an occluded one)
                     C[7] = f4(__int_as_float(shadow ? NEE_VISIBLE : 0), 0.0f, 0.0f, 0.0f);
                 }
-                if (MODE != 4 && MODE != 1 && shadow) {  // a whole record (the Stokes words are [2..4]; partial ones measured slower)
+                if (MODE != 4 && MODE != 1 && !ADJ && shadow) {  // a whole record (the Stokes words are [2..4]; partial ones measured slower)
                     H[0] = f4(so.x, so.y, so.z, stmax);
                     H[1] = f4(sd.x, sd.y, sd.z, __int_as_float(info_shd));
                     if (MODE == 3) st12(H + 5, En);  // (the tape's E_b takes the unweighted part)
@@ -738,6 +901,7 @@ __global__ void __launch_bounds__(BLOCK) k_accum(WArgs A) {
     constexpr int NA = R1 ? 3 : 12;
     PathState& S = A.S;
     Call K{A.table, nullptr};
+    ViewRange range;
     const int lane = lane_id();
     for (int base = blockIdx.x * BLOCK + (threadIdx.x & ~(WAVE - 1)); base < A.n_chunk; base += gridDim.x * BLOCK) {
         int i = base + lane;
@@ -746,14 +910,19 @@ __global__ void __launch_bounds__(BLOCK) k_accum(WArgs A) {
         float acc[NA];
 #pragma unroll
         for (int k = 0; k < NA; ++k) acc[k] = 0.0f;
-        int v = 0, lx = 0, ly = 0;
+        int v = 0;
+        int64_t px_off = 0;  // the pixel's place in the image (first analyzer)
+        if (R1)
+            for_views(A, range, valid, A.g0 + i, [&](int vw, const DevView& V) {
+                const PathId id = path_keys(V, A.g0 + i);
+                v = vw;
+                key = ((int64_t)vw << 32) | (int64_t)id.pix;
+                px_off = V.out_off + ((int64_t)id.ly * V.crop_w + id.lx) * 12;
+            });
         if (R1 && valid) {
             // the keys from the path's index (the wavefront holds consecutive paths), and y from the
             // path's record when the path has a vertex (one byte per path says so): no ray record
             // is read, and no record of a path without radiance
-            const PathId id = path_id(A.views, A.n_views, A.g0 + i, A.g0 + base);
-            v = id.v; lx = id.lx; ly = id.ly;
-            key = ((int64_t)v << 32) | (int64_t)id.pix;
             if (S.nv[i]) {
                 const float4 y = r1_rec(S, i)[2];
                 acc[0] = y.x; acc[1] = y.y; acc[2] = y.z;
@@ -766,8 +935,8 @@ __global__ void __launch_bounds__(BLOCK) k_accum(WArgs A) {
             v = info >> 12;
             const DevView V = gval(A.views, (size_t)v);
             const uint32_t pix = __float_as_uint(r3.y);
-            const int py = (int)(pix / (uint32_t)V.width), px = (int)(pix - (uint32_t)py * (uint32_t)V.width);
-            lx = px - V.crop_x0; ly = py - V.crop_y0;
+            const int py = (int)div_by(pix, V.inv_w), px = (int)(pix - (uint32_t)py * (uint32_t)V.width);
+            px_off = V.out_off + ((int64_t)(py - V.crop_y0) * V.crop_w + (px - V.crop_x0)) * 12;
             key = ((int64_t)v << 32) | (int64_t)pix;
             if (!(info & INFO_DEAD) && (info & 255) != 0) {  // a camera ray that escaped has no radiance
                 if constexpr (!R1) {
@@ -803,7 +972,7 @@ __global__ void __launch_bounds__(BLOCK) k_accum(WArgs A) {
             const DevView V = gval(A.views, (size_t)v);
             float theta = V.sensor == SENSOR_POLARIZER ? K.p(V.theta_slot, V.theta_off) : 0.0f;
             float inv = 1.0f / (float)V.spp;
-            int64_t ob = V.out_off + ((int64_t)ly * V.crop_w + lx) * 12;
+            const int64_t ob = px_off;
             if constexpr (R1) {
                 const float C2 = cosf(2.0f * theta), S2 = sinf(2.0f * theta);
 #pragma unroll
@@ -928,6 +1097,21 @@ DEV void w_matrix(const WC& w, int c, float* m) {
     }
 }
 
+// Polarizer angles: one atomic per distinct view among the wavefront's running sums (gtheta of view
+// tkey, -1 for none).  Every lane of the wavefront calls it.
+DEV void flush_theta(const WArgs& A, const Call& K, int tkey, float gtheta) {
+    bool pending = tkey >= 0;
+    while (__ballot(pending)) {
+        unsigned long long m = __ballot(pending);
+        int leader = __ffsll((long long)m) - 1;
+        int key = __shfl(tkey, leader, WAVE);
+        bool mine = pending && tkey == key;
+        float s = wave_sum(mine ? gtheta : 0.0f);
+        if (lane_id() == leader) K.g(A.views[key].theta_slot, A.views[key].theta_off, s);
+        pending = pending && !mine;
+    }
+}
+
 // ============================================================================ backward: fold
 
 // Per path with at least one vertex: folds the cache into the suffix radiance
@@ -953,6 +1137,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HYB 
     __syncthreads();
     const int r0 = (int)((int64_t)A.n_chunk * blockIdx.x / gridDim.x);
     const int r1 = (int)((int64_t)A.n_chunk * (blockIdx.x + 1) / gridDim.x);
+    ViewRange range;
     float gtheta = 0.0f;
     int tkey = -1;
     for (int base = r0; base < r1; base += BLOCK) {
@@ -962,12 +1147,16 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HYB 
         // its ray record, which would cost a 128-byte line for 16 bytes)
         const int B = i < r1 ? (int)S.nv[i] : 0;
         float gt = 0.0f;
+        PathId id{};
+        int v = 0;
+        uint32_t view_id = 0;
+        for_views(A, range, B > 0, A.g0 + i, [&](int vw, const DevView& V) {
+            id = path_keys(V, A.g0 + i);
+            v = vw;
+            view_id = V.view_id;
+        });
         if (B > 0) {
             push = true;
-            // (keys before the fold only where the fold needs them: fewer registers live across it)
-            const int64_t gw = A.g0 + base + (int)(threadIdx.x & ~(WAVE - 1));
-            PathId id{};
-            if (HYB || PPRB) id = path_id(A.views, A.n_views, A.g0 + i, gw);
             // fold over records B-1 .. 0 (record r holds vertex r+1): the record's E words receive
             // the suffix beyond its vertex, L[r+2], so the replay of a vertex reads one record (the
             // last vertex's suffix is zero and is not stored)
@@ -977,7 +1166,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HYB 
             if (HYB) {
                 // blocks from the last to the first: re-evaluate from the block's checkpoint ray,
                 // store the suffix beyond the block, fold back to the block's first vertex
-                const DevView Vh = gval(A.views, (size_t)id.v);
+                const DevView Vh = gval(A.views, (size_t)v);
                 const DevWorld Wh = world_of(A, Vh);
                 const int kc = A.ckpt;
                 for (int j = (B + kc - 1) / kc - 1; j >= 0; --j) {
@@ -999,7 +1188,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HYB 
                 float e[12];
                 ld12(C + 4, e);
                 if (!PPRB && b < B - 1) st12(C + 4, L);
-                const float u = PPRB ? pprb_noise(A, id.pix, id.smp, id.view_id, b + 1) : 0.0f;
+                const float u = PPRB ? pprb_noise(A, id.pix, id.smp, view_id, b + 1) : 0.0f;
                 WC w;
                 w.rgb[0] = c0.x; w.rgb[1] = c0.y; w.rgb[2] = c0.z;
                 w.A = c0.w; w.B = c1.x; w.C = c1.y; w.D = c1.z;
@@ -1014,11 +1203,9 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HYB 
                 }
             }
             if (PPRB) st12(shd_rec(S, i) + 5, L);
-            if (!(HYB || PPRB)) id = path_id(A.views, A.n_views, A.g0 + i, gw);
-            const int v = id.v;
             const uint32_t pix = id.pix, smp = id.smp;
             const DevView V = gval(A.views, (size_t)v);
-            const int py = (int)(pix / (uint32_t)V.width), px = (int)(pix - (uint32_t)py * (uint32_t)V.width);
+            const int py = (int)div_by(pix, V.inv_w), px = (int)(pix - (uint32_t)py * (uint32_t)V.width);
             const int lx = px - V.crop_x0, ly = py - V.crop_y0;
             v3 o, d;
             camera_ray(V, px, py, smp, A.seed, o, d);
@@ -1026,7 +1213,8 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HYB 
             float Cs, Ss;
             rot_cs(kc, canon_x(kc), normalize(ld3(V.r) - kc * dot(ld3(V.r), kc)), Cs, Ss);
             const bool pol = V.sensor == SENSOR_POLARIZER;
-            float theta = pol ? K.p(V.theta_slot, V.theta_off) : 0.0f;
+            const float theta = pol ? K.p(V.theta_slot, V.theta_off) : 0.0f;
+            const float C2 = cosf(2.0f * theta), S2 = sinf(2.0f * theta);
             // adjoint of the pixel mean in the sensor frame: a_sens_c = sum_a delta_a,c^T A_a / spp;
             // the polarizer-angle term (one analyzer) is delta^T (dP/dtheta) R_s L[1]
             const float inv = 1.0f / (float)V.spp;
@@ -1042,13 +1230,13 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HYB 
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     float r4[4];
-                    analyzer_row(V.sensor, theta, a, dl + 4 * c, r4);
+                    analyzer_row(V.sensor, C2, S2, a, dl + 4 * c, r4);
 #pragma unroll
                     for (int k = 0; k < 4; ++k) asens[4 * c + k] += r4[k];
                     if (pol && a == 0) {
                         float l1 = L[4 * c + 1], l2 = L[4 * c + 2];
                         float ls[4] = {L[4 * c], Cs * l1 + Ss * l2, -Ss * l1 + Cs * l2, L[4 * c + 3]};
-                        gt += polarizer_dtheta(theta, dl + 4 * c, ls);
+                        gt += polarizer_dtheta(C2, S2, dl + 4 * c, ls);
                     }
                 }
             }
@@ -1064,24 +1252,13 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HYB 
             // the replay's start in one record: the camera ray's direction (its origin is the view's),
             // the info word (vertex count, view), the keys and the adjoint rows
             const int info_rs = info_make((int)S.nv[i], false, v);  // (B read again: fewer live registers)
-            if (!HYB && !PPRB && !TAPE && A.r1adj) {
-                // rank-one form: a linear polarizer's analyzer row is q' = (1, C, S, 0) and a_c = s_c q'^T
-                // rotated by R_s, with s_c = asens_c0
-                const float C2 = cosf(2.0f * theta), S2 = sinf(2.0f * theta);
-                float4* Hr = rst_rec(S, i);
-                Hr[0] = f4(d.x, d.y, d.z, __int_as_float(info_rs));
-                Hr[1] = f4(__uint_as_float(pix), __uint_as_float(smp), Cs * C2 - Ss * S2, Ss * C2 + Cs * S2);
-                Hr[2] = f4(asens[0], asens[4], asens[8], 0.0f);
-                Hr[3] = f4(0.0f, 0.0f, 0.0f, 0.0f);
-            } else {
-                float4* Hs = shd_rec(S, i);
-                Hs[0] = f4(d.x, d.y, d.z, __int_as_float(info_rs));
-                Hs[1] = f4(__uint_as_float(pix), __uint_as_float(smp), 0.0f, 0.0f);
-                st12(Hs + 2, av);
-                // the rest of the 128-byte record where nothing else fills it (a line written in part
-                // is the slower path)
-                if (!PPRB && !(HYB && A.hyb_rule)) Hs[5] = Hs[6] = Hs[7] = f4(0.0f, 0.0f, 0.0f, 0.0f);
-            }
+            float4* Hs = shd_rec(S, i);
+            Hs[0] = f4(d.x, d.y, d.z, __int_as_float(info_rs));
+            Hs[1] = f4(__uint_as_float(pix), __uint_as_float(smp), 0.0f, 0.0f);
+            st12(Hs + 2, av);
+            // the rest of the 128-byte record where nothing else fills it (a line written in part
+            // is the slower path)
+            if (!PPRB && !(HYB && A.hyb_rule)) Hs[5] = Hs[6] = Hs[7] = f4(0.0f, 0.0f, 0.0f, 0.0f);
             if (pol) {
                 if (tkey != v) {
                     if (tkey >= 0) K.g(A.views[tkey].theta_slot, A.views[tkey].theta_off, gtheta);
@@ -1095,17 +1272,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HYB 
         bq_flush(rq, &S.counts[3], S.queue0, false);
     }
     bq_flush(rq, &S.counts[3], S.queue0, true);
-    // polarizer angles: one atomic per distinct view among the wavefront's running sums
-    bool pending = tkey >= 0;
-    while (__ballot(pending)) {
-        unsigned long long m = __ballot(pending);
-        int leader = __ffsll((long long)m) - 1;
-        int key = __shfl(tkey, leader, WAVE);
-        bool mine = pending && tkey == key;
-        float s = wave_sum(mine ? gtheta : 0.0f);
-        if (lane_id() == leader) K.g(A.views[key].theta_slot, A.views[key].theta_off, s);
-        pending = pending && !mine;
-    }
+    flush_theta(A, K, tkey, gtheta);
 }
 
 // ============================================================================ gradient accumulators
@@ -1122,6 +1289,44 @@ DEV void flush_lds_grads(const WArgs& A, const Call& K) {
             double val = od >= 0 ? K.lds_d[od + q] : (double)K.lds_f[of + q];
             if (val != 0.0) unsafeAtomicAdd(A.gacc + go + q, val);
         }
+    }
+}
+
+// The workgroup's LDS gradient accumulators cleared and the call table copied to LDS (every thread
+// calls it; it ends with a workgroup barrier).
+DEV void adjoint_begin(const WArgs& A, Call& K, CallTable* tab, double* lds_grad) {
+    table_to_lds(tab, A.table);
+    K.tab = tab;
+    K.lds_d = lds_grad;
+    K.lds_f = (float*)(lds_grad + A.lds_nd);
+    for (int k = threadIdx.x; k < A.lds_nd; k += BLOCK) K.lds_d[k] = 0.0;
+    for (int k = threadIdx.x; k < A.lds_nf; k += BLOCK) K.lds_f[k] = 0.0f;
+    __syncthreads();
+}
+
+// Vertex b of a path in the cached backward's reverse walk, from its record (c0, c1): adds the
+// derivatives of E_b + W_b L[b+1] against the adjoint rows av, with L the suffix beyond the vertex (not
+// read at the last vertex), and leaves L[b] = E_b + W_b L[b+1] in L.
+DEV void adjoint_vertex(const WArgs& A, const Call& K, const DevWorld& W, uint32_t view_id, uint32_t pix, uint32_t smp,
+                        int b, bool last, float4 c0, float4 c1, const float* av, float* L) {
+    const int hw = __float_as_int(c0.x);
+    const v3 d = mk(c1.x, c1.y, c1.z);
+    Vtx x;
+    surface_at(W, hw & (VTX_PREV_DELTA - 1), c0.y, c0.z, mk(c0.y, c0.z, c0.w), x);
+    v3 so, sd;
+    float stmax;
+    vertex_setup<false>(W, K, view_id, A.seed, pix, smp, b, A.max_depth, A.flags, (hw & VTX_PREV_DELTA) != 0, d, x, so, sd,
+                      stmax, last);
+    if (x.nee == NEE_PENDING) x.nee = __float_as_int(c1.w) ? NEE_OCCLUDED : NEE_VISIBLE;
+    WC w;
+    float Ee[12], En[12];
+    eval_vertex<true, false>(W, K, x, w, Ee, En, av, L);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        float o4[4];
+        w_apply(w, c, L + 4 * c, o4);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) L[4 * c + k] = (Ee[4 * c + k] + En[4 * c + k]) + o4[k];
     }
 }
 
@@ -1258,13 +1463,7 @@ __global__ void __launch_bounds__(BLOCK) k_replay(WArgs A) {
     const int Q = A.Q;
     Call K{A.table, A.gacc};
     __shared__ CallTable tab;
-    table_to_lds(&tab, A.table);
-    K.tab = &tab;
-    K.lds_d = lds_grad;
-    K.lds_f = (float*)(lds_grad + A.lds_nd);
-    for (int k = threadIdx.x; k < A.lds_nd; k += BLOCK) K.lds_d[k] = 0.0;
-    for (int k = threadIdx.x; k < A.lds_nf; k += BLOCK) K.lds_f[k] = 0.0f;
-    __syncthreads();
+    adjoint_begin(A, K, &tab, lds_grad);
     const int n = S.counts[3];
     WaveFetch F(n);
     int slot = -1, b = 0, B = 0, v = 0;
@@ -1286,8 +1485,7 @@ __global__ void __launch_bounds__(BLOCK) k_replay(WArgs A) {
         if (idx >= 0) {
             slot = S.queue0[idx];
             // the path's start as the fold left it in the shadow-record array (one record per path)
-            const bool r1s = !HYB && !PPRB && A.r1adj;  // (the 64-byte rank-one form)
-            const float4* H = r1s ? rst_rec(S, slot) : shd_rec(S, slot);
+            const float4* H = shd_rec(S, slot);
             const float4 h0 = H[0], h1 = H[1];
             const int info = __float_as_int(h0.w);
             B = info & 255;
@@ -1296,16 +1494,7 @@ __global__ void __launch_bounds__(BLOCK) k_replay(WArgs A) {
             prev_delta = false;
             pix = __float_as_uint(h1.x);
             smp = __float_as_uint(h1.y);
-            if (r1s) {
-                const float4 h2 = H[2];
-                const float sc[3] = {h2.x, h2.y, h2.z};
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    av[4 * c] = sc[c]; av[4 * c + 1] = sc[c] * h1.z; av[4 * c + 2] = sc[c] * h1.w; av[4 * c + 3] = 0.0f;
-                }
-            } else {
-                ld12(H + 2, av);
-            }
+            ld12(H + 2, av);
             if (PPRB) ld12(H + 5, Lcur);
             d = mk(h0.x, h0.y, h0.z);
             o = ld3(gval(A.views, (size_t)v).o);  // (a pinhole camera's rays leave the view's origin)
@@ -1430,7 +1619,166 @@ __global__ void __launch_bounds__(BLOCK) k_replay(WArgs A) {
     flush_lds_grads(A, K);
 }
 
-#ifndef PPT_EXT_TU  // (non-template kernels and the host side: in the main compilation unit only)
+#ifndef PPT_EXT_TU  // (in the main compilation unit only)
+// ============================================================================ cached backward: reverse walk
+// The gradient of the cached backward (Sec. 4.3, Fig. 2) without a separate fold: the forward pass of
+// the backward carries each path's adjoint row a_b (known from the start, since dL/dI is an input)
+// and keeps it per vertex, so one walk from the last vertex to the first can evaluate every vertex
+// once, differentiate E_b + W_b L[b+1] against a_b, and advance the suffix L[b] = E_b + W_b L[b+1] in
+// registers.  No Mueller matrix is inverted and no suffix goes through memory, except the one
+// beyond the first vertex.  Against the fold (read 96 B, write 48 B of a 128-byte record per vertex)
+// followed by a forward replay (read it again) this moves 32 B written and read per first vertex and
+// 64 to 80 B per later one.
+//
+// k_adjoint_deep walks the paths of two or more vertices (the hit queue of the second bounce) down to
+// their second vertex: persistent, a lane takes the next path as soon as its own is walked, and
+// leaves the suffix L[2] in the path's ray record, which nothing reads any more.
+template <bool R1>
+__global__ void __launch_bounds__(BLOCK) k_adjoint_deep(WArgs A) {
+    extern __shared__ double lds_grad[];
+    PathState& S = A.S;
+    const int Q = A.Q;
+    Call K{A.table, A.gacc};
+    __shared__ CallTable tab;
+    const int n = S.counts[3];
+    if (!fetch_active(n) || n == 0) return;
+    adjoint_begin(A, K, &tab, lds_grad);
+    WaveFetch F(n);
+    int slot = -1, b = 0, B = 0, v = 0;
+    uint32_t pix = 0, smp = 0, view_id = 0;
+    float L[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) L[k] = 0.0f;
+    while (true) {
+        const int idx = F.take(slot < 0, n, &S.counts[4]);
+        if (idx >= 0) {
+            slot = S.dqueue[idx];
+            const float4 r3 = ray_rec(S, slot)[3];
+            const int info = __float_as_int(r3.x);
+            B = b = info & 255;
+            v = info >> 12;
+            pix = __float_as_uint(r3.y);
+            smp = __float_as_uint(r3.z);
+            view_id = __float_as_uint(r3.w);
+#pragma unroll
+            for (int k = 0; k < 12; ++k) L[k] = 0.0f;
+        }
+        if (!__any(slot >= 0)) break;
+        if (slot >= 0) {
+            const float4* C = vtx_rec(S, Q, b - 1, slot);
+            const float4 c0 = C[0], c1 = C[1];
+            float av[12];
+            if (R1) {
+                const float4* RR = row_rec<true>(S, Q, b - 1, slot);
+                const float4 a0 = RR[0], a1 = RR[1];
+                const float sc[3] = {a1.x, a1.y, a1.z};
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    av[4 * c] = sc[c] * a0.x; av[4 * c + 1] = sc[c] * a0.y;
+                    av[4 * c + 2] = sc[c] * a0.z; av[4 * c + 3] = sc[c] * a0.w;
+                }
+            } else {
+                ld12(row_rec<false>(S, Q, b - 1, slot), av);
+            }
+            K.coherent = false;
+            adjoint_vertex(A, K, world_of(A, v), view_id, pix, smp, b, b == B, c0, c1, av, L);
+            if (--b == 1) {
+                st12(ray_rec(S, slot), L);
+                slot = -1;
+            }
+        }
+    }
+    flush_lds_grads(A, K);
+}
+// k_adjoint_first evaluates the first vertex of every path, a wavefront's lanes holding consecutive
+// paths (the samples of one pixel or two: one material, one texel cell, no idle lanes beside the
+// escaped camera rays), with the suffix beyond it from k_adjoint_deep, and adds the polarizer-angle
+// term delta^T (dP/dtheta) R_s L[1].  A wavefront takes runs of ADJ_RUN paths from a counter (a fixed
+// stride walks the same part of every view of a batch of equal views, and the wavefronts on its
+// objects end last: 5.1 ms against 4.0 ms on the 128-view batch), long enough that its lanes seldom change
+// view and keep the angle term in a register until they do.
+constexpr int ADJ_RUN = 8 * WAVE;
+__global__ void __launch_bounds__(BLOCK) k_adjoint_first(WArgs A) {
+    extern __shared__ double lds_grad[];
+    PathState& S = A.S;
+    const int Q = A.Q;
+    Call K{A.table, A.gacc};
+    const Call KG{A.table, A.gacc};  // (the angle terms: straight to the FP64 accumulator)
+    __shared__ CallTable tab;
+    adjoint_begin(A, K, &tab, lds_grad);
+    K.coherent = true;
+    const int n = A.n_chunk;
+    const int waves = (int)gridDim.x * (BLOCK / WAVE);
+    // (shorter where the paths are few: eight runs per wavefront even out their cost)
+    const int run = min(ADJ_RUN, (n / (8 * waves) + WAVE) & ~(WAVE - 1));
+    ViewRange range;
+    float gtheta = 0.0f, C2 = 1.0f, S2 = 0.0f;
+    int tkey = -1, angle_of = -1;
+    while (true) {
+        int r0 = 0;
+        if (lane_id() == 0) r0 = atomicAdd(&S.counts[6], run);
+        r0 = __builtin_amdgcn_readfirstlane(r0);
+        if (r0 >= n) break;
+        for (int base = r0; base < min(r0 + run, n); base += WAVE) {
+            const int i = base + lane_id();
+            const int B = i < n ? (int)S.nv[i] : 0;
+            int v = -1;
+            float gt = 0.0f;
+            bool pol = false;
+            for_views(A, range, B > 0, A.g0 + i, [&](int vw, const DevView& V) {
+                v = vw;
+                const float4* C = vtx_rec(S, Q, 0, i);
+                const float4 c0 = C[0], c1 = C[1];
+                float L[12];
+                if (B > 1) {
+                    ld12(ray_rec(S, i), L);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 12; ++k) L[k] = 0.0f;
+                }
+                const PathId id = path_keys(V, A.g0 + i);
+                pol = V.sensor == SENSOR_POLARIZER;
+                if (pol && angle_of != vw) {  // (the polarizer's angle again only where the view changes)
+                    const float theta = K.p(V.theta_slot, V.theta_off);
+                    C2 = cosf(2.0f * theta);
+                    S2 = sinf(2.0f * theta);
+                    angle_of = vw;
+                }
+                const int64_t px_off = V.out_off + ((int64_t)id.ly * V.crop_w + id.lx) * 12;
+                const v3 kc = mk(-c1.x, -c1.y, -c1.z);
+                float Cs, Ss;
+                rot_cs(kc, canon_x(kc), normalize(ld3(V.r) - kc * dot(ld3(V.r), kc)), Cs, Ss);
+                float av[12];
+                sensor_rows(A, V, px_off, C2, S2, Cs, Ss, av);
+                const DevWorld W = A.one_world ? A.world0 : cval(A.worlds, V.world);
+                adjoint_vertex(A, K, W, V.view_id, id.pix, id.smp, 1, B == 1, c0, c1, av, L);
+                if (pol) {
+                    const float inv = 1.0f / (float)V.spp;
+                    const float* dp = A.dout + px_off;
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        const float l1 = L[4 * c + 1], l2 = L[4 * c + 2];
+                        const float ls[4] = {L[4 * c], Cs * l1 + Ss * l2, -Ss * l1 + Cs * l2, L[4 * c + 3]};
+                        const float dl[3] = {gval(dp, 4 * c) * inv, gval(dp, 4 * c + 1) * inv, gval(dp, 4 * c + 2) * inv};
+                        gt += polarizer_dtheta(C2, S2, dl, ls);
+                    }
+                }
+            });
+            if (__any(pol && tkey >= 0 && tkey != v)) {
+                flush_theta(A, KG, tkey, gtheta);
+                tkey = -1;
+                gtheta = 0.0f;
+            }
+            if (pol) {
+                tkey = v;
+                gtheta += gt;
+            }
+        }
+    }
+    flush_theta(A, KG, tkey, gtheta);
+    flush_lds_grads(A, K);
+}
+
 // ============================================================================ P-RB comparator
 // Polarized radiative backpropagation (the comparator of Sec. 5.1): the replay reads, for each vertex
 // b1, an independent estimate of the suffix beyond it instead of the cached one.  Pass b1 traces,
@@ -1521,13 +1869,7 @@ __global__ void __launch_bounds__(BLOCK) k_tape_reverse(WArgs A) {
     const int Q = A.Q;
     Call K{A.table, A.gacc};
     __shared__ CallTable tab;
-    table_to_lds(&tab, A.table);
-    K.tab = &tab;
-    K.lds_d = lds_grad;
-    K.lds_f = (float*)(lds_grad + A.lds_nd);
-    for (int k = threadIdx.x; k < A.lds_nd; k += BLOCK) K.lds_d[k] = 0.0;
-    for (int k = threadIdx.x; k < A.lds_nf; k += BLOCK) K.lds_f[k] = 0.0f;
-    __syncthreads();
+    adjoint_begin(A, K, &tab, lds_grad);
     const int n = S.counts[3];
     WaveFetch F(n);
     int slot = -1, b = 0, v = 0;
@@ -1758,10 +2100,12 @@ static void launch_extend(const WArgs& a, int grid, size_t lds, hipStream_t s) {
 
 // One chunk of paths through every bounce.  mode 0: render, 1: backward.  M is told the family
 // of every kernel before its launch (event timing).
-hipError_t launch_chunk(WArgs a, int mode, const LaunchGrid& G, hipStream_t s, const LaunchMarker& M) {
-    // the backward's rank-one replay start (cached replay; the comparators and the hybrid keep the
-    // general record)
-    a.r1adj = mode == 1 && a.r1 && a.ckpt == 0 && !a.pprb && !a.tape && !a.prb ? 1 : 0;
+hipError_t launch_chunk(WArgs a, const PathState& S2, int mode, const LaunchGrid& G, hipStream_t s, const LaunchMarker& M) {
+    // (with the light-stage features the fold and forward replay stay: the gradient of a normal-mapped smooth
+    // dielectric runs through its s/p rotators, which amplify the rounding of the ray's direction, and
+    // the reverse walk's differs from the replay's in the last bits: one texel moved by 5e-4)
+    a.adj = mode == 1 && a.ckpt == 0 && !a.ext && !a.pprb && !a.tape && !a.prb ? 1 : 0;
+    a.r1adj = a.adj && a.r1 ? 1 : 0;
     if (mode != 0 || !a.S.nv) a.r1 = 0;  // (the rank-one record is the render's, with its vertex flags)
     size_t lds = (size_t)a.stack_cap * BLOCK * sizeof(int);
     M(KF_OTHER, s);
@@ -1775,6 +2119,11 @@ hipError_t launch_chunk(WArgs a, int mode, const LaunchGrid& G, hipStream_t s, c
     for (int b = 1; b <= a.max_depth; ++b) {
         a.qin = (b - 1) & 1;
         a.first = b == 1;
+        // (cached backward: the second bounce's hits are the paths of two or more vertices, the
+        // reverse walk's queue)
+        a.keep_deep = a.adj && b == 2;
+        int* const hqueue = a.S.hqueue;
+        if (a.keep_deep) a.S.hqueue = a.S.dqueue;
         M(KF_COMPACT, s);
         if (mode == 0) hipLaunchKernelGGL(k_compact<0>, dim3(gb), dim3(BLOCK), 0, s, a);
         else hipLaunchKernelGGL(k_compact<1>, dim3(gb), dim3(BLOCK), 0, s, a);
@@ -1785,6 +2134,9 @@ hipError_t launch_chunk(WArgs a, int mode, const LaunchGrid& G, hipStream_t s, c
             hipLaunchKernelGGL((k_shade<4, false>), dim3(sg), dim3(BLOCK), 0, s, a);
         } else if (mode == 1 && a.tape) {
             hipLaunchKernelGGL((k_shade<3, false>), dim3(sg), dim3(BLOCK), 0, s, a);
+        } else if (a.adj) {
+            if (a.r1adj) hipLaunchKernelGGL((k_shade<6, false>), dim3(sg), dim3(BLOCK), 0, s, a);
+            else hipLaunchKernelGGL((k_shade<5, false>), dim3(sg), dim3(BLOCK), 0, s, a);
         } else if (a.ext) {
             if (mode == 0) hipLaunchKernelGGL((k_shade<0, true>), dim3(sg), dim3(BLOCK), 0, s, a);
             else if (a.ckpt > 0) hipLaunchKernelGGL((k_shade<2, true>), dim3(sg), dim3(BLOCK), 0, s, a);
@@ -1794,6 +2146,7 @@ hipError_t launch_chunk(WArgs a, int mode, const LaunchGrid& G, hipStream_t s, c
             else if (a.ckpt > 0) hipLaunchKernelGGL((k_shade<2, false>), dim3(sg), dim3(BLOCK), 0, s, a);
             else hipLaunchKernelGGL((k_shade<1, false>), dim3(sg), dim3(BLOCK), 0, s, a);
         }
+        a.S.hqueue = hqueue;
         // the rays of bounce b + 1 and the shadow rays of bounce b in one traversal launch (a
         // vertex at the maximum depth starts neither, so nothing follows the last bounce)
         if (b < a.max_depth) {
@@ -1802,6 +2155,7 @@ hipError_t launch_chunk(WArgs a, int mode, const LaunchGrid& G, hipStream_t s, c
             M(KF_EXTEND, s);
             if (mode == 0 && a.r1) launch_extend<4>(a, xg, lds, s);
             else if (mode == 0) launch_extend<0>(a, xg, lds, s);
+            else if (a.adj) launch_extend<5>(a, xg, lds, s);
             else if (a.tape) launch_extend<3>(a, xg, lds, s);
             else if (a.ckpt > 0) launch_extend<2>(a, xg, lds, s);
             else launch_extend<1>(a, xg, lds, s);
@@ -1815,6 +2169,21 @@ hipError_t launch_chunk(WArgs a, int mode, const LaunchGrid& G, hipStream_t s, c
         }
     } else {
         size_t glds = (size_t)a.lds_nd * sizeof(double) + (size_t)a.lds_nf * sizeof(float);
+        if (a.adj) {
+            // grids: as many workgroups per compute unit as this call's accumulator size and the
+            // variant's registers allow
+            if (a.max_depth > 1) {
+                M(KF_FOLD, s);
+                const void* fn = a.r1adj ? (const void*)k_adjoint_deep<true> : (const void*)k_adjoint_deep<false>;
+                const int dg = resident_grid(fn, glds, a.n_chunk, G);
+                if (a.r1adj) hipLaunchKernelGGL(k_adjoint_deep<true>, dim3(dg), dim3(BLOCK), glds, s, a);
+                else hipLaunchKernelGGL(k_adjoint_deep<false>, dim3(dg), dim3(BLOCK), glds, s, a);
+            }
+            M(KF_REPLAY, s);
+            const int fg = resident_grid((const void*)k_adjoint_first, glds, a.n_chunk, G);
+            hipLaunchKernelGGL(k_adjoint_first, dim3(fg), dim3(BLOCK), glds, s, a);
+            return hipGetLastError();
+        }
         M(KF_FOLD, s);
         // each fold workgroup takes one contiguous slice of the chunk, so the grid is the resident
         // one (a second, partial round of workgroups would leave most of the GPU idle)
@@ -1829,7 +2198,7 @@ hipError_t launch_chunk(WArgs a, int mode, const LaunchGrid& G, hipStream_t s, c
         else hipLaunchKernelGGL((k_fold<false, false>), dim3(fg), dim3(BLOCK), 0, s, a);
         if (a.prb) {  // P-RB: independent suffix estimates, one sub-path pass per vertex index
             WArgs b2 = a;
-            b2.S = a.S2;
+            b2.S = S2;
             b2.stats = nullptr;
             b2.sig = nullptr;
             b2.mask = nullptr;
@@ -1837,7 +2206,7 @@ hipError_t launch_chunk(WArgs a, int mode, const LaunchGrid& G, hipStream_t s, c
             for (int b1 = 1; b1 < a.max_depth; ++b1) {
                 M(KF_OTHER, s);
                 hipLaunchKernelGGL(k_reset_counts, dim3(1), dim3(64), 0, s, b2.S.counts);
-                hipLaunchKernelGGL(k_prb_start, dim3(gb), dim3(BLOCK), 0, s, a, a.S2, b1);
+                hipLaunchKernelGGL(k_prb_start, dim3(gb), dim3(BLOCK), 0, s, a, S2, b1);
                 b2.seed = prb_seed_host(a.seed, (uint32_t)(b1 + 1));
                 b2.qin = 0;
                 b2.first = 1;
@@ -1859,7 +2228,7 @@ hipError_t launch_chunk(WArgs a, int mode, const LaunchGrid& G, hipStream_t s, c
                     }
                 }
                 M(KF_OTHER, s);
-                hipLaunchKernelGGL(k_prb_store, dim3(gb), dim3(BLOCK), 0, s, a, a.S2, b1);
+                hipLaunchKernelGGL(k_prb_store, dim3(gb), dim3(BLOCK), 0, s, a, S2, b1);
             }
         }
         M(KF_REPLAY, s);
