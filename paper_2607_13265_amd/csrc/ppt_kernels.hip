@@ -89,19 +89,34 @@ DEV void sig_add(uint64_t& h, uint32_t x) {
 // down to whole wavefronts left up to half of a mid-sized queue to the atomic batches, whose
 // early round ends for refill made such launches slower).  A wavefront gives its positions, in
 // order, to its lanes that have no work; every lane of the wavefront must call take().
+//
+// Traversal spreads a queue that does not fill the GPU (least > 0): with fewer rays than lanes, a launch
+// lasts as long as its slowest wavefront, whose lanes wait for each other's descents and leaves, so
+// a wavefront takes only n / SPREAD_WAVES positions, and at least `least`: 2 in a scene whose tree is deep
+// enough for rays to differ, 8 in a shallow one (fewer cost the 3-sphere scene 3 %).  A 5,917-path preview
+// 304 -> 229 us, a 28,512-path step 1040 -> 873 us, the 3-sphere step 185 -> 180 us; one ray per wavefront
+// gains 2 % more and costs the smallest scene 10 %; from SPREAD_WAVES full wavefronts on, two per SIMD,
+// full wavefronts are the faster.
 constexpr int FETCH_MIN = WAVE, FETCH_BATCH = 4 * WAVE;
-DEV int fetch_blocks(int n) { return max(1, min((int)gridDim.x, (n + BLOCK - 1) / BLOCK)); }
-DEV bool fetch_active(int n) { return (int)blockIdx.x < fetch_blocks(n); }
+constexpr int SPREAD_DEEP = 2, SPREAD_SHALLOW = 8, SPREAD_WAVES = 2048, SHALLOW_STACK = 10;
+DEV int spread_least(const WArgs& A) { return A.stack_cap > SHALLOW_STACK ? SPREAD_DEEP : SPREAD_SHALLOW; }
+DEV int fetch_min(int n, int least) { return least ? max(least, min(FETCH_MIN, (n + SPREAD_WAVES - 1) / SPREAD_WAVES)) : FETCH_MIN; }
+DEV int fetch_blocks(int n, int per_wave) {
+    const int per_block = per_wave * (BLOCK / WAVE);
+    return max(1, min((int)gridDim.x, (n + per_block - 1) / per_block));
+}
+DEV bool fetch_active(int n, int least = 0) { return (int)blockIdx.x < fetch_blocks(n, fetch_min(n, least)); }
 struct WaveFetch {
     int c, cend;    // the wavefront's current batch [c, cend)
     int stat;       // positions covered by the static batches
     bool exhausted;
-    DEV explicit WaveFetch(int n) {
-        const int waves = fetch_blocks(n) * (BLOCK / WAVE);
+    DEV explicit WaveFetch(int n, int least = 0) {
+        const int smin = fetch_min(n, least);
+        const int waves = fetch_blocks(n, smin) * (BLOCK / WAVE);
         // (readfirstlane: the wavefront's number, known uniform, keeps the fetch state in scalar registers)
         const int w = blockIdx.x * (BLOCK / WAVE) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
         int sb = (n + waves - 1) / waves;
-        sb = sb < FETCH_MIN ? FETCH_MIN : (sb > FETCH_BATCH ? FETCH_BATCH : sb);
+        sb = sb < smin ? smin : (sb > FETCH_BATCH ? FETCH_BATCH : sb);
         stat = waves * sb;
         c = min(w * sb, n);
         cend = min(c + sb, n);
@@ -314,9 +329,10 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STAT
     const int ne = A.first ? A.n_chunk : S.counts[A.qin];
     const int ns = SMODE >= 0 ? S.counts[2] : 0;
     const int n = ns + ne;
-    if (!fetch_active(n)) return;
+    const int least = spread_least(A);
+    if (!fetch_active(n, least)) return;
     Count cnt;
-    WaveFetch F(n);
+    WaveFetch F(n, least);
     Trav T;
     bool alive = false, any = false;
     int slot = -1, info = 0;
@@ -2111,7 +2127,8 @@ hipError_t launch_chunk(WArgs a, const PathState& S2, int mode, const LaunchGrid
     M(KF_OTHER, s);
     hipLaunchKernelGGL(k_reset_counts, dim3(1), dim3(64), 0, s, a.S.counts);
     int gb = blocks_for(a.n_chunk, G.other);
-    const int xg = blocks_for(a.n_chunk, a.stats ? G.extend_st : G.extend);
+    // (traversal's grid: enough workgroups for the most spread queue)
+    const int xg = blocks_for((int64_t)a.n_chunk * (WAVE / SPREAD_DEEP), a.stats ? G.extend_st : G.extend);
     a.qin = 0;
     a.first = 1;
     M(KF_EXTEND, s);
