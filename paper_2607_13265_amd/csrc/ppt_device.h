@@ -570,6 +570,19 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 DEV float half_lo(float w) { return (float)__builtin_bit_cast(f16x2, w).x; }
 DEV float half_hi(float w) { return (float)__builtin_bit_cast(f16x2, w).y; }
 
+DEV float near_far(float w, uint32_t rot) {  // (lo, hi) halves swapped where rot = 16
+    return __uint_as_float(__builtin_amdgcn_alignbit(__float_as_uint(w), __float_as_uint(w), rot));
+}
+
+// The smallest of four values that are never NaN, by the plain instructions (fminf first quiets a value
+// that could be a signalling NaN, one more instruction for the ray's length in every node step).
+DEV float min4(float a, float b, float c, float d) {
+    float m, r;
+    asm("v_min_f32 %0, %1, %2" : "=v"(m) : "v"(c), "v"(d));
+    asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(m));
+    return r;
+}
+
 // Reciprocal direction for the slab tests, by the hardware reciprocal (1 ulp): the node boxes are
 // rounded outward to half floats, a margin far wider than the reciprocal's error.
 DEV v3 safe_inv(v3 d) {
@@ -619,10 +632,12 @@ DEV bool hit_prim(const float4* prims, int i, v3 o, v3 d, float& tb, Hit& h) {
 // two entries of padding below the bottom let the node step read the two top entries and write the
 // next one at fixed offsets from one address.  The padding holds TRAV_DONE (trav_stack_init, once
 // per lane; nothing writes it afterwards), so a pop below the bottom reads the end of traversal.
+// (Below the bottom the depth itself may become -1: that pop reads TRAV_DONE, and nothing follows it.)
 constexpr int TRAV_DONE = 0x7fffffff;
 DEV void trav_stack_init(int* stack) { stack[0] = TRAV_DONE; stack[BLOCK] = TRAV_DONE; }
 struct Trav {
     v3 o, d, id, ood;
+    uint32_t rx, ry, rz;  // rotation of a bound pair into (near, far) along each axis: 16 where the ray descends it
     float tb;
     int ref;   // >= 0 inner node, < 0 leaf, TRAV_DONE when the stack is exhausted
     int leaf;  // parked leaf (< 0) or none
@@ -635,6 +650,9 @@ DEV void trav_begin(Trav& T, const DevWorld& W, v3 o, v3 d, float tmax) {
     T.o = o; T.d = d;
     T.id = safe_inv(d);
     T.ood = mk(o.x * T.id.x, o.y * T.id.y, o.z * T.id.z);
+    T.rx = T.id.x < 0.0f ? 16u : 0u;
+    T.ry = T.id.y < 0.0f ? 16u : 0u;
+    T.rz = T.id.z < 0.0f ? 16u : 0u;
     T.tb = tmax;
     T.sp = 0;
     T.h.prim = -1; T.h.t = 0.0f; T.h.u = 0.0f; T.h.v = 0.0f;
@@ -644,6 +662,10 @@ DEV void trav_begin(Trav& T, const DevWorld& W, v3 o, v3 d, float tmax) {
     T.ref = W.n_prims == 0 ? TRAV_DONE : W.root;
     if (T.ref < 0) { T.leaf = T.ref; T.ref = TRAV_DONE; }
 }
+// Bound: the address unit and vector L1 (busy 86 % of the time on the 128-view batch; each lane's node is two
+// 16-byte gathers) together with instruction issue (72 %).  The node step is kept at 47 vector
+// instructions for that (61 with a minimum and maximum per axis, separate tests for a leaf that is
+// reached and one that is popped, and a clamped depth: traversal 13.8 -> 13.1 ms a pass).
 // One round of while-while traversal with speculative leaf postponement (Aila & Laine 2009):
 // the lanes of the wavefront in this call descend, a lane that reaches a leaf parks it and keeps
 // descending until every such lane holds a leaf (or, with refill, until fewer than a quarter of
@@ -664,46 +686,47 @@ DEV bool trav_round(Trav& T, bool any, uint32_t& n_nodes, uint32_t& n_prims, int
         const float4* nd = T.nodes + 2 * T.ref;
         const float4 q0 = ldg4(nd, 0), q1 = ldg4(nd, 1);
         __builtin_amdgcn_sched_barrier(0);  // (keeps the stack reads ahead of the wait for the node)
+        // the bounds of an axis in (near, far) order: the same distances as the smaller and larger of
+        // the two (the product is monotonic), for one rotation instead of a minimum and a maximum
         const v3 id = T.id, ood = T.ood;
-        float a0 = fmaf(half_lo(q0.x), id.x, -ood.x), a1 = fmaf(half_hi(q0.x), id.x, -ood.x);
-        float b0 = fmaf(half_lo(q0.y), id.y, -ood.y), b1 = fmaf(half_hi(q0.y), id.y, -ood.y);
-        float c0 = fmaf(half_lo(q1.x), id.z, -ood.z), c1 = fmaf(half_hi(q1.x), id.z, -ood.z);
-        float tnL = fmaxf(fmaxf(fminf(a0, a1), fminf(b0, b1)), fmaxf(fminf(c0, c1), 0.0f));
-        float txL = fminf(fminf(fmaxf(a0, a1), fmaxf(b0, b1)), fminf(fmaxf(c0, c1), T.tb));
-        float e0 = fmaf(half_lo(q0.z), id.x, -ood.x), e1 = fmaf(half_hi(q0.z), id.x, -ood.x);
-        float f0 = fmaf(half_lo(q0.w), id.y, -ood.y), f1 = fmaf(half_hi(q0.w), id.y, -ood.y);
-        float g0 = fmaf(half_lo(q1.y), id.z, -ood.z), g1 = fmaf(half_hi(q1.y), id.z, -ood.z);
-        float tnR = fmaxf(fmaxf(fminf(e0, e1), fminf(f0, f1)), fmaxf(fminf(g0, g1), 0.0f));
-        float txR = fminf(fminf(fmaxf(e0, e1), fmaxf(f0, f1)), fminf(fmaxf(g0, g1), T.tb));
+        const float lx = near_far(q0.x, T.rx), ly = near_far(q0.y, T.ry), lz = near_far(q1.x, T.rz);
+        const float rx = near_far(q0.z, T.rx), ry = near_far(q0.w, T.ry), rz = near_far(q1.y, T.rz);
+        const float tnL = fmaxf(fmaxf(fmaf(half_lo(lx), id.x, -ood.x), fmaf(half_lo(ly), id.y, -ood.y)),
+                                fmaxf(fmaf(half_lo(lz), id.z, -ood.z), 0.0f));
+        const float txL = min4(fmaf(half_hi(lx), id.x, -ood.x), fmaf(half_hi(ly), id.y, -ood.y),
+                               fmaf(half_hi(lz), id.z, -ood.z), T.tb);
+        const float tnR = fmaxf(fmaxf(fmaf(half_lo(rx), id.x, -ood.x), fmaf(half_lo(ry), id.y, -ood.y)),
+                                fmaxf(fmaf(half_lo(rz), id.z, -ood.z), 0.0f));
+        const float txR = min4(fmaf(half_hi(rx), id.x, -ood.x), fmaf(half_hi(ry), id.y, -ood.y),
+                               fmaf(half_hi(rz), id.z, -ood.z), T.tb);
         const bool hL = tnL <= txL, hR = tnR <= txR;
         const int rL = __float_as_int(q1.z), rR = __float_as_int(q1.w);
         // next reference, by selects: the nearer hit child (the farther one is pushed), else the
-        // top of the stack; a leaf is parked (when none is) and the descent goes on past it.  The
-        // two pops this can need were read above (pushing and at once popping the farther child
-        // of a parked nearer leaf is skipped).
+        // top of the stack; a leaf is parked (when none is) and the descent goes on past it, to the
+        // farther child or the next stack entry (pushing and at once popping the farther child of a
+        // parked nearer leaf is skipped).  The two pops this can need were read above.
+        const bool both = hL && hR, none = !hL && !hR;
         const bool goR = hR & (!hL | (tnR < tnL));  // (bitwise: no branch)
         const int near = goR ? rR : rL, far = goR ? rL : rR;
-        const bool both = hL && hR, none = !hL && !hR, free_slot = T.leaf == 0;
-        const int pop1 = top1, pop2 = top2;  // (below the bottom: the padding, which holds TRAV_DONE)
-        const bool park_near = !none && near < 0 && free_slot;
-        const bool park_pop = none && pop1 < 0 && free_slot;
-        const bool push = both && !park_near;
+        const int next = none ? top1 : near;  // (below the bottom: the padding, which holds TRAV_DONE)
+        const bool park = next < 0 && T.leaf == 0;
         // written whether or not it is pushed: entry sp is above the top unless this pushes, and it
         // is in the stack (at an inner node of depth d at most d entries are held, d < BVH depth,
         // and the capacity is the BVH depth + 2 entries, padding included)
         sb[2 * BLOCK] = far;
-        int ref = park_near ? (both ? far : pop1) : near;
-        ref = none ? (park_pop ? pop2 : pop1) : ref;
-        T.ref = ref;
-        T.leaf = park_near ? near : (park_pop ? pop1 : T.leaf);
-        const int npop = none ? (park_pop ? 2 : 1) : (park_near && !both ? 1 : 0);
-        T.sp = push ? sp + 1 : max(sp - npop, 0);
+        const int after = both ? far : (none ? top2 : top1);
+        T.ref = park ? after : next;
+        T.leaf = park ? next : T.leaf;
+        // (pushed: one more entry; popped: one less; a parked leaf takes one of them back or pops one more)
+        T.sp = sp + (both ? 1 : none ? -1 : 0) - (park ? 1 : 0);
         // the round ends when every lane in this loop holds a leaf, or, while queued rays remain
         // (refill, wave-uniform), when fewer than a quarter of the wavefront's lanes still descend,
         // so that the finished lanes take new rays (thresholds of 1/8, 1/2 and 3/4, and no early
         // end, measured slower); one wave-uniform test
-        const unsigned long long looping = __ballot(true), unparked = __ballot(T.leaf == 0);
-        if (unparked == 0ull || (refill && (int)__builtin_popcountll(looping) < WAVE / 4)) break;
+        const uint64_t looping = __ballot(true), unparked = __ballot(T.leaf == 0);
+        int n_looping = __popcll(looping);
+        asm("" : "+s"(n_looping));  // (kept a scalar 32-bit count: it was compared as a 64-bit vector value)
+        if (unparked == 0ull || (refill && n_looping < WAVE / 4)) break;
     }
     while (T.leaf < 0) {
         int enc = ~T.leaf;
@@ -719,7 +742,8 @@ DEV bool trav_round(Trav& T, bool any, uint32_t& n_nodes, uint32_t& n_prims, int
         T.leaf = 0;
         if (T.ref < 0) {  // the node loop stopped on a second leaf
             T.leaf = T.ref;
-            T.ref = T.sp ? stack[(--T.sp + 2) * BLOCK] : TRAV_DONE;
+            T.ref = stack[(T.sp + 1) * BLOCK];
+            --T.sp;
         }
     }
     return T.ref == TRAV_DONE;

@@ -314,7 +314,7 @@ __global__ void k_reset_counts(int* counts) {
 // STATS: the launch adds to the work counters (A.stats set); without them a lane holds no counter
 // registers.
 template <int SMODE, bool STATS>
-__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STATS ? 1 : 8, 8))) k_extend(WArgs A) {
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STATS ? 7 : 8, 8))) k_extend(WArgs A) {
     extern __shared__ int lds_stack[];
     int* stack = lds_stack + threadIdx.x;
     trav_stack_init(stack);
