@@ -320,6 +320,7 @@ struct Call {
     double* gacc;
     double* lds_d = nullptr;
     float* lds_f = nullptr;
+    float* stage = nullptr;  // this wavefront's staging memory of texture scatters (STAGE_WORDS words of LDS)
     bool coherent = false;  // this lane's vertex is its path's first (texture scatters group such lanes)
     DEV float p(int slot, int idx) const { return gval(tab->p[slot], (size_t)idx); }
     // Bilinear scatter of CH channels: g[c] w_k to element off + B.i[k] + c of a slot.
@@ -361,17 +362,58 @@ struct Call {
     }
 };
 
+// Coalesced bilinear scatter into the global accumulator: the values g[c] w_k of the lanes with todo are laid
+// out in LDS, and the calling lanes then add them in texel order, so that the 4 CH atomics of one scatter,
+// two runs of 2 CH neighbouring doubles, are lanes of one instruction and reach the L2 as a few line
+// requests.  Issued by the lane that owns them, each atomic instruction touched a line per lane: the
+// walk of the uneven worlds, whose time is these atomics, 13.5 -> 4.9 ms.  a: the accumulator of the
+// texture's first element.  The lanes of one wavefront call it together, under divergence.
+constexpr int STAGE_REC = 16;                    // 12 values, address (2 words), offsets of texels 1 and 3
+constexpr int STAGE_WORDS = WAVE * STAGE_REC;
+template <int CH>
+DEV void scatter_staged(float* stage, double* a, const Bilin& B, const float* g, bool todo) {
+    const uint64_t act = __ballot(1), m = __ballot(todo), below = (1ull << lane_id()) - 1ull;
+    const int n = (int)__popcll(m) * 4 * CH, lanes = (int)__popcll(act);
+    if (todo) {
+        float* r = stage + (int)__popcll(m & below) * STAGE_REC;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int c = 0; c < CH; ++c) r[k * CH + c] = g[c] * B.w[k];
+        const uint64_t ad = (uint64_t)(a + B.i[0]);
+        r[12] = __uint_as_float((uint32_t)ad);
+        r[13] = __uint_as_float((uint32_t)(ad >> 32));
+        r[14] = __int_as_float(B.i[1] - B.i[0]);
+        r[15] = __int_as_float(B.i[3] - B.i[0]);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (int t = (int)__popcll(act & below); t < n; t += lanes) {
+        const int q = t / (4 * CH), j = t - q * 4 * CH, k = j / CH;
+        const float* r = stage + q * STAGE_REC;
+        const float v = r[j];
+        if (v == 0.0f) continue;
+        const uint64_t ad = (uint64_t)__float_as_uint(r[12]) | ((uint64_t)__float_as_uint(r[13]) << 32);
+        const int d1 = __float_as_int(r[14]), d3 = __float_as_int(r[15]);
+        const int off = (k & 1 ? (k & 2 ? d3 : d1) : (k & 2 ? d3 - d1 : 0)) + (j - k * CH);
+        unsafeAtomicAdd((double*)ad + off, (double)v);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Grouped bilinear scatter into the global accumulator: adds g[c] w_k to texel k, channel c, through
-// add(k, c, value).  Among
-// the lanes that flag themselves coherent (a path's first vertex: the samples of one pixel land in
-// one or two texel cells), lanes whose four texels are the same (key: texel 0's address and the
-// offsets of texels 1 and 3, which fix texel 2 = 0 + 3 - 1) are found group by group from the first
+// add(k, c, value).  Among the lanes that flag themselves coherent (a path's first vertex: the samples of
+// one pixel land in one or two texel cells), lanes whose four texels are the same (key: texel 0's address
+// and the offsets of texels 1 and 3, which fix texel 2 = 0 + 3 - 1) are found group by group from the first
 // pending lane; a group of at least GROUP_MIN lanes has its 4 CH values summed and added by one lane.
-// Every other lane adds its own values.  (Textures in the workgroup accumulators keep per-lane LDS
-// atomics: grouping there measured slower, the replay of the 128-view batch 6.3 -> 7.0 ms.)
-constexpr int GROUP_MIN = 2, GROUP_ROUNDS = 8;
+// Returns whether the lane's values are not yet added (it was in no group).  Smaller groups cost more
+// shuffles than scatter_staged takes for them (first vertices of the uneven worlds 3.26 ms with groups of
+// 2 and up, 2.95 with 8, 3.2 with 16, 14.9 without groups).  (Textures in the workgroup accumulators keep
+// per-lane LDS atomics: grouping there measured slower, the replay of the 128-view batch 6.3 -> 7.0 ms.)
+constexpr int GROUP_MIN = 8, GROUP_ROUNDS = 4;
 template <int CH, class Add>
-DEV void bilin_grouped(uint64_t key, const Bilin& B, const float* g, bool coherent, Add add) {
+DEV bool bilin_grouped(uint64_t key, const Bilin& B, const float* g, bool coherent, Add add) {
     const uint32_t klo = (uint32_t)key, khi = (uint32_t)(key >> 32);
     const int d1 = B.i[1] - B.i[0], d3 = B.i[3] - B.i[0];
     const uint64_t act = __ballot(1);
@@ -401,15 +443,7 @@ DEV void bilin_grouped(uint64_t key, const Bilin& B, const float* g, bool cohere
             }
         }
     }
-    if (!done) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                const float v = g[c] * B.w[k];
-                if (v != 0.0f) add(k, c, v);
-            }
-    }
+    return !done;
 }
 template <int CH>
 DEV void Call::gb(int slot, int off, const Bilin& B, const float* g) const {
@@ -442,8 +476,9 @@ DEV void Call::gb(int slot, int off, const Bilin& B, const float* g) const {
     const int64_t o = tab->goff[slot];
     if (o >= 0) {
         double* a = gacc + o + off;
-        bilin_grouped<CH>((uint64_t)(a + B.i[0]), B, g, coherent,
-                          [&](int k, int c, float v) { unsafeAtomicAdd(a + B.i[k] + c, (double)v); });
+        const bool left = bilin_grouped<CH>((uint64_t)(a + B.i[0]), B, g, coherent,
+                                            [&](int k, int c, float v) { unsafeAtomicAdd(a + B.i[k] + c, (double)v); });
+        scatter_staged<CH>(stage, a, B, g, left);
     }
 }
 

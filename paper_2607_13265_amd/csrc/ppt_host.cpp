@@ -508,6 +508,7 @@ static int convert_world(ppt_scene* sc, const uint8_t*& p, const uint8_t* end, W
 struct WsLayout {
     size_t table, stats, counts, gacc, total;
     int lds_nd = 0, lds_nf = 0;
+    bool lds_stage = false;  // a requested gradient has no workgroup accumulator
     size_t ray, shd, acc, vtx, row, dq, cache, hits, ckpt, q0, q1, sq, hq, hf, nv, nv_bytes;
     size_t ray2, shd2, acc2, q0_2, q1_2, sq2, hq2, hf2, counts2;  // P-RB sub-path state
     int64_t gacc_n;
@@ -825,6 +826,7 @@ static int fill_table(const ppt_plan* p, const float* const* params, int32_t n_p
         int64_t n = sc->slot_numel[i];
         if (n <= 64 && nd + n <= LDS_GRAD_D) { t.lds_d[i] = nd; nd += (int)n; }
         else if (nf + n <= LDS_GRAD_F) { t.lds_f[i] = nf; nf += (int)n; }
+        else L.lds_stage = true;
     }
     L.lds_nd = nd; L.lds_nf = nf;
     return PPT_OK;
@@ -930,6 +932,7 @@ static int backward_impl(const ppt_plan* p, const float* const* params, int32_t 
     a.gacc = (double*)((char*)ws + L.gacc);
     a.lds_nd = L.lds_nd;
     a.lds_nf = L.lds_nf;
+    a.lds_stage = L.lds_stage ? 1 : 0;
     a.ckpt = p->ckpt;
     a.hyb_rule = p->hyb_rule;
     a.hyb_gamma = p->hyb_gamma;

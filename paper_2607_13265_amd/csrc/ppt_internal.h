@@ -190,6 +190,7 @@ struct WArgs {
     int32_t qin;            // ray queue read in this bounce (0/1)
     int32_t first;          // first bounce: the queue is the identity over the chunk's slots
     int32_t lds_nd, lds_nf;  // used entries of the workgroup gradient accumulators
+    int32_t lds_stage;       // texture gradients go to the global accumulator: staging memory follows them
     int32_t ckpt;           // hybrid replay checkpoint interval k, 0 = cached suffix replay
     int32_t hyb_rule;       // hybrid replay: Eq. 3's decision rule (else recomputation only)
     float hyb_gamma;        // scalar PRB update below this depolarization index

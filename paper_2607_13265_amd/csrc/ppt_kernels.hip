@@ -1315,6 +1315,7 @@ DEV void adjoint_begin(const WArgs& A, Call& K, CallTable* tab, double* lds_grad
     K.tab = tab;
     K.lds_d = lds_grad;
     K.lds_f = (float*)(lds_grad + A.lds_nd);
+    K.stage = K.lds_f + A.lds_nf + (threadIdx.x / WAVE) * STAGE_WORDS;
     for (int k = threadIdx.x; k < A.lds_nd; k += BLOCK) K.lds_d[k] = 0.0;
     for (int k = threadIdx.x; k < A.lds_nf; k += BLOCK) K.lds_f[k] = 0.0f;
     __syncthreads();
@@ -2185,7 +2186,8 @@ hipError_t launch_chunk(WArgs a, const PathState& S2, int mode, const LaunchGrid
             else hipLaunchKernelGGL(k_accum<false>, dim3(gb), dim3(BLOCK), 0, s, a);
         }
     } else {
-        size_t glds = (size_t)a.lds_nd * sizeof(double) + (size_t)a.lds_nf * sizeof(float);
+        const size_t glds = (size_t)a.lds_nd * sizeof(double) + (size_t)a.lds_nf * sizeof(float) +
+                            (a.lds_stage ? (size_t)(BLOCK / WAVE) * STAGE_WORDS * sizeof(float) : 0);
         if (a.adj) {
             // grids: as many workgroups per compute unit as this call's accumulator size and the
             // variant's registers allow

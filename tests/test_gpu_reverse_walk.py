@@ -80,3 +80,49 @@ def test_index_division_by_reciprocal_is_exact():
             n = np.clip(q * d + off, 0, 2 ** 31 - 1)
             got = np.floor((n.astype(np.float64) + 0.5) * inv).astype(np.int64)
             assert np.array_equal(got, n // d)
+
+
+def _textured_ground(aw, ah, rw, rh):
+    """A blended ground with an aw x ah albedo map and an rw x rh roughness map, and a first slot that can
+    fill the workgroup accumulators so that the maps' gradients go to the global one."""
+    rng = np.random.default_rng(aw * 1000 + ah)
+    sc = sg.Scene()
+    sc.add_slot("filler", np.zeros(12800, np.float32))
+    s_alb = sc.add_slot("albedo", rng.uniform(0.2, 0.8, aw * ah * 3))
+    s_rgh = sc.add_slot("rough", rng.uniform(0.2, 0.6, rw * rh))
+    s_ior = sc.add_slot("ior", [1.5])
+    s_le = sc.add_slot("Le", [5.0, 4.0, 3.0])
+    w = sc.add_world()
+    m = w.add_material(type=sg.MAT_BLEND, albedo_slot=s_alb, albedo_tw=aw, albedo_th=ah, alpha_slot=s_rgh,
+                       alpha_tw=rw, alpha_th=rh, eta_slot=s_ior, blend=0.5)
+    w.add_quad((-4, 0, -4), (0, 0, 8), (8, 0, 0), m)
+    w.add_quad((-4, 0, -4), (8, 0, 0), (0, 4, 0), m)
+    w.add_light((-1, 5, -1), (2, 0, 0), (0, 0, 2), s_le)
+    return sc
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("sensor", [sg.SENSOR_POLARIZER, sg.SENSOR_ANALYZER4])
+@pytest.mark.parametrize("aw,ah,rw,rh,spp", [(1, 37, 90, 1, 3), (29, 1, 9, 8, 64), (16, 16, 11, 7, 1), (64, 64, 64, 64, 32)])
+def test_staged_texture_scatter_equals_workgroup_accumulators(aw, ah, rw, rh, spp, sensor):
+    """Texture gradients through the staged scatter into the global accumulator (clamped, one-texel-wide and
+    tiny maps; lone lanes, groups and whole wavefronts per texel cell) against the same gradients asked for
+    alone, which the workgroup accumulators take in FP32: up to 2^14 additions of one sign per texel, whose
+    rounding averages to sqrt(2^14) 2^-24 = 8e-6 of the sum."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2607_13265_amd as ppt
+    sc = _textured_ground(aw, ah, rw, rh)
+    th = sc.add_slot("theta", [0.4])
+    views = np.asarray([sg.make_view(0, 41, 23, spp, (0, 2.5, 6), (0, 0.5, 0), (0, 1, 0), 50.0, sensor,
+                                     th if sensor == sg.SENSOR_POLARIZER else -1, 0, 3)], sg.VIEW_DTYPE)
+    plan = ppt.Plan(ppt.Scene(sc.to_blob()), views, 4)
+    params = [torch.from_numpy(p).cuda() for p in sc.params()]
+    d = torch.zeros(plan.image_numel, device="cuda")
+    d[::4] = 1.0
+    staged = plan.backward(params, 5, d, want=[True] * len(params))
+    assert float(staged[0].abs().max()) == 0.0
+    for name in ("albedo", "rough"):
+        k = sc.slot(name)
+        alone = plan.backward(params, 5, d, want=[i == k for i in range(len(params))])[k].double()
+        assert float((staged[k].double() - alone).norm()) <= 8e-6 * float(alone.norm()), name
