@@ -1474,7 +1474,9 @@ DEV void suffix_by_rule(const WArgs& A, const Call& K, const DevView& V, const D
 // L'_b still to be explained and recovers the suffix as (W_b + u_b I)^-1 (L'_b - E_b) from the
 // primal's weight and emission records, advancing its adjoint rows by W_b + u_b I.
 template <bool HYB, bool EXT, bool RULE = false, bool PPRB = false>
-__global__ void __launch_bounds__(BLOCK) k_replay(WArgs A) {
+// (three waves per SIMD for the hybrid replay: one register more had made it two, 7.2 ms against 5.1 ms for
+// the 230,400 paths of depth 128)
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HYB && !RULE && !EXT ? 3 : 1, 8))) k_replay(WArgs A) {
     extern __shared__ double lds_grad[];
     PathState& S = A.S;
     const int Q = A.Q;
