@@ -15,9 +15,8 @@
 #include <vector>
 
 namespace ppt {
-hipError_t launch_setup(const CallTable& tab, CallTable* dst, Stats* stats, bool reset_stats, hipStream_t s);
-hipError_t launch_fill_f32(float* p, int64_t n, hipStream_t s);
-hipError_t launch_fill_f64(double* p, int64_t n, hipStream_t s);
+hipError_t launch_setup(const CallTable& tab, CallTable* dst, Stats* stats, bool reset_stats, int* counts, float* img,
+                        int64_t n_img, double* gacc, int64_t n_gacc, hipStream_t s);
 hipError_t launch_finalize(const CallTable* tab, const double* gacc, int n_slots, int64_t max_numel, hipStream_t s);
 hipError_t launch_rng(uint64_t seed, const uint32_t* ctr, uint32_t* out, int64_t n, hipStream_t s);
 hipError_t launch_chunk(WArgs a, const PathState& S2, int mode, const LaunchGrid& G, hipStream_t s, const LaunchMarker& M);
@@ -803,6 +802,10 @@ int ppt_plan_launch_info(const ppt_plan* p, int64_t* chunk_paths, int32_t* n_chu
     return PPT_OK;
 }
 
+// A small call's paths run in one launch (not with the light-stage features; per-kernel timing keeps the
+// launches per bounce, whose families it tells apart).
+static bool small_call(const ppt_plan* p) { return p->num_paths <= SMALL_PATHS && !p->scene->has_ext && !p->timing; }
+
 static int fill_table(const ppt_plan* p, const float* const* params, int32_t n_params, float* const* grads,
                       WsLayout& L, CallTable& t, int64_t* max_numel) {
     const ppt_scene* sc = p->scene;
@@ -820,12 +823,15 @@ static int fill_table(const ppt_plan* p, const float* const* params, int32_t n_p
     }
     if (max_numel) *max_numel = mx;
     // workgroup gradient accumulators: small slots in FP64, then textures in FP32 while they fit
+    // (a small call's textures go to the global accumulator: clearing and flushing a texture's copy per
+    // workgroup costs more than its few additions)
+    const bool no_tex = small_call(p) && cached_adjoint(p);
     int nd = 0, nf = 0;
     for (int32_t i = 0; i < n_params; ++i) {
         if (t.goff[i] < 0) continue;
         int64_t n = sc->slot_numel[i];
         if (n <= 64 && nd + n <= LDS_GRAD_D) { t.lds_d[i] = nd; nd += (int)n; }
-        else if (nf + n <= LDS_GRAD_F) { t.lds_f[i] = nf; nf += (int)n; }
+        else if (!no_tex && nf + n <= LDS_GRAD_F) { t.lds_f[i] = nf; nf += (int)n; }
         else L.lds_stage = true;
     }
     L.lds_nd = nd; L.lds_nf = nf;
@@ -849,6 +855,7 @@ static WArgs make_args(const ppt_plan* p, uint64_t seed, void* ws, const WsLayou
     a.mask = p->mask;
     a.ext = p->scene->has_ext ? 1 : 0;  // kernels with normal/specular maps and circular emitters
     a.r1 = rank_one(p) ? 1 : 0;
+    a.small = small_call(p) ? 1 : 0;
     if (p->scene->worlds.size() == 1) {
         a.one_world = 1;
         a.world0 = p->scene->worlds[0]->dev;
@@ -896,8 +903,8 @@ static int render_impl(const ppt_plan* p, const float* const* params, int32_t n_
     const LaunchMarker M = marker(p, 0);
     if (p->timing) p->timer[0].begin();
     M(KF_OTHER, s);
-    HIP_TRY(launch_setup(t, a.table, (Stats*)((char*)ws + L.stats), p->stats, s), "setup launch");
-    if (out) HIP_TRY(launch_fill_f32(out, p->image_numel, s), "clear launch");
+    HIP_TRY(launch_setup(t, a.table, (Stats*)((char*)ws + L.stats), p->stats, a.S.counts, out, out ? p->image_numel : 0,
+                         nullptr, 0, s), "setup launch");
     if ((rc = run_chunks(p, a, PathState{}, 0, s, M))) return rc;
     M(-1, s);
     return PPT_OK;
@@ -934,6 +941,7 @@ static int backward_impl(const ppt_plan* p, const float* const* params, int32_t 
     a.lds_nf = L.lds_nf;
     a.lds_stage = L.lds_stage ? 1 : 0;
     a.ckpt = p->ckpt;
+    a.small = a.small && p->adjoint == PPT_ADJOINT_CACHED ? 1 : 0;
     a.hyb_rule = p->hyb_rule;
     a.hyb_gamma = p->hyb_gamma;
     a.hyb_eps = p->hyb_eps;
@@ -945,8 +953,8 @@ static int backward_impl(const ppt_plan* p, const float* const* params, int32_t 
     const LaunchMarker M = op_timer >= 0 ? marker(p, op_timer) : LaunchMarker{nullptr, nullptr};
     if (op_timer >= 0 && p->timing) p->timer[op_timer].begin();
     M(KF_OTHER, s);
-    HIP_TRY(launch_setup(t, a.table, (Stats*)((char*)ws + L.stats), stats, s), "setup launch");
-    HIP_TRY(launch_fill_f64(a.gacc, L.gacc_n, s), "clear launch");
+    HIP_TRY(launch_setup(t, a.table, (Stats*)((char*)ws + L.stats), stats, a.S.counts, nullptr, 0, a.gacc, L.gacc_n, s),
+            "setup launch");
     if ((rc = run_chunks(p, a, a.prb ? path_state2(ws, L) : PathState{}, 1, s, M))) return rc;
     M(KF_OTHER, s);
     HIP_TRY(launch_finalize(a.table, a.gacc, n_params, mx, s), "finalize launch");

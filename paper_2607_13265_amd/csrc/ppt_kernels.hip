@@ -302,6 +302,132 @@ __global__ void k_reset_counts(int* counts) {
 
 #endif  // PPT_EXT_TU
 
+// ============================================================================ rays of a path
+// Begin and end of the rays of path `slot`, between their record and the traversal state T.
+//
+// Camera ray (info: view and the dead flag of a masked path): generated here, its record written when it is
+// finished; a masked path's keys at once.  Returns whether it is traversed.
+DEV bool camera_begin(const WArgs& A, const ViewRange& range, int slot, Trav& T, int& info, Count& cnt) {
+    const PathState& S = A.S;
+    const int64_t g = A.g0 + slot;
+    int v;
+    const DevView V = view_of(A, range, g, v);
+    const bool live = !(A.mask && !A.mask[g]);
+    const PathId id = path_keys(V, g);
+    v3 o, d;
+    camera_ray(V, V.crop_x0 + id.lx, V.crop_y0 + id.ly, id.smp, A.seed, o, d);
+    info = info_make(0, false, v) | (live ? 0 : INFO_DEAD);
+    trav_begin(T, world_of(A, V), o, d, 3.0e38f);
+    if (A.sig) A.sig[g] = live ? 1469598103934665603ull : 0ull;
+    if (live) {
+        ++cnt.c[ST_PATHS];
+        ++cnt.c[ST_RAYS];
+    } else {
+        ray_rec(S, slot)[3] = f4(__int_as_float(info), __uint_as_float(id.pix), __uint_as_float(id.smp),
+                                 __uint_as_float(V.view_id));
+        S.hflag[slot] = 2;
+        if (S.nv) S.nv[slot] = 0;  // (no vertex)
+    }
+    return live;
+}
+// The camera ray's record: the whole record for a hit (ray, sensor rotation, hit, keys), the keys alone for
+// a ray that escaped (nothing else of it is read); the keys again from the slot and the view.
+DEV void camera_end(const WArgs& A, const ViewRange& range, int slot, const Trav& T, int info) {
+    const PathState& S = A.S;
+    const int64_t g = A.g0 + slot;
+    int v;
+    const DevView V = view_of(A, range, g, v);
+    float4* R = ray_rec(S, slot);
+    const PathId id = path_keys(V, g);
+    if (T.h.prim >= 0) {
+        // rotation from the canonical frame of the light arriving along -d to the
+        // sensor frame, kept in the record's spare words for the pixel reduction
+        const v3 kc = -T.d;
+        float Cs, Ss;
+        rot_cs(kc, canon_x(kc), normalize(ld3(V.r) - kc * dot(ld3(V.r), kc)), Cs, Ss);
+        ray_set(R, T.o, T.d, Cs, Ss);
+        R[2] = f4(T.tb, T.h.u, T.h.v, __int_as_float(T.h.prim));
+    }
+    R[3] = f4(__int_as_float(info), __uint_as_float(id.pix), __uint_as_float(id.smp),
+              __uint_as_float(V.view_id));
+    S.hflag[slot] = T.h.prim >= 0 ? 1 : 0;
+    // whether the path has a vertex (the shading kernels of the backward then count them)
+    if (S.nv) S.nv[slot] = T.h.prim >= 0 ? 1 : 0;
+}
+// Next-event ray: the ray and its vertex's info word in one record (no read of the ray record, whose line
+// would be fetched for its 16-byte key word).
+template <int SMODE>
+DEV void shadow_begin(const WArgs& A, int slot, Trav& T, int& info) {
+    const PathState& S = A.S;
+    const float4* H = SMODE == 4 ? r1_shd(S, A.Q, slot) : SMODE == 1 || SMODE == 5 ? shd1_rec(S, slot) : shd_rec(S, slot);
+    const float4 s0 = H[0], s1 = H[1];
+    info = __float_as_int(s1.w);
+    trav_begin(T, world_of(A, info >> 12), mk(s0.x, s0.y, s0.z), mk(s1.x, s1.y, s1.z), s0.w);
+}
+// What the outcome of a next-event ray (occ: occluded) changes.
+template <int SMODE>
+DEV void shadow_end(const WArgs& A, int slot, int info, bool occ) {
+    const PathState& S = A.S;
+    const int Q = A.Q;
+    if (SMODE == 4) {
+        // rank-one render: the path's radiance words already hold the next-event part
+        // (k_shade<4>); an occluded light sample restores them from word 3
+        if (occ) {
+            float4* AC = r1_rec(S, slot);
+            AC[2] = AC[3];
+        }
+        if (A.sig) sig_add(A.sig[A.g0 + slot], (uint32_t)(occ ? NEE_OCCLUDED : NEE_VISIBLE));
+    } else if (SMODE == 5) {
+        // cached backward: the vertex's record reads visible; an occluded sample marks it
+        if (occ) vtx_rec(S, Q, (info & 255) - 1, slot)[1].w = __int_as_float(1);
+    } else if (SMODE >= 0) {
+        const float4* H = shd_rec(S, slot);
+        if (SMODE == 1) {
+            // the cache record holds E_b plus the next-event part and a visible sample
+            // (k_shade<1>); an occluded light sample sets the E words back to E_b (zero unless
+            // the vertex emits, when it was kept beside the shadow rays) and its visibility word
+            // (two whole 32-byte sectors); a visible one writes nothing
+            if (occ) {
+                float4* dst = cache_rec(S, Q, (info & 255) - 1, slot) + 4;
+                if (info & INFO_EMIT) {
+                    const float4* Eb = emit1_rec(S, Q, slot);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) dst[k] = Eb[k];
+                } else {  // (E_b is zero)
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) dst[k] = f4(0.0f, 0.0f, 0.0f, 0.0f);
+                }
+                dst[3] = f4(__int_as_float(NEE_OCCLUDED), 0.0f, 0.0f, 0.0f);
+            }
+        } else if (SMODE != 2) {  // the hybrid replay recomputes the next-event part from the visibility bit
+            // (the tape forward adds it to both the radiance and the vertex's E_b)
+            float4* dst = acc_rec(S, slot) + 5;
+            if (!occ)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    float4 a = dst[k], p = H[2 + k];
+                    dst[k] = f4(a.x + p.x, a.y + p.y, a.z + p.z, a.w + p.w);
+                }
+            if (SMODE == 3 && !occ) {
+                float4* te = tape_rec(S, Q, (info & 255) - 1, slot) + 4;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    float4 a = te[k], p = H[5 + k];
+                    te[k] = f4(a.x + p.x, a.y + p.y, a.z + p.z, a.w + p.w);
+                }
+            }
+        }
+        if (SMODE != 0 && SMODE != 1) {  // in the hit word of the vertex whose light sample this is
+            float* hwp = SMODE == 3 ? &tape_rec(S, Q, (info & 255) - 1, slot)[2].w
+                                    : &hit_rec(S, Q, (info & 255) - 1, slot)->x;
+            uint32_t hw = (uint32_t)__float_as_int(*hwp);
+            hw = (hw & ~(7u << 26)) | ((uint32_t)(occ ? NEE_OCCLUDED : NEE_VISIBLE) << 26);
+            *hwp = __int_as_float((int)hw);
+        }
+        if (A.sig) sig_add(A.sig[A.g0 + slot], (uint32_t)(occ ? NEE_OCCLUDED : NEE_VISIBLE));
+    }
+}
+
 // Closest hits of the rays of one bounce: a persistent kernel in which a lane takes the next queued
 // ray as soon as its own is finished.  SMODE >= 0: the same launch resolves the shadow rays of the
 // previous bounce (positions [0, n_s) of one work list, any hit; SMODE is that bounce's mode: 0
@@ -319,7 +445,6 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STAT
     int* stack = lds_stack + threadIdx.x;
     trav_stack_init(stack);
     PathState& S = A.S;
-    const int Q = A.Q;
     if (blockIdx.x == 0 && threadIdx.x == 0) {  // the queues the following kernels append to
         S.counts[1 - A.qin] = 0;
         S.counts[7] = 0;
@@ -340,43 +465,16 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STAT
     while (true) {
         const int idx = F.take(!alive, n, &S.counts[5]);
         if constexpr (SMODE == -2) {
-            // the camera ray of path slot, generated here (its record is written when the ray is
-            // finished; a masked path's keys at once, and it is not traversed)
-            const int64_t g = A.g0 + idx;
-            view_find(A, range, idx >= 0, g);
+            view_find(A, range, idx >= 0, A.g0 + idx);
             if (idx >= 0) {
                 slot = idx;
-                int v;
-                const DevView V = view_of(A, range, g, v);
-                const bool live = !(A.mask && !A.mask[g]);
-                const PathId id = path_keys(V, g);
-                v3 o, d;
-                camera_ray(V, V.crop_x0 + id.lx, V.crop_y0 + id.ly, id.smp, A.seed, o, d);
-                info = info_make(0, false, v) | (live ? 0 : INFO_DEAD);
-                trav_begin(T, world_of(A, V), o, d, 3.0e38f);
-                alive = live;
-                if (A.sig) A.sig[g] = live ? 1469598103934665603ull : 0ull;
-                if (live) {
-                    ++cnt.c[ST_PATHS];
-                    ++cnt.c[ST_RAYS];
-                } else {
-                    ray_rec(S, slot)[3] = f4(__int_as_float(info), __uint_as_float(id.pix), __uint_as_float(id.smp),
-                                             __uint_as_float(V.view_id));
-                    S.hflag[slot] = 2;
-                    if (S.nv) S.nv[slot] = 0;  // (no vertex)
-                }
+                alive = camera_begin(A, range, slot, T, info, cnt);
             }
         } else if (idx >= 0) {
             any = idx < ns;
             if (SMODE >= 0 && any) {
                 slot = S.squeue[idx];
-                // the shadow ray and its vertex's info word in one record (no read of the ray
-                // record, whose line would be fetched for its 16-byte key word)
-                const float4* H = SMODE == 4 ? r1_shd(S, Q, slot) : SMODE == 1 || SMODE == 5 ? shd1_rec(S, slot) : shd_rec(S, slot);
-                const float4 s0 = H[0], s1 = H[1];
-                info = __float_as_int(s1.w);
-                trav_begin(T, world_of(A, info >> 12),
-                           mk(s0.x, s0.y, s0.z), mk(s1.x, s1.y, s1.z), s0.w);
+                shadow_begin<SMODE>(A, slot, T, info);
                 alive = true;
                 ++cnt.c[ST_SHADOW_RAYS];
             } else {
@@ -406,91 +504,15 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STAT
             }
         }
         if constexpr (SMODE == -2) {
-            // the camera ray's record: the whole record for a hit (ray, sensor rotation, hit,
-            // keys), the keys alone for a ray that escaped (nothing else of it is read); the
-            // keys again from the slot and the view
-            const int64_t g = A.g0 + slot;
-            view_find(A, range, done, g);
+            view_find(A, range, done, A.g0 + slot);
             if (done) {
                 alive = false;
-                int v;
-                const DevView V = view_of(A, range, g, v);
-                float4* R = ray_rec(S, slot);
-                const PathId id = path_keys(V, g);
-                if (T.h.prim >= 0) {
-                    // rotation from the canonical frame of the light arriving along -d to the
-                    // sensor frame, kept in the record's spare words for the pixel reduction
-                    const v3 kc = -T.d;
-                    float Cs, Ss;
-                    rot_cs(kc, canon_x(kc), normalize(ld3(V.r) - kc * dot(ld3(V.r), kc)), Cs, Ss);
-                    ray_set(R, T.o, T.d, Cs, Ss);
-                    R[2] = f4(T.tb, T.h.u, T.h.v, __int_as_float(T.h.prim));
-                }
-                R[3] = f4(__int_as_float(info), __uint_as_float(id.pix), __uint_as_float(id.smp),
-                          __uint_as_float(V.view_id));
-                S.hflag[slot] = T.h.prim >= 0 ? 1 : 0;
-                // whether the path has a vertex (the shading kernels of the backward then count them)
-                if (S.nv) S.nv[slot] = T.h.prim >= 0 ? 1 : 0;
+                camera_end(A, range, slot, T, info);
             }
         } else if (done) {
             alive = false;
-            if (SMODE == 4 && any) {
-                // rank-one render: the path's radiance words already hold the next-event part
-                // (k_shade<4>); an occluded light sample restores them from word 3
-                if (T.h.prim >= 0) {
-                    float4* AC = r1_rec(S, slot);
-                    AC[2] = AC[3];
-                }
-                if (A.sig) sig_add(A.sig[A.g0 + slot], (uint32_t)(T.h.prim >= 0 ? NEE_OCCLUDED : NEE_VISIBLE));
-            } else if (SMODE == 5 && any) {
-                // cached backward: the vertex's record reads visible; an occluded sample marks it
-                if (T.h.prim >= 0) vtx_rec(S, Q, (info & 255) - 1, slot)[1].w = __int_as_float(1);
-            } else if (SMODE >= 0 && any) {
-                const bool occ = T.h.prim >= 0;
-                const float4* H = shd_rec(S, slot);
-                if (SMODE == 1) {
-                    // the cache record holds E_b plus the next-event part and a visible sample
-                    // (k_shade<1>); an occluded light sample sets the E words back to E_b (zero unless
-                    // the vertex emits, when it was kept beside the shadow rays) and its visibility word
-                    // (two whole 32-byte sectors); a visible one writes nothing
-                    if (occ) {
-                        float4* dst = cache_rec(S, Q, (info & 255) - 1, slot) + 4;
-                        if (info & INFO_EMIT) {
-                            const float4* Eb = emit1_rec(S, Q, slot);
-#pragma unroll
-                            for (int k = 0; k < 3; ++k) dst[k] = Eb[k];
-                        } else {  // (E_b is zero)
-#pragma unroll
-                            for (int k = 0; k < 3; ++k) dst[k] = f4(0.0f, 0.0f, 0.0f, 0.0f);
-                        }
-                        dst[3] = f4(__int_as_float(NEE_OCCLUDED), 0.0f, 0.0f, 0.0f);
-                    }
-                } else if (SMODE != 2) {  // the hybrid replay recomputes the next-event part from the visibility bit
-                    // (the tape forward adds it to both the radiance and the vertex's E_b)
-                    float4* dst = acc_rec(S, slot) + 5;
-                    if (!occ)
-#pragma unroll
-                        for (int k = 0; k < 3; ++k) {
-                            float4 a = dst[k], p = H[2 + k];
-                            dst[k] = f4(a.x + p.x, a.y + p.y, a.z + p.z, a.w + p.w);
-                        }
-                    if (SMODE == 3 && !occ) {
-                        float4* te = tape_rec(S, Q, (info & 255) - 1, slot) + 4;
-#pragma unroll
-                        for (int k = 0; k < 3; ++k) {
-                            float4 a = te[k], p = H[5 + k];
-                            te[k] = f4(a.x + p.x, a.y + p.y, a.z + p.z, a.w + p.w);
-                        }
-                    }
-                }
-                if (SMODE != 0 && SMODE != 1) {  // in the hit word of the vertex whose light sample this is
-                    float* hwp = SMODE == 3 ? &tape_rec(S, Q, (info & 255) - 1, slot)[2].w
-                                            : &hit_rec(S, Q, (info & 255) - 1, slot)->x;
-                    uint32_t hw = (uint32_t)__float_as_int(*hwp);
-                    hw = (hw & ~(7u << 26)) | ((uint32_t)(occ ? NEE_OCCLUDED : NEE_VISIBLE) << 26);
-                    *hwp = __int_as_float((int)hw);
-                }
-                if (A.sig) sig_add(A.sig[A.g0 + slot], (uint32_t)(occ ? NEE_OCCLUDED : NEE_VISIBLE));
+            if (SMODE >= 0 && any) {
+                shadow_end<SMODE>(A, slot, info, T.h.prim >= 0);
             } else {
                 float4* R = ray_rec(S, slot);
                 // the hit in one aligned 16-byte store (a hit's distance is the final tb); a miss
@@ -588,12 +610,300 @@ DEV void sensor_row1(const WArgs& A, const DevView& V, int64_t px_off, float C2,
 }
 
 // ============================================================================ shading
+// The vertex where the ray of path `slot` hit a surface: sampling, weight, radiance or the backward's records,
+// the continuing ray into the ray record (cont) and the next-event ray into its record (shadow).
+template <int MODE, bool EXT>
+DEV void shade_slot(const WArgs& A, const Call& K, int slot, Count& cnt, bool& cont, bool& shadow) {
+    constexpr bool ADJ = MODE == 5 || MODE == 6;  // cached backward: adjoint rows carried forward
+    const PathState& S = A.S;
+    const int Q = A.Q;
+    const float4* R = ray_rec(S, slot);
+    const float4 r3 = R[3], r0 = R[0], r1 = R[1], r2 = R[2];  // one round trip
+    const int info = __float_as_int(r3.x);
+    int nb = info & 255, v = info >> 12;
+    bool prev_delta = (info >> 8) & 1;
+    int64_t g = A.g0 + slot;
+    const uint32_t pix = __float_as_uint(r3.y), smp = __float_as_uint(r3.z);
+    const DevWorld W = world_of(A, v);
+    Hit h;
+    h.prim = __float_as_int(r2.w);
+    h.t = r2.x; h.u = r2.y; h.v = r2.z;
+    v3 o = mk(r0.x, r0.y, r0.z), d = mk(r0.w, r1.x, r1.y);
+    {  // every queued ray hit a surface
+        int b = nb + 1;
+        ++cnt.c[ST_VERTICES];
+        if (MODE == 1 || MODE == 2 || MODE == 3 || ADJ) S.nv[slot] = (uint8_t)b;  // (the fold reads these)
+        Vtx x;
+        surface(W, h, o, d, x);
+        v3 so, sd;
+        float stmax = 0.0f;
+        vertex_setup<EXT>(W, K, __float_as_uint(r3.w), A.seed, pix, smp, b, A.max_depth, A.flags, prev_delta, d, x,
+                          so, sd, stmax);
+        if (A.sig) {
+            uint64_t sg = A.sig[g];
+            sig_add(sg, (uint32_t)x.orig);
+            // (a sampled direction's lobe word also carries the branch of the sampling frame,
+            // the sign of ns.z in the Duff et al. basis, which rounding can flip for a normal
+            // with z near 0)
+            const bool framed = x.lobe == LOBE_DIFFUSE || x.lobe == LOBE_GLOSSY;
+            sig_add(sg, (uint32_t)x.lobe | (framed && signbit(x.ns.z) ? 16u : 0u));
+            if (x.nee != NEE_PENDING) sig_add(sg, (uint32_t)x.nee);
+            A.sig[g] = sg;
+        }
+        WC w;
+        w.kind = 0;
+        float Ee[12], En[12];
+        if (ADJ) eval_vertex<false, EXT, false, true>(W, K, x, w, nullptr, nullptr, nullptr, nullptr);
+        else if (MODE != 2) eval_vertex<false, EXT>(W, K, x, w, Ee, En, nullptr, nullptr);
+        cont = x.lobe != LOBE_NONE && x.lobe != LOBE_INVALID;
+        shadow = x.nee == NEE_PENDING;
+        float4* H = shd_rec(S, slot);
+        // the vertex's info word carried by its shadow ray's record (vertex count and view;
+        // the delta bit is the continuing ray's and is not read for a shadow ray)
+        const int info_shd = info_make(b, false, v);
+        if (MODE == 2) {
+            // hybrid replay: the hit record, and at a block start the ray into this vertex
+            const bool sphere = !x.tri;
+            *hit_rec(S, A.Q, b - 1, slot) = f4(__int_as_float(h.prim | (x.nee << 26)), sphere ? h.t : h.u, h.v, 0.0f);
+            if ((b - 1) % A.ckpt == 0) {
+                float4* CK = ckpt_rec(S, A.Q, (b - 1) / A.ckpt, slot);
+                CK[0] = f4(o.x, o.y, o.z, prev_delta ? 1.0f : 0.0f);
+                CK[1] = f4(d.x, d.y, d.z, 0.0f);
+            }
+        } else if (MODE == 4) {
+            // render with a linear-polarizer sensor: its analyzer is rank one, so the image
+            // needs per channel only the scalar y_c = q^T R_s Lo_c (q: the analyzer's row, R_s:
+            // the sensor rotation).  The path carries the row rho = q^T R_s beta (shared by
+            // the channels, beside beta's RGB scales) instead of beta, and y instead of Lo:
+            // one 64-byte record [rho | rgb | y | y before the next-event part], the shadow ray
+            // in a dense record of its own
+            float4* AC = r1_rec(S, slot);
+            float rho[4], brgb[3], y[3];
+            if (nb == 0) {
+                const DevView V = gval(A.views, (size_t)v);
+                const float th = K.p(V.theta_slot, V.theta_off);
+                const float C2 = cosf(2.0f * th), S2 = sinf(2.0f * th);
+                const float Cs = r1.z, Ss = r1.w;  // sensor rotation of the camera ray
+                rho[0] = 0.5f;
+                rho[1] = 0.5f * (C2 * Cs - S2 * Ss);
+                rho[2] = 0.5f * (C2 * Ss + S2 * Cs);
+                rho[3] = 0.0f;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) { brgb[c] = 1.0f; y[c] = 0.0f; }
+            } else {
+                const float4 a0 = AC[0], a1 = AC[1], a4 = AC[2];
+                rho[0] = a0.x; rho[1] = a0.y; rho[2] = a0.z; rho[3] = a0.w;
+                brgb[0] = a1.x; brgb[1] = a1.y; brgb[2] = a1.z;
+                y[0] = a4.x; y[1] = a4.y; y[2] = a4.z;
+            }
+            float pn[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                y[c] += brgb[c] * (rho[0] * Ee[4 * c] + rho[1] * Ee[4 * c + 1] + rho[2] * Ee[4 * c + 2] +
+                                   rho[3] * Ee[4 * c + 3]);
+                pn[c] = brgb[c] * (rho[0] * En[4 * c] + rho[1] * En[4 * c + 1] + rho[2] * En[4 * c + 2] +
+                                   rho[3] * En[4 * c + 3]);
+            }
+            if (cont) {
+                if (w.kind == 1) {
+                    rho[1] = rho[2] = rho[3] = 0.0f;
+                } else {
+                    WC ws = w;
+                    ws.rgb[0] = 1.0f;
+                    float o4[4];
+                    w_row(ws, 0, rho, o4);
+                    rho[0] = o4[0]; rho[1] = o4[1]; rho[2] = o4[2]; rho[3] = o4[3];
+                }
+#pragma unroll
+                for (int c = 0; c < 3; ++c) brgb[c] *= w.rgb[c];
+            }
+            // the whole record (partial records measured slower)
+            AC[0] = f4(rho[0], rho[1], rho[2], rho[3]);
+            AC[1] = f4(brgb[0], brgb[1], brgb[2], 0.0f);
+            // y with the next-event part as if its light sample were visible (traversal then
+            // writes nothing for a visible one, and restores y from word 3 for an occluded one)
+            if (shadow)
+                AC[2] = f4(y[0] + pn[0], y[1] + pn[1], y[2] + pn[2], 0.0f);
+            else
+                AC[2] = f4(y[0], y[1], y[2], 0.0f);
+            AC[3] = f4(y[0], y[1], y[2], 0.0f);
+            if (shadow) {  // the shadow ray in its dense 32-byte record
+                float4* H4 = r1_shd(S, A.Q, slot);
+                H4[0] = f4(so.x, so.y, so.z, stmax);
+                H4[1] = f4(sd.x, sd.y, sd.z, __int_as_float(info_shd));
+            }
+        } else if (MODE == 0 || MODE == 3) {
+            float4* AC = acc_rec(S, slot);
+            float beta[16], brgb[3], Lo[12];
+            if (nb == 0) {  // first vertex: beta = I, no radiance yet
+#pragma unroll
+                for (int k = 0; k < 16; ++k) beta[k] = (k % 5 == 0) ? 1.0f : 0.0f;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) brgb[c] = 1.0f;
+#pragma unroll
+                for (int k = 0; k < 12; ++k) Lo[k] = 0.0f;
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    float4 t = AC[k];
+                    beta[4 * k] = t.x; beta[4 * k + 1] = t.y; beta[4 * k + 2] = t.z; beta[4 * k + 3] = t.w;
+                }
+                float4 t = AC[4];
+                brgb[0] = t.x; brgb[1] = t.y; brgb[2] = t.z;
+                ld12(AC + 5, Lo);
+            }
+            // Lo_c += brgb_c beta Ee_c; the pending next-event part likewise
+            float pn[12];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float se = beta[4 * r] * Ee[4 * c] + beta[4 * r + 1] * Ee[4 * c + 1] +
+                               beta[4 * r + 2] * Ee[4 * c + 2] + beta[4 * r + 3] * Ee[4 * c + 3];
+                    Lo[4 * c + r] += brgb[c] * se;
+                    float sn = beta[4 * r] * En[4 * c] + beta[4 * r + 1] * En[4 * c + 1] +
+                               beta[4 * r + 2] * En[4 * c + 2] + beta[4 * r + 3] * En[4 * c + 3];
+                    pn[4 * c + r] = brgb[c] * sn;
+                }
+            }
+            if (shadow) st12(H + 2, pn);
+            st12(AC + 5, Lo);
+            if (MODE == 3) {
+                // the tape record of this vertex: weight, hit, emission (its next-event part is
+                // added when the shadow ray is resolved), the prefix throughput before the
+                // vertex, and the ray into it
+                float4* T = tape_rec(S, A.Q, b - 1, slot);
+                const bool sphere = !x.tri;
+                T[0] = f4(w.rgb[0], w.rgb[1], w.rgb[2], w.A);
+                T[1] = f4(w.B, w.C, w.D, w.ci);
+                T[2] = f4(w.si, w.co, w.so, __int_as_float(h.prim | (x.nee << 26) | (w.kind << 29)));
+                T[3] = f4(sphere ? h.t : h.u, h.v, 0.0f, 0.0f);
+                st12(T + 4, Ee);
+                T[7] = f4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) T[8 + k] = f4(beta[4 * k], beta[4 * k + 1], beta[4 * k + 2], beta[4 * k + 3]);
+                T[12] = f4(brgb[0], brgb[1], brgb[2], prev_delta ? 1.0f : 0.0f);
+                T[13] = f4(o.x, o.y, o.z, d.x);
+                T[14] = f4(d.y, d.z, 0.0f, 0.0f);
+            }
+            if (cont) {
+                if (w.kind == 1) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) { beta[4 * r + 1] = beta[4 * r + 2] = beta[4 * r + 3] = 0.0f; }
+                } else {
+                    WC ws = w;
+                    ws.rgb[0] = 1.0f;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        float row[4] = {beta[4 * r], beta[4 * r + 1], beta[4 * r + 2], beta[4 * r + 3]}, o4[4];
+                        w_row(ws, 0, row, o4);
+                        beta[4 * r] = o4[0]; beta[4 * r + 1] = o4[1]; beta[4 * r + 2] = o4[2]; beta[4 * r + 3] = o4[3];
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) AC[k] = f4(beta[4 * k], beta[4 * k + 1], beta[4 * k + 2], beta[4 * k + 3]);
+                AC[4] = f4(brgb[0] * w.rgb[0], brgb[1] * w.rgb[1], brgb[2] * w.rgb[2], 0.0f);
+            }
+        } else if (ADJ) {
+            // cached backward: what the reverse walk needs to evaluate the vertex again (32 bytes:
+            // hit, incoming direction, visibility word), and the adjoint row of the next vertex,
+            // a <- a W_b, started here from dL/dI (the first vertex's row is made again from it)
+            float4* VR = vtx_rec(S, Q, b - 1, slot);
+            VR[0] = f4(__int_as_float(h.prim | (prev_delta ? VTX_PREV_DELTA : 0)), x.tri ? h.u : x.p.x,
+                       x.tri ? h.v : x.p.y, x.p.z);
+            VR[1] = f4(d.x, d.y, d.z, 0.0f);
+            if (cont) {
+                float C2 = 1.0f, S2 = 0.0f;
+                DevView V;
+                if (nb == 0) {
+                    V = gval(A.views, (size_t)v);
+                    if (V.sensor == SENSOR_POLARIZER) {
+                        const float th = K.p(V.theta_slot, V.theta_off);
+                        C2 = cosf(2.0f * th);
+                        S2 = sinf(2.0f * th);
+                    }
+                }
+                if (MODE == 6) {
+                    float rho[4], sc[3];
+                    if (nb == 0) {
+                        sensor_row1(A, V, pixel_offset(V, pix), C2, S2, r1.z, r1.w, rho, sc);
+                    } else {
+                        const float4* RR = row_rec<true>(S, Q, b - 1, slot);
+                        const float4 a0 = RR[0], a1 = RR[1];
+                        rho[0] = a0.x; rho[1] = a0.y; rho[2] = a0.z; rho[3] = a0.w;
+                        sc[0] = a1.x; sc[1] = a1.y; sc[2] = a1.z;
+                    }
+                    if (w.kind == 1) {
+                        rho[1] = rho[2] = rho[3] = 0.0f;
+                    } else {
+                        WC ws = w;
+                        ws.rgb[0] = 1.0f;
+                        float o4[4];
+                        w_row(ws, 0, rho, o4);
+                        rho[0] = o4[0]; rho[1] = o4[1]; rho[2] = o4[2]; rho[3] = o4[3];
+                    }
+                    float4* RW = row_rec<true>(S, Q, b, slot);
+                    RW[0] = f4(rho[0], rho[1], rho[2], rho[3]);
+                    RW[1] = f4(sc[0] * w.rgb[0], sc[1] * w.rgb[1], sc[2] * w.rgb[2], 0.0f);
+                } else {
+                    float av[12], an[12];
+                    if (nb == 0) sensor_rows(A, V, pixel_offset(V, pix), C2, S2, r1.z, r1.w, av);
+                    else ld12(row_rec<false>(S, Q, b - 1, slot), av);
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) w_row(w, c, av + 4 * c, an + 4 * c);
+                    st12(row_rec<false>(S, Q, b, slot), an);
+                }
+            }
+            if (shadow) {  // the shadow ray in its dense 32-byte record
+                float4* H1 = shd1_rec(S, slot);
+                H1[0] = f4(so.x, so.y, so.z, stmax);
+                H1[1] = f4(sd.x, sd.y, sd.z, __int_as_float(info_shd));
+            }
+        } else {  // MODE 1
+            float4* C = cache_rec(S, A.Q, b - 1, slot);
+            const bool sphere = !x.tri;
+            C[0] = f4(w.rgb[0], w.rgb[1], w.rgb[2], w.A);
+            C[1] = f4(w.B, w.C, w.D, w.ci);
+            C[2] = f4(w.si, w.co, w.so, __int_as_float(h.prim | (x.nee << 26) | (w.kind << 29)));
+            C[3] = f4(sphere ? h.t : h.u, h.v, 0.0f, 0.0f);
+            // E_b with the next-event part as if its light sample were visible, so that traversal
+            // writes nothing here for a visible one (an occluded one restores E_b from the
+            // shadow record's words 5..7)
+            if (shadow) {
+                float EN[12];
+#pragma unroll
+                for (int k = 0; k < 12; ++k) EN[k] = Ee[k] + En[k];
+                st12(C + 4, EN);
+                // the shadow ray in its dense 32-byte record, and E_b where the vertex emits (an
+                // occluded sample restores it; a non-emitting vertex's E_b is zero)
+                float4* H1 = shd1_rec(S, slot);
+                H1[0] = f4(so.x, so.y, so.z, stmax);
+                H1[1] = f4(sd.x, sd.y, sd.z, __int_as_float(info_shd | (x.emit ? INFO_EMIT : 0)));
+                if (x.emit) st12(emit1_rec(S, A.Q, slot), Ee);
+            } else {
+                st12(C + 4, Ee);
+            }
+            // a whole 128-byte record is written; a pending light sample's visibility as if
+            // visible (traversal rewrites it for an occluded one)
+            C[7] = f4(__int_as_float(shadow ? NEE_VISIBLE : 0), 0.0f, 0.0f, 0.0f);
+        }
+        if (MODE != 4 && MODE != 1 && !ADJ && shadow) {  // a whole record (the Stokes words are [2..4]; partial ones measured slower)
+            H[0] = f4(so.x, so.y, so.z, stmax);
+            H[1] = f4(sd.x, sd.y, sd.z, __int_as_float(info_shd));
+            if (MODE == 3) st12(H + 5, En);  // (the tape's E_b takes the unweighted part)
+            else H[5] = H[6] = H[7] = f4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
+        float4* Rw = ray_rec(S, slot);
+        if (cont) ray_set(Rw, spawn(x.p, x.ng, x.wi), x.wi, r1.z, r1.w);  // (keeps the sensor rotation)
+        Rw[3].x = __int_as_float(info_make(b, is_delta(gval(W.mats, (size_t)x.mat).type), v));
+    }
+}
+
 template <int MODE, bool EXT>
 // (four waves per SIMD where the registers then fit without spills)
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MODE == 1 && EXT ? 1 : 4, 8))) k_shade(WArgs A) {
     constexpr bool ADJ = MODE == 5 || MODE == 6;  // cached backward: adjoint rows carried forward
     PathState& S = A.S;
-    const int Q = A.Q;
     Call K{A.table, nullptr};
     int* qout = A.qin ? S.queue0 : S.queue1;
     const int n = S.counts[7];
@@ -610,288 +920,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MODE
         bool cont = false, shadow = false;
         int slot = 0;
         if (i < n) slot = S.hqueue[i];
-        const float4* R = ray_rec(S, slot);
-        if (i < n) {  // a queued ray is a live path's hit (a dead slot's outcome is never a hit)
-            const float4 r3 = R[3], r0 = R[0], r1 = R[1], r2 = R[2];  // one round trip
-            const int info = __float_as_int(r3.x);
-            int nb = info & 255, v = info >> 12;
-            bool prev_delta = (info >> 8) & 1;
-            int64_t g = A.g0 + slot;
-            const uint32_t pix = __float_as_uint(r3.y), smp = __float_as_uint(r3.z);
-            const DevWorld W = world_of(A, v);
-            Hit h;
-            h.prim = __float_as_int(r2.w);
-            h.t = r2.x; h.u = r2.y; h.v = r2.z;
-            v3 o = mk(r0.x, r0.y, r0.z), d = mk(r0.w, r1.x, r1.y);
-            {  // every queued ray hit a surface
-                int b = nb + 1;
-                ++cnt.c[ST_VERTICES];
-                if (MODE == 1 || MODE == 2 || MODE == 3 || ADJ) S.nv[slot] = (uint8_t)b;  // (the fold reads these)
-                Vtx x;
-                surface(W, h, o, d, x);
-                v3 so, sd;
-                float stmax = 0.0f;
-                vertex_setup<EXT>(W, K, __float_as_uint(r3.w), A.seed, pix, smp, b, A.max_depth, A.flags, prev_delta, d, x,
-                                  so, sd, stmax);
-                if (A.sig) {
-                    uint64_t sg = A.sig[g];
-                    sig_add(sg, (uint32_t)x.orig);
-                    // (a sampled direction's lobe word also carries the branch of the sampling frame,
-                    // the sign of ns.z in the Duff et al. basis, which rounding can flip for a normal
-                    // with z near 0)
-                    const bool framed = x.lobe == LOBE_DIFFUSE || x.lobe == LOBE_GLOSSY;
-                    sig_add(sg, (uint32_t)x.lobe | (framed && signbit(x.ns.z) ? 16u : 0u));
-                    if (x.nee != NEE_PENDING) sig_add(sg, (uint32_t)x.nee);
-                    A.sig[g] = sg;
-                }
-                WC w;
-                w.kind = 0;
-                float Ee[12], En[12];
-                if (ADJ) eval_vertex<false, EXT, false, true>(W, K, x, w, nullptr, nullptr, nullptr, nullptr);
-                else if (MODE != 2) eval_vertex<false, EXT>(W, K, x, w, Ee, En, nullptr, nullptr);
-                cont = x.lobe != LOBE_NONE && x.lobe != LOBE_INVALID;
-                shadow = x.nee == NEE_PENDING;
-                float4* H = shd_rec(S, slot);
-                // the vertex's info word carried by its shadow ray's record (vertex count and view;
-                // the delta bit is the continuing ray's and is not read for a shadow ray)
-                const int info_shd = info_make(b, false, v);
-                if (MODE == 2) {
-                    // hybrid replay: the hit record, and at a block start the ray into this vertex
-                    const bool sphere = !x.tri;
-                    *hit_rec(S, A.Q, b - 1, slot) = f4(__int_as_float(h.prim | (x.nee << 26)), sphere ? h.t : h.u, h.v, 0.0f);
-                    if ((b - 1) % A.ckpt == 0) {
-                        float4* CK = ckpt_rec(S, A.Q, (b - 1) / A.ckpt, slot);
-                        CK[0] = f4(o.x, o.y, o.z, prev_delta ? 1.0f : 0.0f);
-                        CK[1] = f4(d.x, d.y, d.z, 0.0f);
-                    }
-                } else if (MODE == 4) {
-                    // render with a linear-polarizer sensor: its analyzer is rank one, so the image
-                    // needs per channel only the scalar y_c = q^T R_s Lo_c (q: the analyzer's row, R_s:
-                    // the sensor rotation).  The path carries the row rho = q^T R_s beta (shared by
-                    // the channels, beside beta's RGB scales) instead of beta, and y instead of Lo:
-                    // one 64-byte record [rho | rgb | y | y before the next-event part], the shadow ray
-                    // in a dense record of its own
-                    float4* AC = r1_rec(S, slot);
-                    float rho[4], brgb[3], y[3];
-                    if (nb == 0) {
-                        const DevView V = gval(A.views, (size_t)v);
-                        const float th = K.p(V.theta_slot, V.theta_off);
-                        const float C2 = cosf(2.0f * th), S2 = sinf(2.0f * th);
-                        const float Cs = r1.z, Ss = r1.w;  // sensor rotation of the camera ray
-                        rho[0] = 0.5f;
-                        rho[1] = 0.5f * (C2 * Cs - S2 * Ss);
-                        rho[2] = 0.5f * (C2 * Ss + S2 * Cs);
-                        rho[3] = 0.0f;
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) { brgb[c] = 1.0f; y[c] = 0.0f; }
-                    } else {
-                        const float4 a0 = AC[0], a1 = AC[1], a4 = AC[2];
-                        rho[0] = a0.x; rho[1] = a0.y; rho[2] = a0.z; rho[3] = a0.w;
-                        brgb[0] = a1.x; brgb[1] = a1.y; brgb[2] = a1.z;
-                        y[0] = a4.x; y[1] = a4.y; y[2] = a4.z;
-                    }
-                    float pn[3];
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        y[c] += brgb[c] * (rho[0] * Ee[4 * c] + rho[1] * Ee[4 * c + 1] + rho[2] * Ee[4 * c + 2] +
-                                           rho[3] * Ee[4 * c + 3]);
-                        pn[c] = brgb[c] * (rho[0] * En[4 * c] + rho[1] * En[4 * c + 1] + rho[2] * En[4 * c + 2] +
-                                           rho[3] * En[4 * c + 3]);
-                    }
-                    if (cont) {
-                        if (w.kind == 1) {
-                            rho[1] = rho[2] = rho[3] = 0.0f;
-                        } else {
-                            WC ws = w;
-                            ws.rgb[0] = 1.0f;
-                            float o4[4];
-                            w_row(ws, 0, rho, o4);
-                            rho[0] = o4[0]; rho[1] = o4[1]; rho[2] = o4[2]; rho[3] = o4[3];
-                        }
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) brgb[c] *= w.rgb[c];
-                    }
-                    // the whole record (partial records measured slower)
-                    AC[0] = f4(rho[0], rho[1], rho[2], rho[3]);
-                    AC[1] = f4(brgb[0], brgb[1], brgb[2], 0.0f);
-                    // y with the next-event part as if its light sample were visible (traversal then
-                    // writes nothing for a visible one, and restores y from word 3 for an occluded one)
-                    if (shadow)
-                        AC[2] = f4(y[0] + pn[0], y[1] + pn[1], y[2] + pn[2], 0.0f);
-                    else
-                        AC[2] = f4(y[0], y[1], y[2], 0.0f);
-                    AC[3] = f4(y[0], y[1], y[2], 0.0f);
-                    if (shadow) {  // the shadow ray in its dense 32-byte record
-                        float4* H4 = r1_shd(S, A.Q, slot);
-                        H4[0] = f4(so.x, so.y, so.z, stmax);
-                        H4[1] = f4(sd.x, sd.y, sd.z, __int_as_float(info_shd));
-                    }
-                } else if (MODE == 0 || MODE == 3) {
-                    float4* AC = acc_rec(S, slot);
-                    float beta[16], brgb[3], Lo[12];
-                    if (nb == 0) {  // first vertex: beta = I, no radiance yet
-#pragma unroll
-                        for (int k = 0; k < 16; ++k) beta[k] = (k % 5 == 0) ? 1.0f : 0.0f;
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) brgb[c] = 1.0f;
-#pragma unroll
-                        for (int k = 0; k < 12; ++k) Lo[k] = 0.0f;
-                    } else {
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            float4 t = AC[k];
-                            beta[4 * k] = t.x; beta[4 * k + 1] = t.y; beta[4 * k + 2] = t.z; beta[4 * k + 3] = t.w;
-                        }
-                        float4 t = AC[4];
-                        brgb[0] = t.x; brgb[1] = t.y; brgb[2] = t.z;
-                        ld12(AC + 5, Lo);
-                    }
-                    // Lo_c += brgb_c beta Ee_c; the pending next-event part likewise
-                    float pn[12];
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            float se = beta[4 * r] * Ee[4 * c] + beta[4 * r + 1] * Ee[4 * c + 1] +
-                                       beta[4 * r + 2] * Ee[4 * c + 2] + beta[4 * r + 3] * Ee[4 * c + 3];
-                            Lo[4 * c + r] += brgb[c] * se;
-                            float sn = beta[4 * r] * En[4 * c] + beta[4 * r + 1] * En[4 * c + 1] +
-                                       beta[4 * r + 2] * En[4 * c + 2] + beta[4 * r + 3] * En[4 * c + 3];
-                            pn[4 * c + r] = brgb[c] * sn;
-                        }
-                    }
-                    if (shadow) st12(H + 2, pn);
-                    st12(AC + 5, Lo);
-                    if (MODE == 3) {
-                        // the tape record of this vertex: weight, hit, emission (its next-event part is
-                        // added when the shadow ray is resolved), the prefix throughput before the
-                        // vertex, and the ray into it
-                        float4* T = tape_rec(S, A.Q, b - 1, slot);
-                        const bool sphere = !x.tri;
-                        T[0] = f4(w.rgb[0], w.rgb[1], w.rgb[2], w.A);
-                        T[1] = f4(w.B, w.C, w.D, w.ci);
-                        T[2] = f4(w.si, w.co, w.so, __int_as_float(h.prim | (x.nee << 26) | (w.kind << 29)));
-                        T[3] = f4(sphere ? h.t : h.u, h.v, 0.0f, 0.0f);
-                        st12(T + 4, Ee);
-                        T[7] = f4(0.0f, 0.0f, 0.0f, 0.0f);
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) T[8 + k] = f4(beta[4 * k], beta[4 * k + 1], beta[4 * k + 2], beta[4 * k + 3]);
-                        T[12] = f4(brgb[0], brgb[1], brgb[2], prev_delta ? 1.0f : 0.0f);
-                        T[13] = f4(o.x, o.y, o.z, d.x);
-                        T[14] = f4(d.y, d.z, 0.0f, 0.0f);
-                    }
-                    if (cont) {
-                        if (w.kind == 1) {
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) { beta[4 * r + 1] = beta[4 * r + 2] = beta[4 * r + 3] = 0.0f; }
-                        } else {
-                            WC ws = w;
-                            ws.rgb[0] = 1.0f;
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) {
-                                float row[4] = {beta[4 * r], beta[4 * r + 1], beta[4 * r + 2], beta[4 * r + 3]}, o4[4];
-                                w_row(ws, 0, row, o4);
-                                beta[4 * r] = o4[0]; beta[4 * r + 1] = o4[1]; beta[4 * r + 2] = o4[2]; beta[4 * r + 3] = o4[3];
-                            }
-                        }
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) AC[k] = f4(beta[4 * k], beta[4 * k + 1], beta[4 * k + 2], beta[4 * k + 3]);
-                        AC[4] = f4(brgb[0] * w.rgb[0], brgb[1] * w.rgb[1], brgb[2] * w.rgb[2], 0.0f);
-                    }
-                } else if (ADJ) {
-                    // cached backward: what the reverse walk needs to evaluate the vertex again (32 bytes:
-                    // hit, incoming direction, visibility word), and the adjoint row of the next vertex,
-                    // a <- a W_b, started here from dL/dI (the first vertex's row is made again from it)
-                    float4* VR = vtx_rec(S, Q, b - 1, slot);
-                    VR[0] = f4(__int_as_float(h.prim | (prev_delta ? VTX_PREV_DELTA : 0)), x.tri ? h.u : x.p.x,
-                               x.tri ? h.v : x.p.y, x.p.z);
-                    VR[1] = f4(d.x, d.y, d.z, 0.0f);
-                    if (cont) {
-                        float C2 = 1.0f, S2 = 0.0f;
-                        DevView V;
-                        if (nb == 0) {
-                            V = gval(A.views, (size_t)v);
-                            if (V.sensor == SENSOR_POLARIZER) {
-                                const float th = K.p(V.theta_slot, V.theta_off);
-                                C2 = cosf(2.0f * th);
-                                S2 = sinf(2.0f * th);
-                            }
-                        }
-                        if (MODE == 6) {
-                            float rho[4], sc[3];
-                            if (nb == 0) {
-                                sensor_row1(A, V, pixel_offset(V, pix), C2, S2, r1.z, r1.w, rho, sc);
-                            } else {
-                                const float4* RR = row_rec<true>(S, Q, b - 1, slot);
-                                const float4 a0 = RR[0], a1 = RR[1];
-                                rho[0] = a0.x; rho[1] = a0.y; rho[2] = a0.z; rho[3] = a0.w;
-                                sc[0] = a1.x; sc[1] = a1.y; sc[2] = a1.z;
-                            }
-                            if (w.kind == 1) {
-                                rho[1] = rho[2] = rho[3] = 0.0f;
-                            } else {
-                                WC ws = w;
-                                ws.rgb[0] = 1.0f;
-                                float o4[4];
-                                w_row(ws, 0, rho, o4);
-                                rho[0] = o4[0]; rho[1] = o4[1]; rho[2] = o4[2]; rho[3] = o4[3];
-                            }
-                            float4* RW = row_rec<true>(S, Q, b, slot);
-                            RW[0] = f4(rho[0], rho[1], rho[2], rho[3]);
-                            RW[1] = f4(sc[0] * w.rgb[0], sc[1] * w.rgb[1], sc[2] * w.rgb[2], 0.0f);
-                        } else {
-                            float av[12], an[12];
-                            if (nb == 0) sensor_rows(A, V, pixel_offset(V, pix), C2, S2, r1.z, r1.w, av);
-                            else ld12(row_rec<false>(S, Q, b - 1, slot), av);
-#pragma unroll
-                            for (int c = 0; c < 3; ++c) w_row(w, c, av + 4 * c, an + 4 * c);
-                            st12(row_rec<false>(S, Q, b, slot), an);
-                        }
-                    }
-                    if (shadow) {  // the shadow ray in its dense 32-byte record
-                        float4* H1 = shd1_rec(S, slot);
-                        H1[0] = f4(so.x, so.y, so.z, stmax);
-                        H1[1] = f4(sd.x, sd.y, sd.z, __int_as_float(info_shd));
-                    }
-                } else {  // MODE 1
-                    float4* C = cache_rec(S, A.Q, b - 1, slot);
-                    const bool sphere = !x.tri;
-                    C[0] = f4(w.rgb[0], w.rgb[1], w.rgb[2], w.A);
-                    C[1] = f4(w.B, w.C, w.D, w.ci);
-                    C[2] = f4(w.si, w.co, w.so, __int_as_float(h.prim | (x.nee << 26) | (w.kind << 29)));
-                    C[3] = f4(sphere ? h.t : h.u, h.v, 0.0f, 0.0f);
-                    // E_b with the next-event part as if its light sample were visible, so that traversal
-                    // writes nothing here for a visible one (an occluded one restores E_b from the
-                    // shadow record's words 5..7)
-                    if (shadow) {
-                        float EN[12];
-#pragma unroll
-                        for (int k = 0; k < 12; ++k) EN[k] = Ee[k] + En[k];
-                        st12(C + 4, EN);
-                        // the shadow ray in its dense 32-byte record, and E_b where the vertex emits (an
-                        // occluded sample restores it; a non-emitting vertex's E_b is zero)
-                        float4* H1 = shd1_rec(S, slot);
-                        H1[0] = f4(so.x, so.y, so.z, stmax);
-                        H1[1] = f4(sd.x, sd.y, sd.z, __int_as_float(info_shd | (x.emit ? INFO_EMIT : 0)));
-                        if (x.emit) st12(emit1_rec(S, A.Q, slot), Ee);
-                    } else {
-                        st12(C + 4, Ee);
-                    }
-                    // a whole 128-byte record is written; a pending light sample's visibility as if
-                    // visible (traversal rewrites it for an occluded one)
-                    C[7] = f4(__int_as_float(shadow ? NEE_VISIBLE : 0), 0.0f, 0.0f, 0.0f);
-                }
-                if (MODE != 4 && MODE != 1 && !ADJ && shadow) {  // a whole record (the Stokes words are [2..4]; partial ones measured slower)
-                    H[0] = f4(so.x, so.y, so.z, stmax);
-                    H[1] = f4(sd.x, sd.y, sd.z, __int_as_float(info_shd));
-                    if (MODE == 3) st12(H + 5, En);  // (the tape's E_b takes the unweighted part)
-                    else H[5] = H[6] = H[7] = f4(0.0f, 0.0f, 0.0f, 0.0f);
-                }
-                float4* Rw = ray_rec(S, slot);
-                if (cont) ray_set(Rw, spawn(x.p, x.ng, x.wi), x.wi, r1.z, r1.w);  // (keeps the sensor rotation)
-                Rw[3].x = __int_as_float(info_make(b, is_delta(gval(W.mats, (size_t)x.mat).type), v));
-            }
-        }
+        if (i < n) shade_slot<MODE, EXT>(A, K, slot, cnt, cont, shadow);  // (a queued ray is a live path's hit)
         bq_push(qn, cont, slot);
         bq_push(qs, shadow, slot);
         bq_flush(qn, &S.counts[1 - A.qin], qout, false);
@@ -903,6 +932,92 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MODE
 }
 
 #ifndef PPT_EXT_TU  // (in the main compilation unit only)
+// ============================================================================ whole paths of a small call
+// Every bounce of the paths of a small call in one launch: a wavefront takes per_wave consecutive paths
+// (at most 32) in its lower lanes and traces and shades them from the camera to their end, through the same
+// records as the launches per bounce.  The upper lanes trace the next-event rays beside the lower lanes'
+// continuing rays.  A small call is bound by its launches (three per bounce, each some 5 us and as long
+// as its slowest ray); here a path waits for the other paths of its wavefront only.
+template <bool STATS>
+DEV void trace(Trav& T, bool active, bool any, int* stack, Count& cnt) {
+    bool todo = active;
+    while (__any(todo)) {
+        uint32_t nn = 0, np = 0;
+        if (todo && trav_round<STATS>(T, any, nn, np, stack, false)) todo = false;
+        if (STATS) {
+            if (any) { cnt.c[ST_SHADOW_NODES] += nn; cnt.c[ST_SHADOW_PRIMS] += np; }
+            else { cnt.c[ST_NODES] += nn; cnt.c[ST_PRIMS] += np; }
+        }
+    }
+}
+// what one lane wrote to global memory before is read by another lane of the wavefront after
+DEV void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+// MODE: the shading mode (0, 4 render; 5, 6 cached backward; 2 hybrid replay)
+template <int MODE, bool STATS>
+__global__ void __launch_bounds__(BLOCK) k_paths(WArgs A, int per_wave) {
+    constexpr int SMODE = MODE == 6 ? 5 : MODE;
+    extern __shared__ int lds_stack[];
+    int* stack = lds_stack + threadIdx.x;
+    trav_stack_init(stack);
+    Call K{A.table, nullptr};
+    __shared__ CallTable tab;
+    table_to_lds(&tab, A.table);
+    K.tab = &tab;
+    __syncthreads();
+    const PathState& S = A.S;
+    const int wave = blockIdx.x * (BLOCK / WAVE) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    const int lane = lane_id(), mate = lane & (WAVE / 2 - 1);  // (the lower lane of this lane's path)
+    const bool lower = lane < WAVE / 2;
+    const int slot = wave * per_wave + mate;
+    const bool mine = mate < per_wave && slot < A.n_chunk;
+    Count cnt;
+    ViewRange range;
+    Trav T;
+    int info = 0;
+    bool alive = false;
+    view_find(A, range, lower && mine, A.g0 + slot);
+    if (lower && mine) alive = camera_begin(A, range, slot, T, info, cnt);
+    trace<STATS>(T, alive, false, stack, cnt);
+    bool hit = false;
+    if (alive) {
+        camera_end(A, range, slot, T, info);
+        hit = T.h.prim >= 0;
+        if (!hit && A.sig) sig_add(A.sig[A.g0 + slot], 0xffffffffu);
+    }
+    for (int b = 1; b <= A.max_depth && __any(hit); ++b) {
+        bool cont = false, shadow = false;
+        if (hit) shade_slot<MODE, false>(A, K, slot, cnt, cont, shadow);
+        hit = false;
+        if (b == A.max_depth) break;  // (a vertex at the maximum depth starts no ray)
+        wave_fence();
+        const bool any = !lower & (__shfl((int)shadow, mate, WAVE) != 0);
+        alive = any || (lower && cont);
+        if (any) {
+            shadow_begin<SMODE>(A, slot, T, info);
+            ++cnt.c[ST_SHADOW_RAYS];
+        } else if (alive) {
+            const float4* R = ray_rec(S, slot);
+            v3 o, d;
+            ray_od(R, o, d);
+            const int ri = A.one_world ? 0 : __float_as_int(R[3].x);
+            trav_begin(T, world_of(A, ri >> 12), o, d, 3.0e38f);
+            ++cnt.c[ST_RAYS];
+        }
+        trace<STATS>(T, alive, any, stack, cnt);
+        if (any) shadow_end<SMODE>(A, slot, info, T.h.prim >= 0);
+        wave_fence();  // (a path's next-event outcome before its next vertex or its end)
+        if (alive && lower) {
+            hit = T.h.prim >= 0;
+            if (hit) ray_rec(S, slot)[2] = f4(T.tb, T.h.u, T.h.v, __int_as_float(T.h.prim));
+            else if (A.sig) sig_add(A.sig[A.g0 + slot], 0xffffffffu);
+        }
+    }
+    if (STATS) flush_stats(A.stats, cnt);
+}
+
 // ============================================================================ render: pixel reduction
 // Every lane rotates its path's radiance into the sensor frame; the lanes of one pixel (adjacent,
 // samples fastest) are summed by a segmented wavefront scan, and the last lane of each segment
@@ -1649,6 +1764,28 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HYB 
 // followed by a forward replay (read it again) this moves 32 B written and read per first vertex and
 // 64 to 80 B per later one.
 //
+// the adjoint rows of a vertex from their rank-one form
+DEV void row1_load(const float4* r, float* av) {
+    const float4 a0 = r[0], a1 = r[1];
+    const float sc[3] = {a1.x, a1.y, a1.z};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        av[4 * c] = sc[c] * a0.x; av[4 * c + 1] = sc[c] * a0.y;
+        av[4 * c + 2] = sc[c] * a0.z; av[4 * c + 3] = sc[c] * a0.w;
+    }
+}
+// the polarizer-angle term of a path whose radiance at its first vertex is L: dp is the pixel's dL/dI, inv = 1 / spp
+DEV float theta_term(const float* dp, float inv, float C2, float S2, float Cs, float Ss, const float* L) {
+    float gt = 0.0f;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const float l1 = L[4 * c + 1], l2 = L[4 * c + 2];
+        const float ls[4] = {L[4 * c], Cs * l1 + Ss * l2, -Ss * l1 + Cs * l2, L[4 * c + 3]};
+        const float dl[3] = {gval(dp, 4 * c) * inv, gval(dp, 4 * c + 1) * inv, gval(dp, 4 * c + 2) * inv};
+        gt += polarizer_dtheta(C2, S2, dl, ls);
+    }
+    return gt;
+}
 // k_adjoint_deep walks the paths of two or more vertices (the hit queue of the second bounce) down to
 // their second vertex: persistent, a lane takes the next path as soon as its own is walked, and
 // leaves the suffix L[2] in the path's ray record, which nothing reads any more.
@@ -1688,14 +1825,7 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint_deep(WArgs A) {
             const float4 c0 = C[0], c1 = C[1];
             float av[12];
             if (R1) {
-                const float4* RR = row_rec<true>(S, Q, b - 1, slot);
-                const float4 a0 = RR[0], a1 = RR[1];
-                const float sc[3] = {a1.x, a1.y, a1.z};
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    av[4 * c] = sc[c] * a0.x; av[4 * c + 1] = sc[c] * a0.y;
-                    av[4 * c + 2] = sc[c] * a0.z; av[4 * c + 3] = sc[c] * a0.w;
-                }
+                row1_load(row_rec<true>(S, Q, b - 1, slot), av);
             } else {
                 ld12(row_rec<false>(S, Q, b - 1, slot), av);
             }
@@ -1771,17 +1901,7 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint_first(WArgs A) {
                 sensor_rows(A, V, px_off, C2, S2, Cs, Ss, av);
                 const DevWorld W = A.one_world ? A.world0 : cval(A.worlds, V.world);
                 adjoint_vertex(A, K, W, V.view_id, id.pix, id.smp, 1, B == 1, c0, c1, av, L);
-                if (pol) {
-                    const float inv = 1.0f / (float)V.spp;
-                    const float* dp = A.dout + px_off;
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        const float l1 = L[4 * c + 1], l2 = L[4 * c + 2];
-                        const float ls[4] = {L[4 * c], Cs * l1 + Ss * l2, -Ss * l1 + Cs * l2, L[4 * c + 3]};
-                        const float dl[3] = {gval(dp, 4 * c) * inv, gval(dp, 4 * c + 1) * inv, gval(dp, 4 * c + 2) * inv};
-                        gt += polarizer_dtheta(C2, S2, dl, ls);
-                    }
-                }
+                if (pol) gt = theta_term(A.dout + px_off, 1.0f / (float)V.spp, C2, S2, Cs, Ss, L);
             });
             if (__any(pol && tkey >= 0 && tkey != v)) {
                 flush_theta(A, KG, tkey, gtheta);
@@ -1795,6 +1915,64 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint_first(WArgs A) {
         }
     }
     flush_theta(A, KG, tkey, gtheta);
+    flush_lds_grads(A, K);
+}
+
+// The reverse walk of a small call in one launch, every vertex of a path from its last to its first: a
+// wavefront takes per_wave consecutive paths.
+template <bool R1>
+__global__ void __launch_bounds__(BLOCK) k_adjoint_paths(WArgs A, int per_wave) {
+    extern __shared__ double lds_grad[];
+    PathState& S = A.S;
+    const int Q = A.Q;
+    Call K{A.table, A.gacc};
+    const Call KG{A.table, A.gacc};  // (the angle terms: straight to the FP64 accumulator)
+    __shared__ CallTable tab;
+    adjoint_begin(A, K, &tab, lds_grad);
+    K.coherent = false;
+    const int wave = blockIdx.x * (BLOCK / WAVE) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    const int i = wave * per_wave + lane_id();
+    const int B = lane_id() < per_wave && i < A.n_chunk ? (int)S.nv[i] : 0;
+    int v = 0, tkey = -1;
+    uint32_t pix = 0, smp = 0, view_id = 0;
+    if (B > 0) {
+        const float4 r3 = ray_rec(S, i)[3];
+        v = __float_as_int(r3.x) >> 12;
+        pix = __float_as_uint(r3.y);
+        smp = __float_as_uint(r3.z);
+        view_id = __float_as_uint(r3.w);
+    }
+    float L[12], gt = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) L[k] = 0.0f;
+    for (int b = B; b > 0; --b) {
+        const float4* C = vtx_rec(S, Q, b - 1, i);
+        const float4 c0 = C[0], c1 = C[1];
+        float av[12], Cs = 1.0f, Ss = 0.0f, C2 = 1.0f, S2 = 0.0f, inv = 0.0f;
+        const float* dp = nullptr;
+        if (b == 1) {
+            const DevView V = gval(A.views, (size_t)v);
+            if (V.sensor == SENSOR_POLARIZER) {
+                const float th = K.p(V.theta_slot, V.theta_off);
+                C2 = cosf(2.0f * th);
+                S2 = sinf(2.0f * th);
+                tkey = v;
+            }
+            const v3 kc = mk(-c1.x, -c1.y, -c1.z);
+            rot_cs(kc, canon_x(kc), normalize(ld3(V.r) - kc * dot(ld3(V.r), kc)), Cs, Ss);
+            const int64_t px_off = pixel_offset(V, pix);
+            sensor_rows(A, V, px_off, C2, S2, Cs, Ss, av);
+            dp = A.dout + px_off;
+            inv = 1.0f / (float)V.spp;
+        } else if (R1) {
+            row1_load(row_rec<true>(S, Q, b - 1, i), av);
+        } else {
+            ld12(row_rec<false>(S, Q, b - 1, i), av);
+        }
+        adjoint_vertex(A, K, world_of(A, v), view_id, pix, smp, b, b == B, c0, c1, av, L);
+        if (b == 1 && tkey >= 0) gt = theta_term(dp, inv, C2, S2, Cs, Ss, L);
+    }
+    flush_theta(A, KG, tkey, gt);
     flush_lds_grads(A, K);
 }
 
@@ -1991,26 +2169,21 @@ __global__ void __launch_bounds__(BLOCK) k_tape_reverse(WArgs A) {
 }
 
 // ============================================================================ small kernels
-__global__ void k_setup(CallTable tab, CallTable* dst, Stats* stats, int reset_stats) {
-    int i = threadIdx.x;
-    if (i < MAX_SLOTS) {
-        dst->p[i] = tab.p[i];
-        dst->goff[i] = tab.goff[i];
-        dst->gout[i] = tab.gout[i];
-        dst->numel[i] = tab.numel[i];
-        dst->lds_d[i] = tab.lds_d[i];
-        dst->lds_f[i] = tab.lds_f[i];
+// Start of a call: the call table, the work counters, the queue counts of the first chunk, and the arrays that the
+// call accumulates into (image, FP64 gradients) cleared, in one launch.
+__global__ void k_setup(CallTable tab, CallTable* dst, Stats* stats, int reset_stats, int* counts, float* img,
+                        int64_t n_img, double* gacc, int64_t n_gacc) {
+    if (blockIdx.x == 0) {
+        const int n = (int)(sizeof(CallTable) / sizeof(int));
+        for (int k = threadIdx.x; k < n; k += BLOCK) ((int*)dst)[k] = ((const int*)&tab)[k];
+        const int i = threadIdx.x;
+        if (i < ST_COUNT && reset_stats) stats->c[i] = 0ull;
+        if (i < 3 && reset_stats) stats->hyb[i] = 0ull;
+        if (i < 8) counts[i] = 0;
     }
-    if (i < ST_COUNT && reset_stats) stats->c[i] = 0ull;
-    if (i < 3 && reset_stats) stats->hyb[i] = 0ull;
-}
-__global__ void k_fill_f32(float* p, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0.0f;
-}
-__global__ void k_fill_f64(double* p, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0.0;
+    const int64_t i0 = (int64_t)blockIdx.x * BLOCK + threadIdx.x, step = (int64_t)gridDim.x * BLOCK;
+    for (int64_t i = i0; i < n_img; i += step) img[i] = 0.0f;
+    for (int64_t i = i0; i < n_gacc; i += step) gacc[i] = 0.0;
 }
 __global__ void k_finalize(const CallTable* tab, const double* gacc, int n_slots) {
     for (int s = 0; s < n_slots; ++s) {
@@ -2066,18 +2239,11 @@ static int blocks_for(int64_t n, int cap) {
     return (int)b;
 }
 
-hipError_t launch_setup(const CallTable& tab, CallTable* dst, Stats* stats, bool reset_stats, hipStream_t s) {
-    hipLaunchKernelGGL(k_setup, dim3(1), dim3(MAX_SLOTS), 0, s, tab, dst, stats, reset_stats ? 1 : 0);
-    return hipGetLastError();
-}
-hipError_t launch_fill_f32(float* p, int64_t n, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fill_f32, dim3(blocks_for(n, 4096)), dim3(BLOCK), 0, s, p, n);
-    return hipGetLastError();
-}
-hipError_t launch_fill_f64(double* p, int64_t n, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fill_f64, dim3(blocks_for(n, 4096)), dim3(BLOCK), 0, s, p, n);
+hipError_t launch_setup(const CallTable& tab, CallTable* dst, Stats* stats, bool reset_stats, int* counts, float* img,
+                        int64_t n_img, double* gacc, int64_t n_gacc, hipStream_t s) {
+    const int64_t n = n_img > n_gacc ? n_img : n_gacc;
+    hipLaunchKernelGGL(k_setup, dim3(blocks_for(n, 4096)), dim3(BLOCK), 0, s, tab, dst, stats, reset_stats ? 1 : 0, counts,
+                       img, n_img, gacc, n_gacc);
     return hipGetLastError();
 }
 hipError_t launch_finalize(const CallTable* tab, const double* gacc, int n_slots, int64_t max_numel, hipStream_t s) {
@@ -2110,11 +2276,59 @@ extern template __global__ void k_replay<true, true, false, false>(WArgs);
 extern template __global__ void k_replay<true, true, true, false>(WArgs);
 extern template __global__ void k_replay<false, true, false, true>(WArgs);
 
+// LDS of a gradient kernel: the workgroup accumulators, and the staging memory of texture scatters
+static size_t grad_lds(const WArgs& a) {
+    return (size_t)a.lds_nd * sizeof(double) + (size_t)a.lds_nf * sizeof(float) +
+           (a.lds_stage ? (size_t)(BLOCK / WAVE) * STAGE_WORDS * sizeof(float) : 0);
+}
+
+// Paths per wavefront of a small call, at least `least` and at most half a wavefront: spread over four wavefronts
+// per SIMD where the tree is deep (a path's rays then differ, and wait for each other), over two where it is
+// shallow and shading, the same for every wavefront, is the larger part (16,384 paths of the 20.5k-triangle scene
+// 361 us against 398, of the 3-sphere scene 128 us against 96).
+constexpr int SMALL_LEAST = 2, SMALL_LEAST_ADJ = 4, SMALL_WAVES_DEEP = 4096, SMALL_WAVES_SHALLOW = 2048;
+static int small_per_wave(const WArgs& a, int least) {
+    const int waves = a.stack_cap > SHALLOW_STACK ? SMALL_WAVES_DEEP : SMALL_WAVES_SHALLOW;
+    const int pw = (a.n_chunk + waves - 1) / waves;
+    return pw < least ? least : pw > WAVE / 2 ? WAVE / 2 : pw;
+}
+
 // A traversal launch, with or without the work counters.
 template <int SMODE>
 static void launch_extend(const WArgs& a, int grid, size_t lds, hipStream_t s) {
     if (a.stats) hipLaunchKernelGGL((k_extend<SMODE, true>), dim3(grid), dim3(BLOCK), lds, s, a);
     else hipLaunchKernelGGL((k_extend<SMODE, false>), dim3(grid), dim3(BLOCK), lds, s, a);
+}
+
+// A small call: its paths in one launch, then the pixel reduction or the reverse walk.
+template <int MODE>
+static void launch_paths(const WArgs& a, int per_wave, size_t lds, hipStream_t s) {
+    const int per_block = per_wave * (BLOCK / WAVE), grid = (a.n_chunk + per_block - 1) / per_block;
+    if (a.stats) hipLaunchKernelGGL((k_paths<MODE, true>), dim3(grid), dim3(BLOCK), lds, s, a, per_wave);
+    else hipLaunchKernelGGL((k_paths<MODE, false>), dim3(grid), dim3(BLOCK), lds, s, a, per_wave);
+}
+static void launch_small_paths(const WArgs& a, int mode, hipStream_t s) {
+    const size_t lds = (size_t)a.stack_cap * BLOCK * sizeof(int);
+    const int pw = small_per_wave(a, SMALL_LEAST);
+    if (mode == 0 && a.r1) launch_paths<4>(a, pw, lds, s);
+    else if (mode == 0) launch_paths<0>(a, pw, lds, s);
+    else if (a.ckpt > 0) launch_paths<2>(a, pw, lds, s);
+    else if (a.r1adj) launch_paths<6>(a, pw, lds, s);
+    else launch_paths<5>(a, pw, lds, s);
+}
+static hipError_t launch_small(const WArgs& a, int mode, const LaunchGrid& G, hipStream_t s) {
+    launch_small_paths(a, mode, s);
+    if (mode == 0) {
+        const int gb = blocks_for(a.n_chunk, G.other);
+        if (a.out && a.r1) hipLaunchKernelGGL(k_accum<true>, dim3(gb), dim3(BLOCK), 0, s, a);
+        else if (a.out) hipLaunchKernelGGL(k_accum<false>, dim3(gb), dim3(BLOCK), 0, s, a);
+        return hipGetLastError();
+    }
+    const int aw = small_per_wave(a, SMALL_LEAST_ADJ), per_block = aw * (BLOCK / WAVE);
+    const int grid = (a.n_chunk + per_block - 1) / per_block;
+    if (a.r1adj) hipLaunchKernelGGL(k_adjoint_paths<true>, dim3(grid), dim3(BLOCK), grad_lds(a), s, a, aw);
+    else hipLaunchKernelGGL(k_adjoint_paths<false>, dim3(grid), dim3(BLOCK), grad_lds(a), s, a, aw);
+    return hipGetLastError();
 }
 
 // One chunk of paths through every bounce.  mode 0: render, 1: backward.  M is told the family
@@ -2127,16 +2341,23 @@ hipError_t launch_chunk(WArgs a, const PathState& S2, int mode, const LaunchGrid
     a.r1adj = a.adj && a.r1 ? 1 : 0;
     if (mode != 0 || !a.S.nv) a.r1 = 0;  // (the rank-one record is the render's, with its vertex flags)
     size_t lds = (size_t)a.stack_cap * BLOCK * sizeof(int);
-    M(KF_OTHER, s);
-    hipLaunchKernelGGL(k_reset_counts, dim3(1), dim3(64), 0, s, a.S.counts);
+    if (a.small && (mode == 0 || a.adj)) return launch_small(a, mode, G, s);
+    if (a.g0 > 0) {  // (the first chunk's counts were cleared with the call's other memory)
+        M(KF_OTHER, s);
+        hipLaunchKernelGGL(k_reset_counts, dim3(1), dim3(64), 0, s, a.S.counts);
+    }
     int gb = blocks_for(a.n_chunk, G.other);
     // (traversal's grid: enough workgroups for the most spread queue)
     const int xg = blocks_for((int64_t)a.n_chunk * (WAVE / SPREAD_DEEP), a.stats ? G.extend_st : G.extend);
     a.qin = 0;
     a.first = 1;
-    M(KF_EXTEND, s);
-    launch_extend<-2>(a, xg, lds, s);  // (camera rays generated in the launch)
-    for (int b = 1; b <= a.max_depth; ++b) {
+    if (a.small) {  // (the hybrid replay's forward pass)
+        launch_small_paths(a, mode, s);
+    } else {
+        M(KF_EXTEND, s);
+        launch_extend<-2>(a, xg, lds, s);  // (camera rays generated in the launch)
+    }
+    for (int b = 1; b <= a.max_depth && !a.small; ++b) {
         a.qin = (b - 1) & 1;
         a.first = b == 1;
         // (cached backward: the second bounce's hits are the paths of two or more vertices, the
@@ -2188,8 +2409,7 @@ hipError_t launch_chunk(WArgs a, const PathState& S2, int mode, const LaunchGrid
             else hipLaunchKernelGGL(k_accum<false>, dim3(gb), dim3(BLOCK), 0, s, a);
         }
     } else {
-        const size_t glds = (size_t)a.lds_nd * sizeof(double) + (size_t)a.lds_nf * sizeof(float) +
-                            (a.lds_stage ? (size_t)(BLOCK / WAVE) * STAGE_WORDS * sizeof(float) : 0);
+        const size_t glds = grad_lds(a);
         if (a.adj) {
             // grids: as many workgroups per compute unit as this call's accumulator size and the
             // variant's registers allow
