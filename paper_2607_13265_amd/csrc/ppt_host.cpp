@@ -531,7 +531,7 @@ static WsLayout ws_layout(const ppt_plan* p, int op, int32_t Qslots, bool packed
     auto take = [&](size_t bytes) { size_t r = at; at = align256(at + bytes); return r; };
     L.table = take(sizeof(CallTable));
     L.stats = take(sizeof(Stats));
-    L.counts = take(32);
+    L.counts = take(COUNT_INTS * 4);
     L.ray = take(RAY_F4 * 16 * Q);
     const bool adj = op == 1 && cached_adjoint(p);
     L.shd = take(op == 0 && rank_one(p) ? 0 : (adj ? SHD1_F4 : SHD_F4) * 16 * Q);
@@ -555,7 +555,7 @@ static WsLayout ws_layout(const ppt_plan* p, int op, int32_t Qslots, bool packed
     L.q0 = take(4 * Q); L.q1 = take(4 * Q); L.sq = take(4 * Q); L.hq = take(4 * Q); L.hf = take(Q);
     const bool prb = op == 1 && p->adjoint == PPT_ADJOINT_PRB;
     const size_t Q2 = prb ? Q : 0;
-    L.counts2 = take(prb ? 32 : 0);
+    L.counts2 = take(prb ? COUNT_INTS * 4 : 0);
     L.ray2 = take(RAY_F4 * 16 * Q2); L.shd2 = take(SHD_F4 * 16 * Q2); L.acc2 = take(ACC_F4 * 16 * Q2);
     L.q0_2 = take(4 * Q2); L.q1_2 = take(4 * Q2); L.sq2 = take(4 * Q2); L.hq2 = take(4 * Q2); L.hf2 = take(Q2);
     L.gacc_n = 0;

@@ -82,13 +82,19 @@ DEV void sig_add(uint64_t& h, uint32_t x) {
 
 // Work distribution of the persistent kernels.  Only the first ceil(n / BLOCK) workgroups take
 // part (fetch_active; the others leave at once).  Active wavefront w first takes the static batch
-// [w * s, (w + 1) * s) with s = n / active wavefronts rounded up and kept in [FETCH_MIN,
-// FETCH_BATCH]; positions beyond all static batches are handed out in batches of FETCH_BATCH
-// through one atomic on a counter that the previous kernel cleared.  A queue of up to FETCH_BATCH
-// positions per wavefront is thus covered by the static batches alone, with no atomic (rounding s
-// down to whole wavefronts left up to half of a mid-sized queue to the atomic batches, whose
-// early round ends for refill made such launches slower).  A wavefront gives its positions, in
-// order, to its lanes that have no work; every lane of the wavefront must call take().
+// [w * s, (w + 1) * s) with s = n / active wavefronts rounded up and kept in [FETCH_MIN, batch];
+// positions beyond all static batches are handed out in batches through one atomic on a counter that an earlier
+// kernel cleared, one of WORK_SHARDS: wavefront w takes from counter w mod WORK_SHARDS, whose t-th ticket is
+// batch t WORK_SHARDS + (w + t) mod WORK_SHARDS, so that no counter's batches keep to one part of an image.
+// On a single counter the additions (10 ns each, one after the other) took most of a camera-ray launch and
+// forced batches of 256; with 16 counters and batches of 64 (128 where each wavefront takes many) the
+// camera rays of 4.2M paths take 181 us instead of 340, those of the 128-view batch 6.1 ms a step
+// instead of 7.0, the walk of the 921,600 depth-128 paths 3.7 ms instead of 4.7, and launches end evenly.
+// (The forward replay and the tape's sweep keep batches of FETCH_REPLAY: with the paths of a wavefront handed
+// out together the hybrid replay's lanes meet their blocks together, 11.6 ms against 15.5.)
+// A queue of up to one batch per wavefront is covered by the static batches alone, with no atomic.  A
+// wavefront gives its positions, in order, to its lanes that have no work; every lane of the wavefront
+// must call take().
 //
 // Traversal spreads a queue that does not fill the GPU (least > 0): with fewer rays than lanes, a launch
 // lasts as long as its slowest wavefront, whose lanes wait for each other's descents and leaves, so
@@ -97,7 +103,7 @@ DEV void sig_add(uint64_t& h, uint32_t x) {
 // 304 -> 229 us, a 28,512-path step 1040 -> 873 us, the 3-sphere step 185 -> 180 us; one ray per wavefront
 // gains 2 % more and costs the smallest scene 10 %; from SPREAD_WAVES full wavefronts on, two per SIMD,
 // full wavefronts are the faster.
-constexpr int FETCH_MIN = WAVE, FETCH_BATCH = 4 * WAVE;
+constexpr int FETCH_MIN = WAVE, FETCH_BATCH = 2 * WAVE, FETCH_REPLAY = 4 * WAVE, FETCH_SHARE = 8;
 constexpr int SPREAD_DEEP = 2, SPREAD_SHALLOW = 8, SPREAD_WAVES = 2048, SHALLOW_STACK = 10;
 DEV int spread_least(const WArgs& A) { return A.stack_cap > SHALLOW_STACK ? SPREAD_DEEP : SPREAD_SHALLOW; }
 DEV int fetch_min(int n, int least) { return least ? max(least, min(FETCH_MIN, (n + SPREAD_WAVES - 1) / SPREAD_WAVES)) : FETCH_MIN; }
@@ -106,40 +112,49 @@ DEV int fetch_blocks(int n, int per_wave) {
     return max(1, min((int)gridDim.x, (n + per_block - 1) / per_block));
 }
 DEV bool fetch_active(int n, int least = 0) { return (int)blockIdx.x < fetch_blocks(n, fetch_min(n, least)); }
+DEV int* work_counter(const PathState& S, int set, int shard) {
+    return S.counts + WORK_FIRST + (set * WORK_SHARDS + shard) * WORK_LINE;
+}
+// the next ticket of a work counter, wave-uniform (every lane of the wavefront calls it)
+DEV int work_ticket(const PathState& S, int set, int wave) {
+    const int shard = wave & (WORK_SHARDS - 1);
+    int t = 0;
+    if (lane_id() == 0) t = atomicAdd(work_counter(S, set, shard), 1);
+    t = __builtin_amdgcn_readfirstlane(t);
+    return t * WORK_SHARDS + ((shard + t) & (WORK_SHARDS - 1));
+}
+DEV int wave_number() { return blockIdx.x * (BLOCK / WAVE) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE)); }
 struct WaveFetch {
     int c, cend;    // the wavefront's current batch [c, cend)
     int stat;       // positions covered by the static batches
+    int batch;      // positions per ticket
     bool exhausted;
-    DEV explicit WaveFetch(int n, int least = 0) {
+    DEV explicit WaveFetch(int n, int least = 0, bool replay = false) {
         const int smin = fetch_min(n, least);
         const int waves = fetch_blocks(n, smin) * (BLOCK / WAVE);
-        // (readfirstlane: the wavefront's number, known uniform, keeps the fetch state in scalar registers)
-        const int w = blockIdx.x * (BLOCK / WAVE) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+        const int w = wave_number();  // (known uniform: the fetch state stays in scalar registers)
+        batch = replay ? FETCH_REPLAY : max(FETCH_MIN, min(FETCH_BATCH, n / (FETCH_SHARE * waves)));
         int sb = (n + waves - 1) / waves;
-        sb = sb < smin ? smin : (sb > FETCH_BATCH ? FETCH_BATCH : sb);
+        sb = sb < smin ? smin : (sb > batch ? batch : sb);
         stat = waves * sb;
         c = min(w * sb, n);
         cend = min(c + sb, n);
         exhausted = n <= stat;
     }
-    DEV int take(bool need, int n, int* grab) {
+    DEV int take(bool need, int n, const PathState& S, int set) {
         const unsigned long long m = __ballot(need);
         const int k = (int)__popcll(m), rank = (int)__popcll(m & ((1ull << lane_id()) - 1ull));
         const int rem = cend - c;
         int nb = -1;
-        if (k > rem && !exhausted) {
-            int base = 0;
-            if (lane_id() == 0) base = atomicAdd(grab, FETCH_BATCH);
-            nb = stat + __builtin_amdgcn_readfirstlane(__shfl(base, 0, WAVE));
-        }
+        if (k > rem && !exhausted) nb = stat + work_ticket(S, set, wave_number()) * batch;
         int idx = -1;
         if (need) {
             if (rank < rem) idx = c + rank;
-            else if (nb >= 0 && nb + (rank - rem) < min(nb + FETCH_BATCH, n)) idx = nb + (rank - rem);
+            else if (nb >= 0 && nb + (rank - rem) < min(nb + batch, n)) idx = nb + (rank - rem);
         }
         if (nb >= 0) {
             if (nb >= n) { exhausted = true; c = cend = 0; }
-            else { cend = min(nb + FETCH_BATCH, n); c = min(nb + (k - rem), cend); }
+            else { cend = min(nb + batch, n); c = min(nb + (k - rem), cend); }
         } else {
             c = min(c + k, cend);
         }
@@ -297,7 +312,7 @@ DEV DevWorld world_of(const WArgs& A, const DevView& V) { return A.one_world ? A
 // ============================================================================ chunk start
 #ifndef PPT_EXT_TU  // (non-template kernels: in the main compilation unit only)
 __global__ void k_reset_counts(int* counts) {
-    if (threadIdx.x < 8) counts[threadIdx.x] = 0;
+    for (int k = threadIdx.x; k < COUNT_INTS; k += BLOCK) counts[k] = 0;
 }
 
 #endif  // PPT_EXT_TU
@@ -463,7 +478,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STAT
     int slot = -1, info = 0;
     ViewRange range;  // (camera rays)
     while (true) {
-        const int idx = F.take(!alive, n, &S.counts[5]);
+        const int idx = F.take(!alive, n, S, WORK_TRAVERSAL);
         if constexpr (SMODE == -2) {
             view_find(A, range, idx >= 0, A.g0 + idx);
             if (idx >= 0) {
@@ -535,9 +550,9 @@ __global__ void __launch_bounds__(BLOCK) k_compact(WArgs A) {
     PathState& S = A.S;
     const int* qin = A.qin ? S.queue1 : S.queue0;
     const int n = A.first ? A.n_chunk : S.counts[A.qin];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        S.counts[2] = 0;  // the shadow queue the shading kernel appends to (the traversal read it)
-        S.counts[5] = 0;  // the work counter of the next traversal launch
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) S.counts[2] = 0;  // the shadow queue the shading kernel appends to (the traversal read it)
+        if (threadIdx.x < WORK_SHARDS) *work_counter(S, WORK_TRAVERSAL, threadIdx.x) = 0;  // (of the next traversal launch)
     }
     __shared__ BlockQueue qh;
     if (threadIdx.x == 0) qh.n = 0;
@@ -968,7 +983,7 @@ __global__ void __launch_bounds__(BLOCK) k_paths(WArgs A, int per_wave) {
     K.tab = &tab;
     __syncthreads();
     const PathState& S = A.S;
-    const int wave = blockIdx.x * (BLOCK / WAVE) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    const int wave = wave_number();
     const int lane = lane_id(), mate = lane & (WAVE / 2 - 1);  // (the lower lane of this lane's path)
     const bool lower = lane < WAVE / 2;
     const int slot = wave * per_wave + mate;
@@ -1599,7 +1614,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HYB 
     __shared__ CallTable tab;
     adjoint_begin(A, K, &tab, lds_grad);
     const int n = S.counts[3];
-    WaveFetch F(n);
+    WaveFetch F(n, 0, true);
     int slot = -1, b = 0, B = 0, v = 0;
     uint32_t pix = 0, smp = 0;
     bool prev_delta = false;
@@ -1615,7 +1630,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HYB 
     uint32_t n_br[3] = {0u, 0u, 0u};
     while (true) {
         // hand queue entries to the lanes without a path
-        const int idx = F.take(slot < 0, n, &S.counts[4]);
+        const int idx = F.take(slot < 0, n, S, WORK_REPLAY);
         if (idx >= 0) {
             slot = S.queue0[idx];
             // the path's start as the fold left it in the shadow-record array (one record per path)
@@ -1806,7 +1821,7 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint_deep(WArgs A) {
 #pragma unroll
     for (int k = 0; k < 12; ++k) L[k] = 0.0f;
     while (true) {
-        const int idx = F.take(slot < 0, n, &S.counts[4]);
+        const int idx = F.take(slot < 0, n, S, WORK_REPLAY);
         if (idx >= 0) {
             slot = S.dqueue[idx];
             const float4 r3 = ray_rec(S, slot)[3];
@@ -1844,7 +1859,7 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint_deep(WArgs A) {
 // escaped camera rays), with the suffix beyond it from k_adjoint_deep, and adds the polarizer-angle
 // term delta^T (dP/dtheta) R_s L[1].  A wavefront takes runs of ADJ_RUN paths from a counter (a fixed
 // stride walks the same part of every view of a batch of equal views, and the wavefronts on its
-// objects end last: 5.1 ms against 4.0 ms on the 128-view batch), long enough that its lanes seldom change
+// objects end last: 5.2 ms against 2.7 ms on the 128-view batch), long enough that its lanes seldom change
 // view and keep the angle term in a register until they do.
 constexpr int ADJ_RUN = 8 * WAVE;
 __global__ void __launch_bounds__(BLOCK) k_adjoint_first(WArgs A) {
@@ -1864,9 +1879,7 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint_first(WArgs A) {
     float gtheta = 0.0f, C2 = 1.0f, S2 = 0.0f;
     int tkey = -1, angle_of = -1;
     while (true) {
-        int r0 = 0;
-        if (lane_id() == 0) r0 = atomicAdd(&S.counts[6], run);
-        r0 = __builtin_amdgcn_readfirstlane(r0);
+        const int r0 = work_ticket(S, WORK_ADJOINT, wave_number()) * run;
         if (r0 >= n) break;
         for (int base = r0; base < min(r0 + run, n); base += WAVE) {
             const int i = base + lane_id();
@@ -1930,7 +1943,7 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint_paths(WArgs A, int per_wave) 
     __shared__ CallTable tab;
     adjoint_begin(A, K, &tab, lds_grad);
     K.coherent = false;
-    const int wave = blockIdx.x * (BLOCK / WAVE) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+    const int wave = wave_number();
     const int i = wave * per_wave + lane_id();
     const int B = lane_id() < per_wave && i < A.n_chunk ? (int)S.nv[i] : 0;
     int v = 0, tkey = -1;
@@ -2068,7 +2081,7 @@ __global__ void __launch_bounds__(BLOCK) k_tape_reverse(WArgs A) {
     __shared__ CallTable tab;
     adjoint_begin(A, K, &tab, lds_grad);
     const int n = S.counts[3];
-    WaveFetch F(n);
+    WaveFetch F(n, 0, true);
     int slot = -1, b = 0, v = 0;
     uint32_t pix = 0, smp = 0;
     float a0[12], bbar[48];  // adjoint at the sensor; adjoint of beta_{b+1} per channel (4x4, row-major)
@@ -2077,7 +2090,7 @@ __global__ void __launch_bounds__(BLOCK) k_tape_reverse(WArgs A) {
 #pragma unroll
     for (int k = 0; k < 48; ++k) bbar[k] = 0.0f;
     while (true) {
-        const int idx = F.take(slot < 0, n, &S.counts[4]);
+        const int idx = F.take(slot < 0, n, S, WORK_REPLAY);
         if (idx >= 0) {
             slot = S.queue0[idx];
             const float4 r3 = ray_rec(S, slot)[3];
@@ -2179,7 +2192,7 @@ __global__ void k_setup(CallTable tab, CallTable* dst, Stats* stats, int reset_s
         const int i = threadIdx.x;
         if (i < ST_COUNT && reset_stats) stats->c[i] = 0ull;
         if (i < 3 && reset_stats) stats->hyb[i] = 0ull;
-        if (i < 8) counts[i] = 0;
+        for (int k = i; k < COUNT_INTS; k += BLOCK) counts[k] = 0;
     }
     const int64_t i0 = (int64_t)blockIdx.x * BLOCK + threadIdx.x, step = (int64_t)gridDim.x * BLOCK;
     for (int64_t i = i0; i < n_img; i += step) img[i] = 0.0f;
@@ -2344,7 +2357,7 @@ hipError_t launch_chunk(WArgs a, const PathState& S2, int mode, const LaunchGrid
     if (a.small && (mode == 0 || a.adj)) return launch_small(a, mode, G, s);
     if (a.g0 > 0) {  // (the first chunk's counts were cleared with the call's other memory)
         M(KF_OTHER, s);
-        hipLaunchKernelGGL(k_reset_counts, dim3(1), dim3(64), 0, s, a.S.counts);
+        hipLaunchKernelGGL(k_reset_counts, dim3(1), dim3(BLOCK), 0, s, a.S.counts);
     }
     int gb = blocks_for(a.n_chunk, G.other);
     // (traversal's grid: enough workgroups for the most spread queue)
@@ -2446,7 +2459,7 @@ hipError_t launch_chunk(WArgs a, const PathState& S2, int mode, const LaunchGrid
             b2.out = nullptr;
             for (int b1 = 1; b1 < a.max_depth; ++b1) {
                 M(KF_OTHER, s);
-                hipLaunchKernelGGL(k_reset_counts, dim3(1), dim3(64), 0, s, b2.S.counts);
+                hipLaunchKernelGGL(k_reset_counts, dim3(1), dim3(BLOCK), 0, s, b2.S.counts);
                 hipLaunchKernelGGL(k_prb_start, dim3(gb), dim3(BLOCK), 0, s, a, S2, b1);
                 b2.seed = prb_seed_host(a.seed, (uint32_t)(b1 + 1));
                 b2.qin = 0;
