@@ -148,9 +148,12 @@ struct LaunchMarker {
     void operator()(int family, hipStream_t s) const { if (fn) fn(ctx, family, s); }
 };
 
-// Work counters of the persistent kernels: WORK_SHARDS counters for each of WORK_SETS uses, every one in a
+// Queue sizes (the two ray queues, the shadow queue, the replay or reverse-walk queue, the hit queue) and
+// work counters of the persistent kernels: WORK_SHARDS counters for each of WORK_SETS uses, every one in a
 // cache line of its own (additions to one address pass one after the other, some 10 ns apart).
-constexpr int WORK_SHARDS = 16, WORK_LINE = 32, WORK_FIRST = WORK_LINE;
+constexpr int WORK_SHARDS = 16, WORK_LINE = 32, WORK_FIRST = 5 * WORK_LINE;
+__host__ __device__ constexpr int CNT_RAY(int q) { return q * WORK_LINE; }
+constexpr int CNT_SHADOW = 2 * WORK_LINE, CNT_REPLAY = 3 * WORK_LINE, CNT_HIT = 4 * WORK_LINE;
 constexpr int WORK_TRAVERSAL = 0, WORK_REPLAY = 1, WORK_ADJOINT = 2, WORK_SETS = 3;
 constexpr int COUNT_INTS = WORK_FIRST + WORK_SETS * WORK_SHARDS * WORK_LINE;
 
@@ -174,8 +177,7 @@ struct PathState {
     int* squeue;    // shadow-ray queue
     int* hqueue;    // queue of the rays of this bounce that hit a surface (input of the shading kernel)
     uint8_t* hflag; // [Q] outcome of the slot's last closest-hit ray: 0 miss, 1 hit, 2 no ray (masked path)
-    int* counts;    // COUNT_INTS ints: [0], [1] sizes of queue0, queue1; [2] size of the shadow queue; [3] size of
-                    // the replay queue; [7] size of the hit queue; from WORK_FIRST on the work counters
+    int* counts;    // COUNT_INTS ints: queue sizes (CNT_*) and work counters
 };
 
 struct WArgs {

@@ -461,13 +461,13 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STAT
     trav_stack_init(stack);
     PathState& S = A.S;
     if (blockIdx.x == 0 && threadIdx.x == 0) {  // the queues the following kernels append to
-        S.counts[1 - A.qin] = 0;
-        S.counts[7] = 0;
-        if (SMODE < 0) S.counts[2] = 0;  // (a launch with shadow rays reads it: compaction clears it)
+        S.counts[CNT_RAY(1 - A.qin)] = 0;
+        S.counts[CNT_HIT] = 0;
+        if (SMODE < 0) S.counts[CNT_SHADOW] = 0;  // (a launch with shadow rays reads it: compaction clears it)
     }
     const int* q = A.qin ? S.queue1 : S.queue0;
-    const int ne = A.first ? A.n_chunk : S.counts[A.qin];
-    const int ns = SMODE >= 0 ? S.counts[2] : 0;
+    const int ne = A.first ? A.n_chunk : S.counts[CNT_RAY(A.qin)];
+    const int ns = SMODE >= 0 ? S.counts[CNT_SHADOW] : 0;
     const int n = ns + ne;
     const int least = spread_least(A);
     if (!fetch_active(n, least)) return;
@@ -540,38 +540,74 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(STAT
     if (STATS) flush_stats(A.stats, cnt);
 }
 
+#ifndef PPT_EXT_TU  // (in the main compilation unit only)
 // ============================================================================ hit compaction
 // Splits the rays of this bounce by the outcome byte traversal wrote for each slot: misses end their
 // path here (signature; a camera ray that escapes keeps a vertex count of 0, which the pixel
 // reduction reads as no radiance), hits go, in queue order, to the hit queue that the shading kernel
 // reads, so its lanes all hold a vertex.
-template <int MODE>
+// A workgroup takes tiles of up to COMPACT_ITEMS positions per thread (COMPACT_TILES tiles while they are
+// smaller) and adds to the hit queue's size once per
+// tile: the additions of all workgroups to that one word pass one after the other, 10 ns each (with a flush
+// per 1,800 hits and one at every workgroup's end they took most of the launch: 24 us for 0.9M rays,
+// now 11 us).
+constexpr int COMPACT_ITEMS = 16, COMPACT_TILES = 512;
 __global__ void __launch_bounds__(BLOCK) k_compact(WArgs A) {
     PathState& S = A.S;
     const int* qin = A.qin ? S.queue1 : S.queue0;
-    const int n = A.first ? A.n_chunk : S.counts[A.qin];
+    const int n = A.first ? A.n_chunk : S.counts[CNT_RAY(A.qin)];
     if (blockIdx.x == 0) {
-        if (threadIdx.x == 0) S.counts[2] = 0;  // the shadow queue the shading kernel appends to (the traversal read it)
+        if (threadIdx.x == 0) S.counts[CNT_SHADOW] = 0;  // the shadow queue the shading kernel appends to (the traversal read it)
         if (threadIdx.x < WORK_SHARDS) *work_counter(S, WORK_TRAVERSAL, threadIdx.x) = 0;  // (of the next traversal launch)
     }
-    __shared__ BlockQueue qh;
-    if (threadIdx.x == 0) qh.n = 0;
-    __syncthreads();
-    for (int bb = blockIdx.x * BLOCK; bb < n; bb += gridDim.x * BLOCK) {
-        const int i = bb + threadIdx.x;
-        bool hit = false;
-        int slot = 0;
-        if (i < n) {
-            slot = A.first ? i : qin[i];
-            const int f = S.hflag[slot];  // (a byte per ray instead of the hit words of its record)
-            hit = f == 1;
-            if (f == 0 && A.sig) sig_add(A.sig[A.g0 + slot], 0xffffffffu);
+    constexpr int WAVES = BLOCK / WAVE;
+    static_assert(COMPACT_ITEMS * WAVES <= WAVE, "one wavefront scans a tile's counts");
+    __shared__ int at[WAVE];  // hits of (item, wavefront), then where they go
+    const int wave = threadIdx.x / WAVE, lane = lane_id();
+    const int items = max(1, min(COMPACT_ITEMS, (n + COMPACT_TILES * BLOCK - 1) / (COMPACT_TILES * BLOCK)));
+    for (int t0 = blockIdx.x * items * BLOCK; t0 < n; t0 += gridDim.x * items * BLOCK) {
+        int slot[COMPACT_ITEMS], rank[COMPACT_ITEMS];
+        if (threadIdx.x < WAVE) at[threadIdx.x] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < COMPACT_ITEMS; ++k) {
+            rank[k] = -1;
+            if (k >= items) continue;
+            const int i = t0 + k * BLOCK + threadIdx.x;
+            bool hit = false;
+            if (i < n) {
+                slot[k] = A.first ? i : qin[i];
+                const int f = S.hflag[slot[k]];  // (a byte per ray instead of the hit words of its record)
+                hit = f == 1;
+                if (f == 0 && A.sig) sig_add(A.sig[A.g0 + slot[k]], 0xffffffffu);
+            }
+            const uint64_t m = __ballot(hit);
+            if (hit) rank[k] = (int)__popcll(m & ((1ull << lane) - 1ull));
+            if (lane == 0) at[k * WAVES + wave] = (int)__popcll(m);
         }
-        bq_push(qh, hit, slot);
-        bq_flush(qh, &S.counts[7], S.hqueue, false);
+        __syncthreads();
+        if (wave == 0) {
+            const int c = at[lane];
+            int sum = c;
+#pragma unroll
+            for (int o = 1; o < WAVE; o <<= 1) {
+                const int up = __shfl_up(sum, o, WAVE);
+                if (lane >= o) sum += up;
+            }
+            const int total = __shfl(sum, WAVE - 1, WAVE);
+            int base = 0;
+            if (lane == 0 && total) base = atomicAdd(&S.counts[CNT_HIT], total);
+            at[lane] = __shfl(base, 0, WAVE) + sum - c;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < COMPACT_ITEMS; ++k)
+            if (rank[k] >= 0) S.hqueue[at[k * WAVES + wave] + rank[k]] = slot[k];
+        __syncthreads();
     }
-    bq_flush(qh, &S.counts[7], S.hqueue, true);
 }
+
+#endif  // PPT_EXT_TU
 
 // ============================================================================ sensor adjoint
 // dL/dI of a pixel (analyzer a, per sample) and the adjoint rows at the camera ray it gives:
@@ -921,8 +957,8 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MODE
     PathState& S = A.S;
     Call K{A.table, nullptr};
     int* qout = A.qin ? S.queue0 : S.queue1;
-    const int n = S.counts[7];
-    if (ADJ && A.keep_deep && blockIdx.x == 0 && threadIdx.x == 0) S.counts[3] = n;
+    const int n = S.counts[CNT_HIT];
+    if (ADJ && A.keep_deep && blockIdx.x == 0 && threadIdx.x == 0) S.counts[CNT_REPLAY] = n;
     __shared__ BlockQueue qn, qs;
     __shared__ CallTable tab;
     table_to_lds(&tab, A.table);
@@ -938,11 +974,11 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MODE
         if (i < n) shade_slot<MODE, EXT>(A, K, slot, cnt, cont, shadow);  // (a queued ray is a live path's hit)
         bq_push(qn, cont, slot);
         bq_push(qs, shadow, slot);
-        bq_flush(qn, &S.counts[1 - A.qin], qout, false);
-        bq_flush(qs, &S.counts[2], S.squeue, false);
+        bq_flush(qn, &S.counts[CNT_RAY(1 - A.qin)], qout, false);
+        bq_flush(qs, &S.counts[CNT_SHADOW], S.squeue, false);
     }
-    bq_flush(qn, &S.counts[1 - A.qin], qout, true);
-    bq_flush(qs, &S.counts[2], S.squeue, true);
+    bq_flush(qn, &S.counts[CNT_RAY(1 - A.qin)], qout, true);
+    bq_flush(qs, &S.counts[CNT_SHADOW], S.squeue, true);
     flush_stats(A.stats, cnt);
 }
 
@@ -1415,9 +1451,9 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HYB 
             }
         }
         bq_push(rq, push, i);
-        bq_flush(rq, &S.counts[3], S.queue0, false);
+        bq_flush(rq, &S.counts[CNT_REPLAY], S.queue0, false);
     }
-    bq_flush(rq, &S.counts[3], S.queue0, true);
+    bq_flush(rq, &S.counts[CNT_REPLAY], S.queue0, true);
     flush_theta(A, K, tkey, gtheta);
 }
 
@@ -1613,7 +1649,7 @@ __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HYB 
     Call K{A.table, A.gacc};
     __shared__ CallTable tab;
     adjoint_begin(A, K, &tab, lds_grad);
-    const int n = S.counts[3];
+    const int n = S.counts[CNT_REPLAY];
     WaveFetch F(n, 0, true);
     int slot = -1, b = 0, B = 0, v = 0;
     uint32_t pix = 0, smp = 0;
@@ -1811,7 +1847,7 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint_deep(WArgs A) {
     const int Q = A.Q;
     Call K{A.table, A.gacc};
     __shared__ CallTable tab;
-    const int n = S.counts[3];
+    const int n = S.counts[CNT_REPLAY];
     if (!fetch_active(n) || n == 0) return;
     adjoint_begin(A, K, &tab, lds_grad);
     WaveFetch F(n);
@@ -2080,7 +2116,7 @@ __global__ void __launch_bounds__(BLOCK) k_tape_reverse(WArgs A) {
     Call K{A.table, A.gacc};
     __shared__ CallTable tab;
     adjoint_begin(A, K, &tab, lds_grad);
-    const int n = S.counts[3];
+    const int n = S.counts[CNT_REPLAY];
     WaveFetch F(n, 0, true);
     int slot = -1, b = 0, v = 0;
     uint32_t pix = 0, smp = 0;
@@ -2359,7 +2395,7 @@ hipError_t launch_chunk(WArgs a, const PathState& S2, int mode, const LaunchGrid
         M(KF_OTHER, s);
         hipLaunchKernelGGL(k_reset_counts, dim3(1), dim3(BLOCK), 0, s, a.S.counts);
     }
-    int gb = blocks_for(a.n_chunk, G.other);
+    const int gb = blocks_for(a.n_chunk, G.other), cg = blocks_for(a.n_chunk, 4 * G.cu);
     // (traversal's grid: enough workgroups for the most spread queue)
     const int xg = blocks_for((int64_t)a.n_chunk * (WAVE / SPREAD_DEEP), a.stats ? G.extend_st : G.extend);
     a.qin = 0;
@@ -2379,8 +2415,7 @@ hipError_t launch_chunk(WArgs a, const PathState& S2, int mode, const LaunchGrid
         int* const hqueue = a.S.hqueue;
         if (a.keep_deep) a.S.hqueue = a.S.dqueue;
         M(KF_COMPACT, s);
-        if (mode == 0) hipLaunchKernelGGL(k_compact<0>, dim3(gb), dim3(BLOCK), 0, s, a);
-        else hipLaunchKernelGGL(k_compact<1>, dim3(gb), dim3(BLOCK), 0, s, a);
+        hipLaunchKernelGGL(k_compact, dim3(cg), dim3(BLOCK), 0, s, a);
         M(KF_SHADE, s);
         // (a grid sized to each variant's own occupancy measured slower for the render variant)
         const int sg = blocks_for(a.n_chunk, G.shade);
@@ -2471,7 +2506,7 @@ hipError_t launch_chunk(WArgs a, const PathState& S2, int mode, const LaunchGrid
                     b2.qin = (it - 1) & 1;
                     b2.first = it == 1;
                     M(KF_COMPACT, s);
-                    hipLaunchKernelGGL(k_compact<0>, dim3(gb), dim3(BLOCK), 0, s, b2);
+                    hipLaunchKernelGGL(k_compact, dim3(cg), dim3(BLOCK), 0, s, b2);
                     M(KF_SHADE, s);
                     hipLaunchKernelGGL((k_shade<0, false>), dim3(blocks_for(a.n_chunk, G.shade)), dim3(BLOCK), 0, s, b2);
                     if (bb < a.max_depth) {
@@ -2528,7 +2563,7 @@ hipError_t occupancy_grid(int cu, int stack_cap, LaunchGrid* G) {
     if ((r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&sh, k_shade<1, false>, BLOCK, 0)) != hipSuccess) return r;
     size_t glds = (size_t)LDS_GRAD_D * sizeof(double) + (size_t)LDS_GRAD_F * sizeof(float);
     if ((r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&ad, k_replay<false, false>, BLOCK, glds)) != hipSuccess) return r;
-    if ((r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&ot, k_compact<0>, BLOCK, 0)) != hipSuccess) return r;
+    if ((r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&ot, k_accum<true>, BLOCK, 0)) != hipSuccess) return r;
     G->extend = (e > 0 ? e : 1) * cu;
     G->extend_st = (es > 0 ? es : 1) * cu;
     G->shade = (sh > 0 ? sh : 1) * cu;
