@@ -802,11 +802,14 @@ int ppt_plan_launch_info(const ppt_plan* p, int64_t* chunk_paths, int32_t* n_chu
     return PPT_OK;
 }
 
-// A small call's paths run in one launch (not with the light-stage features; per-kernel timing keeps the
-// launches per bounce, whose families it tells apart).
-static bool small_call(const ppt_plan* p) { return p->num_paths <= SMALL_PATHS && !p->scene->has_ext && !p->timing; }
+// A small chunk's paths run in one launch (not with the light-stage features; per-kernel timing keeps the
+// launches per bounce, whose families it tells apart).  Q: paths per chunk.
+static bool small_call(const ppt_plan* p, int32_t Q) {
+    const int64_t most = p->max_depth >= SMALL_DEPTH ? SMALL_PATHS_DEEP : SMALL_PATHS;
+    return std::min<int64_t>(Q, p->num_paths) <= most && !p->scene->has_ext && !p->timing;
+}
 
-static int fill_table(const ppt_plan* p, const float* const* params, int32_t n_params, float* const* grads,
+static int fill_table(const ppt_plan* p, int32_t Q, const float* const* params, int32_t n_params, float* const* grads,
                       WsLayout& L, CallTable& t, int64_t* max_numel) {
     const ppt_scene* sc = p->scene;
     if (!params || n_params != (int32_t)sc->slot_numel.size()) return fail(PPT_EINVAL, "parameter count mismatch");
@@ -825,7 +828,7 @@ static int fill_table(const ppt_plan* p, const float* const* params, int32_t n_p
     // workgroup gradient accumulators: small slots in FP64, then textures in FP32 while they fit
     // (a small call's textures go to the global accumulator: clearing and flushing a texture's copy per
     // workgroup costs more than its few additions)
-    const bool no_tex = small_call(p) && cached_adjoint(p);
+    const bool no_tex = small_call(p, Q) && cached_adjoint(p);
     int nd = 0, nf = 0;
     for (int32_t i = 0; i < n_params; ++i) {
         if (t.goff[i] < 0) continue;
@@ -855,7 +858,7 @@ static WArgs make_args(const ppt_plan* p, uint64_t seed, void* ws, const WsLayou
     a.mask = p->mask;
     a.ext = p->scene->has_ext ? 1 : 0;  // kernels with normal/specular maps and circular emitters
     a.r1 = rank_one(p) ? 1 : 0;
-    a.small = small_call(p) ? 1 : 0;
+    a.small = small_call(p, Q) ? 1 : 0;
     if (p->scene->worlds.size() == 1) {
         a.one_world = 1;
         a.world0 = p->scene->worlds[0]->dev;
@@ -895,7 +898,7 @@ static int render_impl(const ppt_plan* p, const float* const* params, int32_t n_
     if (rc) return rc;
     if (!out && !sig) return fail(PPT_EINVAL, "null output");
     CallTable t;
-    if ((rc = fill_table(p, params, n_params, nullptr, L, t, nullptr))) return rc;
+    if ((rc = fill_table(p, p->Q, params, n_params, nullptr, L, t, nullptr))) return rc;
     hipStream_t s = (hipStream_t)stream;
     WArgs a = make_args(p, seed, ws, L, p->Q);
     a.out = out;
@@ -931,7 +934,7 @@ static int backward_impl(const ppt_plan* p, const float* const* params, int32_t 
     CallTable t;
     int64_t mx = 1;
     int rc;
-    if ((rc = fill_table(p, params, n_params, grads, L, t, &mx))) return rc;
+    if ((rc = fill_table(p, Q, params, n_params, grads, L, t, &mx))) return rc;
     hipStream_t s = (hipStream_t)stream;
     WArgs a = make_args(p, seed, ws, L, Q);
     if (!stats) a.stats = nullptr;

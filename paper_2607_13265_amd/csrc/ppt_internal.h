@@ -222,10 +222,13 @@ struct WArgs {
     DevWorld world0;
 };
 
-// A call of at most this many paths runs each path's bounces in one launch instead of three launches per
-// bounce (steps of the 20.5k-triangle scene, depth 6: 131,072 paths 970 -> 552 us, 262,144 paths 1123 -> 840 us,
-// 524,288 paths 1409 -> 1560 us: from there on the compacted queues fill the GPU better).
-constexpr int SMALL_PATHS = 1 << 18;
+// A chunk of at most this many paths runs each path's bounces in one launch instead of three launches per
+// bounce.  Steps of the 20.5k-triangle scene, depth 6: 131,072 paths 950 -> 551 us, 196,608 paths 1011 -> 687 us,
+// 4.2M paths in chunks of 196,608 16.7 -> 15.4 ms, but in chunks of 262,144 13.0 -> 14.2 ms: from there on the
+// compacted queues fill the GPU better.  Deep plans (SMALL_DEPTH and more), with three launches for each of
+// many bounces, gain further: 921,600 depth-128 paths in chunks of 262,144 59.1 -> 46.2 ms, 460,800 at once
+// 22.2 -> 21.5, 921,600 at once 34.3 -> 39.8.
+constexpr int SMALL_PATHS = 3 << 16, SMALL_PATHS_DEEP = 6 << 16, SMALL_DEPTH = 32;
 
 // workgroups per kernel family (extend_st: traversal with work counters); compute units
 struct LaunchGrid { int extend, shade, adjoint, other, cu, extend_st; };

@@ -49,7 +49,10 @@ def _views(kind, sensor, sizes, theta):
     ("tiny", sg.SENSOR_NONE, [(31, 1, 1), (0, 5, 3), (33, 2, 1)], 4, 0, {}),
     ("tiny", sg.SENSOR_ANALYZER4, [(64, 32, 4)], 1, 0, {}),
     ("ring", sg.SENSOR_POLARIZER, [(37, 29, 3)] * 3, 6, 0, dict(chunk_paths=1000)),
-    ("ring", sg.SENSOR_NONE, [(256, 128, 8)], 3, 0, {}),  # (the largest small call)
+    ("ring", sg.SENSOR_NONE, [(256, 128, 8)], 3, 0, {}),  # (above the limit of one chunk)
+    ("ring", sg.SENSOR_NONE, [(256, 128, 6)], 3, 0, {}),  # (the largest small call)
+    ("ring", sg.SENSOR_ANALYZER4, [(128, 128, 16)], 4, 0, dict(chunk_paths=100000)),  # (a larger call in small chunks)
+    ("worlds", sg.SENSOR_NONE, [(256, 256, 5)], 32, 0, {}),  # (the limit of deep plans)
     ("ring", sg.SENSOR_POLARIZER, [(64, 64, 2)], 5, 1, {}),  # (no next-event estimation)
     ("worlds", sg.SENSOR_POLARIZER, [(23, 17, 5)] * 4, 6, 0, {}),
     ("worlds", sg.SENSOR_ANALYZER4, [(40, 30, 1), (11, 7, 9)], 8, 0, {}),
