@@ -20,13 +20,15 @@ constexpr int STACK = 64;       // BVH traversal stack entries per lane
 //     [0] ro.x ro.y ro.z rd.x   [1] rd.y rd.z Cs Ss   [2] t u v prim   [3] info pix smp view-id
 //     (Cs, Ss: sensor rotation of the camera ray; view-id: the view's sampling identity; the hit is
 //     one aligned vector, written by traversal in one 16-byte store)
-//   shadow record, SHD_F4 = 8 vectors (128 B):
-//     [0] so.x so.y so.z tmax   [1] sd.x sd.y sd.z info (of the vertex whose light sample it is)
-//     [2..4] 12 Stokes words: the pending next-event contribution   [5..7] the backward's E_b (restored
-//     into the cache record for an occluded sample), or zeros.  After the fold (backward): [0] the
-//     camera ray's direction, info   [1] pix smp - -   [2..4] the replay's adjoint rows
+//   shadow array, SHD_F4 = 8 vectors (128 B) per slot.  During the bounces two dense arrays: the shadow
+//     rays (SHD1_F4 = 2 vectors: [0] so.x so.y so.z tmax   [1] sd.x sd.y sd.z info, of the vertex whose light
+//     sample it is), and behind them what an occluded sample restores (3 vectors: the full render's Lo, or
+//     the comparators' E_b of an emitting vertex).  The tape keeps whole records instead: [0..1] the shadow
+//     ray   [2..4] the pending next-event contribution   [5..7] its unweighted part.  After a fold, whole
+//     records: [0] the camera ray's direction, info   [1] pix smp - -   [2..4] the replay's adjoint rows
 //   accumulator record (render), ACC_F4 = 8 vectors (128 B):
-//     [0..3] prefix Mueller product beta (16)   [4] beta RGB scales (3)   [5..7] radiance Lo (12)
+//     [0..3] prefix Mueller product beta (16)   [4] beta RGB scales (3)   [5..7] radiance Lo (12),
+//     with a pending next-event part included as if visible
 //   rank-one render record (every view a linear polarizer), R1_F4 = 4 vectors (64 B, two to a cache
 //   line): [0] rho = q^T R_s beta   [1] RGB scales   [2] y_c = q^T R_s Lo_c (3), with a pending
 //   next-event part included as if visible   [3] y without that part (restored for an occluded

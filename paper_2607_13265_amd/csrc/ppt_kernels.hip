@@ -256,12 +256,16 @@ DEV float4* r1_rec(const PathState& S, int i) { return S.acc + (size_t)i * R1_F4
 // the rank-one render's shadow rays: a dense 32-byte record per slot behind the rank-one records
 DEV float4* r1_shd(const PathState& S, int Q, int i) { return S.acc + (size_t)Q * R1_F4 + (size_t)i * 2; }
 static_assert(R1_F4 + 2 <= ACC_F4, "the rank-one records and their shadow rays fit in the accumulator array");
-// The comparators' bounces (P-PRB, P-RB) use the shadow-record array as two dense arrays (the fold
-// later writes whole 128-byte records there): a 32-byte shadow ray per slot, four to a cache line,
-// and the 48-byte E_b of an emitting vertex behind them.  The cached backward keeps the shadow rays alone.
-static_assert(2 + 3 <= SHD_F4, "the dense shadow rays and the emitting E_b fit in the shadow-record array");
+// Except for the tape's, bounces use the shadow-record array as two dense arrays (a fold later writes whole
+// 128-byte records there): a 32-byte shadow ray per slot, four to a cache line, and behind them the 48 bytes
+// that an occluded light sample restores, the path's radiance (full render) or the E_b of an emitting vertex
+// (comparators).  The hybrid replay's and the cached backward's bounces use the shadow rays alone.  (In
+// whole 128-byte records with the pending next-event part, which traversal read for every ray and added to the
+// radiance of the visible ones, the full render of 43M paths of 12 bounces cost 27.4 ms of traversal and 9.1 of shading
+// instead of 25.0 and 8.6.)
+static_assert(2 + 3 <= SHD_F4, "the dense shadow rays and what they restore fit in the shadow-record array");
 DEV float4* shd1_rec(const PathState& S, int i) { return S.shd + (size_t)i * SHD1_F4; }
-DEV float4* emit1_rec(const PathState& S, int Q, int i) { return S.shd + (size_t)Q * 2 + (size_t)i * 3; }
+DEV float4* rest_rec(const PathState& S, int Q, int i) { return S.shd + (size_t)Q * 2 + (size_t)i * 3; }
 // cached backward: a vertex's record, and the adjoint row of a vertex after the first (b0 >= 1)
 DEV float4* vtx_rec(const PathState& S, int Q, int b0, int i) { return S.vtx + ((size_t)b0 * Q + i) * VTX_F4; }
 template <bool R1>
@@ -284,6 +288,11 @@ DEV void ld12(const float4* r, float* v) {
 DEV void st12(float4* r, const float* v) {
 #pragma unroll
     for (int k = 0; k < 3; ++k) r[k] = f4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
+}
+// a + b of two rounded values (never contracted with the product that gave one of them)
+DEV float add_rounded(float a, float b) {
+#pragma clang fp contract(off)
+    return a + b;
 }
 // ray record: origin and direction ([0], [1].xy); keys in [3]
 DEV void ray_od(const float4* R, v3& o, v3& d) {
@@ -374,7 +383,7 @@ DEV void camera_end(const WArgs& A, const ViewRange& range, int slot, const Trav
 template <int SMODE>
 DEV void shadow_begin(const WArgs& A, int slot, Trav& T, int& info) {
     const PathState& S = A.S;
-    const float4* H = SMODE == 4 ? r1_shd(S, A.Q, slot) : SMODE == 1 || SMODE == 5 ? shd1_rec(S, slot) : shd_rec(S, slot);
+    const float4* H = SMODE == 4 ? r1_shd(S, A.Q, slot) : SMODE == 3 ? shd_rec(S, slot) : shd1_rec(S, slot);
     const float4 s0 = H[0], s1 = H[1];
     info = __float_as_int(s1.w);
     trav_begin(T, world_of(A, info >> 12), mk(s0.x, s0.y, s0.z), mk(s1.x, s1.y, s1.z), s0.w);
@@ -395,8 +404,17 @@ DEV void shadow_end(const WArgs& A, int slot, int info, bool occ) {
     } else if (SMODE == 5) {
         // cached backward: the vertex's record reads visible; an occluded sample marks it
         if (occ) vtx_rec(S, Q, (info & 255) - 1, slot)[1].w = __int_as_float(1);
+    } else if (SMODE == 0) {
+        // the path's radiance already holds the next-event part (k_shade<0>); an occluded light sample
+        // restores it from beside the shadow rays
+        if (occ) {
+            float4* dst = acc_rec(S, slot) + 5;
+            const float4* Lw = rest_rec(S, Q, slot);
+            const float4 l0 = Lw[0], l1 = Lw[1], l2 = Lw[2];
+            dst[0] = l0; dst[1] = l1; dst[2] = l2;
+        }
+        if (A.sig) sig_add(A.sig[A.g0 + slot], (uint32_t)(occ ? NEE_OCCLUDED : NEE_VISIBLE));
     } else if (SMODE >= 0) {
-        const float4* H = shd_rec(S, slot);
         if (SMODE == 1) {
             // the cache record holds E_b plus the next-event part and a visible sample
             // (k_shade<1>); an occluded light sample sets the E words back to E_b (zero unless
@@ -405,7 +423,7 @@ DEV void shadow_end(const WArgs& A, int slot, int info, bool occ) {
             if (occ) {
                 float4* dst = cache_rec(S, Q, (info & 255) - 1, slot) + 4;
                 if (info & INFO_EMIT) {
-                    const float4* Eb = emit1_rec(S, Q, slot);
+                    const float4* Eb = rest_rec(S, Q, slot);
 #pragma unroll
                     for (int k = 0; k < 3; ++k) dst[k] = Eb[k];
                 } else {  // (E_b is zero)
@@ -416,15 +434,15 @@ DEV void shadow_end(const WArgs& A, int slot, int info, bool occ) {
             }
         } else if (SMODE != 2) {  // the hybrid replay recomputes the next-event part from the visibility bit
             // (the tape forward adds it to both the radiance and the vertex's E_b)
+            const float4* H = shd_rec(S, slot);
             float4* dst = acc_rec(S, slot) + 5;
-            if (!occ)
+            if (!occ) {
+                float4* te = tape_rec(S, Q, (info & 255) - 1, slot) + 4;
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
                     float4 a = dst[k], p = H[2 + k];
                     dst[k] = f4(a.x + p.x, a.y + p.y, a.z + p.z, a.w + p.w);
                 }
-            if (SMODE == 3 && !occ) {
-                float4* te = tape_rec(S, Q, (info & 255) - 1, slot) + 4;
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
                     float4 a = te[k], p = H[5 + k];
@@ -432,7 +450,7 @@ DEV void shadow_end(const WArgs& A, int slot, int info, bool occ) {
                 }
             }
         }
-        if (SMODE != 0 && SMODE != 1) {  // in the hit word of the vertex whose light sample this is
+        if (SMODE != 1) {  // in the hit word of the vertex whose light sample this is
             float* hwp = SMODE == 3 ? &tape_rec(S, Q, (info & 255) - 1, slot)[2].w
                                     : &hit_rec(S, Q, (info & 255) - 1, slot)->x;
             uint32_t hw = (uint32_t)__float_as_int(*hwp);
@@ -708,7 +726,6 @@ DEV void shade_slot(const WArgs& A, const Call& K, int slot, Count& cnt, bool& c
         else if (MODE != 2) eval_vertex<false, EXT>(W, K, x, w, Ee, En, nullptr, nullptr);
         cont = x.lobe != LOBE_NONE && x.lobe != LOBE_INVALID;
         shadow = x.nee == NEE_PENDING;
-        float4* H = shd_rec(S, slot);
         // the vertex's info word carried by its shadow ray's record (vertex count and view;
         // the delta bit is the continuing ray's and is not read for a shadow ray)
         const int info_shd = info_make(b, false, v);
@@ -817,9 +834,9 @@ DEV void shade_slot(const WArgs& A, const Call& K, int slot, Count& cnt, bool& c
                     pn[4 * c + r] = brgb[c] * sn;
                 }
             }
-            if (shadow) st12(H + 2, pn);
-            st12(AC + 5, Lo);
             if (MODE == 3) {
+                if (shadow) st12(shd_rec(S, slot) + 2, pn);
+                st12(AC + 5, Lo);
                 // the tape record of this vertex: weight, hit, emission (its next-event part is
                 // added when the shadow ray is resolved), the prefix throughput before the
                 // vertex, and the ray into it
@@ -836,6 +853,15 @@ DEV void shade_slot(const WArgs& A, const Call& K, int slot, Count& cnt, bool& c
                 T[12] = f4(brgb[0], brgb[1], brgb[2], prev_delta ? 1.0f : 0.0f);
                 T[13] = f4(o.x, o.y, o.z, d.x);
                 T[14] = f4(d.y, d.z, 0.0f, 0.0f);
+            } else if (shadow) {
+                // Lo with the next-event part as if its light sample were visible, the Lo that an occluded
+                // one restores beside the shadow rays: traversal writes nothing for a visible one
+                st12(rest_rec(S, Q, slot), Lo);
+#pragma unroll
+                for (int k = 0; k < 12; ++k) Lo[k] = add_rounded(Lo[k], pn[k]);
+                st12(AC + 5, Lo);
+            } else {
+                st12(AC + 5, Lo);
             }
             if (cont) {
                 if (w.kind == 1) {
@@ -930,7 +956,7 @@ DEV void shade_slot(const WArgs& A, const Call& K, int slot, Count& cnt, bool& c
                 float4* H1 = shd1_rec(S, slot);
                 H1[0] = f4(so.x, so.y, so.z, stmax);
                 H1[1] = f4(sd.x, sd.y, sd.z, __int_as_float(info_shd | (x.emit ? INFO_EMIT : 0)));
-                if (x.emit) st12(emit1_rec(S, A.Q, slot), Ee);
+                if (x.emit) st12(rest_rec(S, A.Q, slot), Ee);
             } else {
                 st12(C + 4, Ee);
             }
@@ -938,11 +964,11 @@ DEV void shade_slot(const WArgs& A, const Call& K, int slot, Count& cnt, bool& c
             // visible (traversal rewrites it for an occluded one)
             C[7] = f4(__int_as_float(shadow ? NEE_VISIBLE : 0), 0.0f, 0.0f, 0.0f);
         }
-        if (MODE != 4 && MODE != 1 && !ADJ && shadow) {  // a whole record (the Stokes words are [2..4]; partial ones measured slower)
+        if ((MODE == 0 || MODE == 2 || MODE == 3) && shadow) {  // (the tape: a whole 128-byte record)
+            float4* H = MODE == 3 ? shd_rec(S, slot) : shd1_rec(S, slot);
             H[0] = f4(so.x, so.y, so.z, stmax);
             H[1] = f4(sd.x, sd.y, sd.z, __int_as_float(info_shd));
             if (MODE == 3) st12(H + 5, En);  // (the tape's E_b takes the unweighted part)
-            else H[5] = H[6] = H[7] = f4(0.0f, 0.0f, 0.0f, 0.0f);
         }
         float4* Rw = ray_rec(S, slot);
         if (cont) ray_set(Rw, spawn(x.p, x.ng, x.wi), x.wi, r1.z, r1.w);  // (keeps the sensor rotation)
