@@ -508,7 +508,7 @@ struct WsLayout {
     size_t table, stats, counts, gacc, total;
     int lds_nd = 0, lds_nf = 0;
     bool lds_stage = false;  // a requested gradient has no workgroup accumulator
-    size_t ray, shd, acc, vtx, row, dq, cache, hits, ckpt, q0, q1, sq, hq, hf, nv, nv_bytes;
+    size_t ray, shd, acc, vtx, row, dq, cache, hits, ckpt, q0, q1, sq, hq, hf, nv;
     size_t ray2, shd2, acc2, q0_2, q1_2, sq2, hq2, hf2, counts2;  // P-RB sub-path state
     int64_t gacc_n;
 };
@@ -537,8 +537,8 @@ static WsLayout ws_layout(const ppt_plan* p, int op, int32_t Qslots, bool packed
     L.shd = take(op == 0 && rank_one(p) ? 0 : (adj ? SHD1_F4 : SHD_F4) * 16 * Q);
     const bool tape = op == 1 && p->adjoint == PPT_ADJOINT_TAPE;  // (forward accumulator + per-vertex tape)
     L.acc = take(op == 0 || tape ? ACC_F4 * 16 * Q : 0);
-    L.nv_bytes = (op == 0 && rank_one(p)) || op == 1 ? Q : 0;  // vertex counts (rank-one render, backward)
-    L.nv = take(L.nv_bytes);
+    // vertex counts (the full render's behind the shadow rays and what they restore, in the shadow array)
+    L.nv = op == 0 && !rank_one(p) ? L.shd + 5 * 16 * Q : take(Q);
     const bool hybrid = op == 1 && p->ckpt > 0;
     const size_t records = hybrid ? (size_t)std::min(p->ckpt, p->max_depth) : (size_t)p->max_depth;
     // the cached backward's vertex records and adjoint rows: within the 128 bytes per vertex that the
@@ -582,7 +582,7 @@ static PathState path_state(void* ws, const WsLayout& L) {
     S.ray = (float4*)(w + L.ray);
     S.shd = (float4*)(w + L.shd);
     S.acc = (float4*)(w + L.acc);
-    S.nv = L.nv_bytes ? (uint8_t*)(w + L.nv) : nullptr;
+    S.nv = (uint8_t*)(w + L.nv);
     S.vtx = (float4*)(w + L.vtx);
     S.row = (float4*)(w + L.row);
     S.dqueue = (int*)(w + L.dq);

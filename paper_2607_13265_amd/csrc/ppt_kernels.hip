@@ -329,8 +329,8 @@ __global__ void k_reset_counts(int* counts) {
 // ============================================================================ rays of a path
 // Begin and end of the rays of path `slot`, between their record and the traversal state T.
 //
-// Camera ray (info: view and the dead flag of a masked path): generated here, its record written when it is
-// finished; a masked path's keys at once.  Returns whether it is traversed.
+// Camera ray: generated here, its record written when it is finished.  Returns whether it is traversed (not
+// that of a masked path).
 DEV bool camera_begin(const WArgs& A, const ViewRange& range, int slot, Trav& T, int& info, Count& cnt) {
     const PathState& S = A.S;
     const int64_t g = A.g0 + slot;
@@ -340,30 +340,28 @@ DEV bool camera_begin(const WArgs& A, const ViewRange& range, int slot, Trav& T,
     const PathId id = path_keys(V, g);
     v3 o, d;
     camera_ray(V, V.crop_x0 + id.lx, V.crop_y0 + id.ly, id.smp, A.seed, o, d);
-    info = info_make(0, false, v) | (live ? 0 : INFO_DEAD);
+    info = info_make(0, false, v);
     trav_begin(T, world_of(A, V), o, d, 3.0e38f);
     if (A.sig) A.sig[g] = live ? 1469598103934665603ull : 0ull;
     if (live) {
         ++cnt.c[ST_PATHS];
         ++cnt.c[ST_RAYS];
     } else {
-        ray_rec(S, slot)[3] = f4(__int_as_float(info), __uint_as_float(id.pix), __uint_as_float(id.smp),
-                                 __uint_as_float(V.view_id));
         S.hflag[slot] = 2;
         if (S.nv) S.nv[slot] = 0;  // (no vertex)
     }
     return live;
 }
-// The camera ray's record: the whole record for a hit (ray, sensor rotation, hit, keys), the keys alone for
-// a ray that escaped (nothing else of it is read); the keys again from the slot and the view.
+// The camera ray's record if it hit a surface (ray, sensor rotation, hit, keys; the keys again from the slot
+// and the view); of a ray that escaped only the bytes that say so.
 DEV void camera_end(const WArgs& A, const ViewRange& range, int slot, const Trav& T, int info) {
     const PathState& S = A.S;
     const int64_t g = A.g0 + slot;
     int v;
     const DevView V = view_of(A, range, g, v);
-    float4* R = ray_rec(S, slot);
-    const PathId id = path_keys(V, g);
     if (T.h.prim >= 0) {
+        float4* R = ray_rec(S, slot);
+        const PathId id = path_keys(V, g);
         // rotation from the canonical frame of the light arriving along -d to the
         // sensor frame, kept in the record's spare words for the pixel reduction
         const v3 kc = -T.d;
@@ -371,9 +369,9 @@ DEV void camera_end(const WArgs& A, const ViewRange& range, int slot, const Trav
         rot_cs(kc, canon_x(kc), normalize(ld3(V.r) - kc * dot(ld3(V.r), kc)), Cs, Ss);
         ray_set(R, T.o, T.d, Cs, Ss);
         R[2] = f4(T.tb, T.h.u, T.h.v, __int_as_float(T.h.prim));
+        R[3] = f4(__int_as_float(info), __uint_as_float(id.pix), __uint_as_float(id.smp),
+                  __uint_as_float(V.view_id));
     }
-    R[3] = f4(__int_as_float(info), __uint_as_float(id.pix), __uint_as_float(id.smp),
-              __uint_as_float(V.view_id));
     S.hflag[slot] = T.h.prim >= 0 ? 1 : 0;
     // whether the path has a vertex (the shading kernels of the backward then count them)
     if (S.nv) S.nv[slot] = T.h.prim >= 0 ? 1 : 0;
@@ -1099,10 +1097,32 @@ __global__ void __launch_bounds__(BLOCK) k_paths(WArgs A, int per_wave) {
 // Every lane rotates its path's radiance into the sensor frame; the lanes of one pixel (adjacent,
 // samples fastest) are summed by a segmented wavefront scan, and the last lane of each segment
 // applies the analyzers and adds the mean to the image.  A pixel whose samples span two
-// wavefronts or chunks receives several additions.
+// wavefronts or chunks receives several additions; one of up to STORE_SPP samples, all
+// held by the wavefront, is stored to the cleared image instead: with many pixels a wavefront the additions, 9 to
+// 48 atomics a pixel, bounded the kernel (1 sample, 0.9M paths: 266 -> 41 us; 16 samples, 33.6M paths: 0.75 -> 0.42 ms;
+// but 32 samples, 67M paths: 0.84 -> 0.98 ms, since the next loads wait for the stores).
+// The scan takes its segments from one ballot and as many steps as the longest one (67M paths of 32 samples:
+// 1.17 -> 0.84 ms).
 // R1: the rank-one render of a linear-polarizer sensor, whose paths carry y_c = q^T R_s Lo_c (rotation
 // and analyzer row already applied): the scan sums three scalars and the output is (1, C, S, 0) y_c,
 // C = cos 2 theta, S = sin 2 theta (the polarizer's Mueller matrix is q' q'^T / 2 with q' = (1, C, S, 0)).
+constexpr int STORE_SPP = 16;
+// Adds o to a pixel of the image; whole: nothing else is added to it (aligned: the image lies on 16 bytes).
+DEV void pixel_add(float* out, const float* o, bool whole, bool aligned) {
+    bool any = false;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) any |= o[k] != 0.0f;
+    if (!any) return;
+    if (whole && aligned) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            ((float4*)out)[k] = f4(o[4 * k] + 0.0f, o[4 * k + 1] + 0.0f, o[4 * k + 2] + 0.0f, o[4 * k + 3] + 0.0f);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 12; ++k)
+            if (o[k] != 0.0f) atomicAdd(out + k, o[k]);
+    }
+}
 template <bool R1>
 __global__ void __launch_bounds__(BLOCK) k_accum(WArgs A) {
     if (!A.out) return;  // signature-only runs produce no image
@@ -1111,6 +1131,7 @@ __global__ void __launch_bounds__(BLOCK) k_accum(WArgs A) {
     Call K{A.table, nullptr};
     ViewRange range;
     const int lane = lane_id();
+    const bool aligned = ((uintptr_t)A.out & 15) == 0;
     for (int base = blockIdx.x * BLOCK + (threadIdx.x & ~(WAVE - 1)); base < A.n_chunk; base += gridDim.x * BLOCK) {
         int i = base + lane;
         bool valid = i < A.n_chunk;
@@ -1120,87 +1141,75 @@ __global__ void __launch_bounds__(BLOCK) k_accum(WArgs A) {
         for (int k = 0; k < NA; ++k) acc[k] = 0.0f;
         int v = 0;
         int64_t px_off = 0;  // the pixel's place in the image (first analyzer)
-        if (R1)
-            for_views(A, range, valid, A.g0 + i, [&](int vw, const DevView& V) {
-                const PathId id = path_keys(V, A.g0 + i);
-                v = vw;
-                key = ((int64_t)vw << 32) | (int64_t)id.pix;
-                px_off = V.out_off + ((int64_t)id.ly * V.crop_w + id.lx) * 12;
-            });
-        if (R1 && valid) {
-            // the keys from the path's index (the wavefront holds consecutive paths), and y from the
-            // path's record when the path has a vertex (one byte per path says so): no ray record
-            // is read, and no record of a path without radiance
-            if (S.nv[i]) {
+        // the keys from the path's index (the wavefront holds consecutive paths), and the radiance from the
+        // path's record when the path has a vertex (one byte per path says so): no record of a path
+        // without radiance is read
+        for_views(A, range, valid, A.g0 + i, [&](int vw, const DevView& V) {
+            const PathId id = path_keys(V, A.g0 + i);
+            v = vw;
+            key = ((int64_t)vw << 32) | (int64_t)id.pix;
+            px_off = V.out_off + ((int64_t)id.ly * V.crop_w + id.lx) * 12;
+        });
+        if (valid && S.nv[i]) {
+            if constexpr (R1) {
                 const float4 y = r1_rec(S, i)[2];
                 acc[0] = y.x; acc[1] = y.y; acc[2] = y.z;
-            }
-        } else if (valid) {
-            // pixel of the path from its stored keys; the segment key is (view, pixel)
-            const float4* R = ray_rec(S, i);
-            const float4 r3 = R[3];
-            const int info = __float_as_int(r3.x);
-            v = info >> 12;
-            const DevView V = gval(A.views, (size_t)v);
-            const uint32_t pix = __float_as_uint(r3.y);
-            const int py = (int)div_by(pix, V.inv_w), px = (int)(pix - (uint32_t)py * (uint32_t)V.width);
-            px_off = V.out_off + ((int64_t)(py - V.crop_y0) * V.crop_w + (px - V.crop_x0)) * 12;
-            key = ((int64_t)v << 32) | (int64_t)pix;
-            if (!(info & INFO_DEAD) && (info & 255) != 0) {  // a camera ray that escaped has no radiance
-                if constexpr (!R1) {
-                    const float4 r1 = R[1];
-                    const float Cs = r1.z, Ss = r1.w;  // sensor rotation of the camera ray
-                    float Lo[12];
-                    ld12(acc_rec(S, i) + 5, Lo);
+            } else {
+                const float4 r1 = ray_rec(S, i)[1];
+                const float Cs = r1.z, Ss = r1.w;  // sensor rotation of the camera ray
+                float Lo[12];
+                ld12(acc_rec(S, i) + 5, Lo);
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        float l1 = Lo[4 * c + 1], l2 = Lo[4 * c + 2];
-                        acc[4 * c] = Lo[4 * c];
-                        acc[4 * c + 1] = Cs * l1 + Ss * l2;
-                        acc[4 * c + 2] = -Ss * l1 + Cs * l2;
-                        acc[4 * c + 3] = Lo[4 * c + 3];
-                    }
+                for (int c = 0; c < 3; ++c) {
+                    float l1 = Lo[4 * c + 1], l2 = Lo[4 * c + 2];
+                    acc[4 * c] = Lo[4 * c];
+                    acc[4 * c + 1] = Cs * l1 + Ss * l2;
+                    acc[4 * c + 2] = -Ss * l1 + Cs * l2;
+                    acc[4 * c + 3] = Lo[4 * c + 3];
                 }
             }
         }
-        // inclusive segmented scan toward higher lanes
-#pragma unroll
+        // inclusive segmented scan toward higher lanes, over as many steps as the longest segment needs; the
+        // segments from one ballot of their first lanes
+        const int64_t kprev = __shfl_up(key, 1, WAVE);
+        const uint64_t first = __ballot(lane == 0 || kprev != key);
+        const int start = 63 - __clzll((long long)(first & (~0ull >> (63 - lane))));
         for (int off = 1; off < WAVE; off <<= 1) {
-            int64_t kup = __shfl_up(key, off, WAVE);
-            bool take = lane >= off && kup == key;
+            const bool take = lane - off >= start;
+            if (!__any(take)) break;
 #pragma unroll
             for (int k = 0; k < NA; ++k) {
                 float t = __shfl_up(acc[k], off, WAVE);
                 if (take) acc[k] += t;
             }
         }
-        int64_t knext = __shfl_down(key, 1, WAVE);
-        bool tail = valid && (lane == WAVE - 1 || knext != key);
+        const bool tail = valid && (lane == WAVE - 1 || ((first >> (lane + 1)) & 1ull) != 0ull);
         if (tail) {
             const DevView V = gval(A.views, (size_t)v);
             float theta = V.sensor == SENSOR_POLARIZER ? K.p(V.theta_slot, V.theta_off) : 0.0f;
             float inv = 1.0f / (float)V.spp;
-            const int64_t ob = px_off;
+            const bool whole = lane - start + 1 == V.spp && V.spp <= STORE_SPP;
             if constexpr (R1) {
                 const float C2 = cosf(2.0f * theta), S2 = sinf(2.0f * theta);
+                float o[12];
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
-                    const float o4[3] = {acc[c], C2 * acc[c], S2 * acc[c]};
-#pragma unroll
-                    for (int k = 0; k < 3; ++k)
-                        if (o4[k] != 0.0f) atomicAdd(A.out + ob + 4 * c + k, o4[k] * inv);
+                    o[4 * c] = acc[c] * inv; o[4 * c + 1] = C2 * acc[c] * inv; o[4 * c + 2] = S2 * acc[c] * inv;
+                    o[4 * c + 3] = 0.0f;
                 }
+                pixel_add(A.out + px_off, o, whole, aligned);
             } else {
                 int64_t astride = (int64_t)V.crop_w * V.crop_h * 12;
-                for (int a = 0; a < V.n_analyzers; ++a)
+                for (int a = 0; a < V.n_analyzers; ++a) {
+                    float o[12];
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {
-                        float o4[4];
-                        analyzer_apply(V.sensor, theta, a, acc + 4 * c, o4);
+                        analyzer_apply(V.sensor, theta, a, acc + 4 * c, o + 4 * c);
 #pragma unroll
-                        for (int k = 0; k < 4; ++k)
-                            if (o4[k] != 0.0f) atomicAdd(A.out + ob + a * astride + 4 * c + k, o4[k] * inv);
+                        for (int k = 0; k < 4; ++k) o[4 * c + k] *= inv;
                     }
+                    pixel_add(A.out + px_off + a * astride, o, whole, aligned);
+                }
             }
         }
     }
@@ -2067,17 +2076,14 @@ __global__ void __launch_bounds__(BLOCK) k_prb_start(WArgs A, PathState S2, int 
     const int Q = A.Q;
     Call K{A.table, nullptr};
     for (int i = blockIdx.x * BLOCK + threadIdx.x; i < A.n_chunk; i += gridDim.x * BLOCK) {
-        const float4* R = ray_rec(S, i);
-        const float4 r3 = R[3];
-        const int info = __float_as_int(r3.x);
-        const int B = (info & INFO_DEAD) ? 0 : (info & 255);
-        const int view = info >> 12;
         float4* R2 = ray_rec(S2, i);
-        if (B <= b1) {
-            R2[3] = f4(__int_as_float(info_make(b1, false, view) | INFO_DEAD), r3.y, r3.z, r3.w);
+        if ((int)S.nv[i] <= b1) {
+            R2[3] = f4(__int_as_float(info_make(b1, false, 0) | INFO_DEAD), 0.0f, 0.0f, 0.0f);
             S2.hflag[i] = 2;
             continue;
         }
+        const float4 r3 = ray_rec(S, i)[3];
+        const int view = __float_as_int(r3.x) >> 12;
         const DevView V = gval(A.views, (size_t)view);
         const DevWorld W = world_of(A, V);
         const uint32_t pix = __float_as_uint(r3.y), smp = __float_as_uint(r3.z);
@@ -2116,9 +2122,7 @@ __global__ void __launch_bounds__(BLOCK) k_prb_start(WArgs A, PathState S2, int 
 __global__ void __launch_bounds__(BLOCK) k_prb_store(WArgs A, PathState S2, int b1) {
     const PathState& S = A.S;
     for (int i = blockIdx.x * BLOCK + threadIdx.x; i < A.n_chunk; i += gridDim.x * BLOCK) {
-        const int info = __float_as_int(ray_rec(S, i)[3].x);
-        const int B = (info & INFO_DEAD) ? 0 : (info & 255);
-        if (B <= b1) continue;
+        if ((int)S.nv[i] <= b1) continue;
         float Lo[12];
         ld12(acc_rec(S2, i) + 5, Lo);
         st12(cache_rec(S, A.Q, b1 - 1, i) + 4, Lo);
