@@ -32,7 +32,7 @@ FLOP_NODE = 51          # one two-box BVH node test: 12 FMA + 24 min/max + 3 com
 FLOP_PRIM = 52          # one Moller-Trumbore triangle test
 FLOP_SHADE = 450        # one vertex in the shading kernel (sampling, Fresnel/GGX weight, next-event setup)
 FLOP_REPLAY = 950       # one vertex of the adjoint replay (re-evaluation + vector-Jacobian products)
-BYTES_FOLD_VERTEX = 144  # fold: 24 cache words read + 12 written back per vertex
+BYTES_FOLD_VERTEX = 144  # fold (light stage): 24 cache words read + 12 written back per vertex
 BYTES_FOLD_PATH = 96     # fold: keys read (16), adjoint rows (48) + camera ray (32) written per folded path
 PEAK_FP32_TFLOPS = 157.3  # MI355X FP32 vector peak (256 CU x 2.4 GHz x 64 lanes x FMA x packed)
 PEAK_HBM_GBS = 8000.0
@@ -44,7 +44,8 @@ KERNEL_SOURCES = ("paper_2607_13265_amd/csrc/ppt_kernels.hip", "paper_2607_13265
                   "paper_2607_13265_amd/build.py")  # (and the compiler flags)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_{}.md")
 KERNEL_SYMBOL = {"extend": "ppt::k_extend", "shade": "ppt::k_shade", "compact": "ppt::k_compact",
-                 "fold": "ppt::k_fold", "replay": "ppt::k_replay", "accum": "ppt::k_accum"}
+                 "fold": "ppt::k_fold", "replay": "ppt::k_replay", "accum": "ppt::k_accum",
+                 "walk": "ppt::k_adjoint"}  # (k_adjoint_deep and k_adjoint_first)
 
 
 def one_or_list(xs):
@@ -626,9 +627,14 @@ def main():
         "extend": ("alu", FLOP_NODE * (st["nodes"] + st["shadow_nodes"])
                    + FLOP_PRIM * (st["prim_tests"] + st["shadow_prim_tests"])),
         "shade": ("alu", FLOP_SHADE * st["vertices"]),
-        "replay": ("alu", FLOP_REPLAY * st_b["vertices"]),
-        "fold": ("hbm", BYTES_FOLD_VERTEX * st_b["vertices"] + BYTES_FOLD_PATH * st_b["paths"]),
     }
+    if args.workload == "lightstage":  # (its features keep the fold and the forward replay)
+        work["replay"] = ("alu", FLOP_REPLAY * st_b["vertices"])
+        work["fold"] = ("hbm", BYTES_FOLD_VERTEX * st_b["vertices"] + BYTES_FOLD_PATH * st_b["paths"])
+    else:  # the reverse walk: its later vertices and its first ones, in two families
+        work["walk"] = ("alu", FLOP_REPLAY * st_b["vertices"])
+        per_step["walk"] = sum(per_step.get(f, 0.0) for f in ("fold", "replay"))
+        launches["walk"] = max(launches.get("fold", 0), launches.get("replay", 1))
     fams = {}
     for f, (bound, amount) in work.items():
         if f not in per_step:

@@ -66,7 +66,7 @@ typedef struct ppt_view {
 typedef struct ppt_plan_opts {
     int64_t chunk_paths;          /* paths in flight per chunk (path-state capacity); 0 = min(all, 16M) */
     int64_t checkpoint_interval;  /* backward replay (Sec. 4.4): 0 = cached suffix replay, every vertex
-                                   * keeps W_b, E_b and its suffix (128 B); k >= 1 = hybrid cached
+                                   * keeps its records (at most 128 B); k >= 1 = hybrid cached
                                    * replay, only a 16-byte hit record per vertex, the suffix every k
                                    * vertices, and the vertices in between recomputed from it (exact;
                                    * less workspace for deep paths, more arithmetic).  k <= 128. */
@@ -178,8 +178,8 @@ int64_t ppt_plan_image_numel(const ppt_plan* plan);
 int64_t ppt_plan_num_paths(const ppt_plan* plan);
 
 /* Device workspace bytes needed by ppt_render (op = 0) or ppt_backward (op = 1): the
- * per-path records of one chunk of paths (for the backward pass including the per-vertex cache
- * of max_depth 128-byte records per path of the chunk, or the tape of the conventional-AD
+ * per-path records of one chunk of paths (for the backward pass including room for
+ * max_depth 128-byte records per path of the chunk, or the tape of the conventional-AD
  * baseline), independent of the total number of paths, and the FP64 gradient accumulators. */
 size_t ppt_plan_workspace_bytes(const ppt_plan* plan, int32_t op);
 
@@ -211,7 +211,7 @@ int ppt_backward(const ppt_plan* plan, const float* const* params, int32_t n_par
  * FP64 gradient accumulators live in a fixed device array of PPT_NOALLOC_SCRATCH_BYTES inside the
  * library, one per GPU, held until the process ends; the first call on a device looks up that
  * device's array.  Paths run in chunks of at most the plan's chunk size, cut down to what the array
- * holds (results do not depend on the chunking; a deep path needs 128 bytes per vertex of max_depth).
+ * holds (results do not depend on the chunking; a deep path needs 64 to 128 bytes per vertex of max_depth).
  * Every call on one GPU uses the same array, which keeps the previous call's contents (each call
  * clears what it needs): calls that overlap on one GPU, from other streams or threads, race and must
  * be serialized by the caller.  Work counters are not collected and per-kernel timing is not
@@ -245,14 +245,16 @@ int ppt_read_stats(const void* ws, int64_t* out, void* stream);
 int ppt_read_hybrid_stats(const void* ws, int64_t* out, void* stream);
 
 /* Per-kernel event timing (diagnostics).  While enabled, every render/backward call on the plan
- * records a HIP event on its stream before each kernel launch and one after its last launch.
+ * records a HIP event on its stream before each kernel launch and one after its last launch (and
+ * launches per bounce also where a chunk of few paths otherwise runs all its bounces in one launch).
  * ppt_plan_kernel_times waits for the most recent such call of `op` (0 render, 1 backward) and
  * writes, for kernel family k < n, the summed time between an event and the next (ms[k], in
  * milliseconds) and the number of launches (launches[k]).  Families: 0 camera rays launched
  * alone (none at present: the first traversal launch generates them), 1 traversal (closest hits
  * of a bounce's rays, from the second bounce on in the same launch as the shadow rays of the
  * previous bounce), 2 shading, 3 shadow rays launched alone (none at
- * present), 4 pixel reduction, 5 suffix fold, 6 adjoint replay, 7 setup / clearing /
+ * present), 4 pixel reduction, 5 suffix fold, or the walk from the last vertex to the second in the
+ * cached backward, 6 adjoint replay, or the cached backward's first vertices, 7 setup / clearing /
  * finalization, 8 hit compaction.  Enabling or disabling clears the
  * records.  Not for use under stream capture; calls on one plan must not overlap while
  * enabled.  Errors: PPT_EINVAL when no timed call of `op` was made, PPT_EDEVICE on HIP errors. */

@@ -12,10 +12,13 @@
 //              global atomic per flush).
 // Render (Sec. 3.1, Eq. 2): the state carries the prefix Mueller product beta and the radiance
 // sum; k_accum reduces the samples of each pixel.  Backward (Sec. 3.2, 4.3, Fig. 2): the primal
-// pass caches, per vertex, the weight W_b, the emission + next-event Stokes E_b and a hit record;
-// k_fold folds the cache into suffix radiance L[b] = E_b + W_b L[b+1] and queues the paths;
-// k_replay replays them forward from the hit records (no second traversal), differentiating each
-// vertex against the cached L[b+1].  No Mueller matrix is inverted.
+// pass keeps a hit record per vertex and carries the path's adjoint row forward; one walk from the last
+// vertex to the first (k_adjoint_deep, k_adjoint_first) evaluates each vertex again (no second
+// traversal), differentiates it against the suffix radiance L[b+1] it carries, and advances
+// L[b] = E_b + W_b L[b+1].  The light-stage variants and the comparators cache W_b and E_b per vertex instead:
+// k_fold folds them into suffixes and queues the paths, k_replay replays them forward.  No Mueller
+// matrix is inverted.
+// A chunk of few paths runs each path's bounces in one launch (k_paths, k_adjoint_paths).
 #include "ppt_device.h"
 
 #include <mutex>
