@@ -224,6 +224,7 @@ struct WorldHost {
 struct ppt_scene {
     int device = 0;
     std::vector<int64_t> slot_numel;
+    std::vector<int64_t> slot_cells;  // addresses of a slot that a material's reads spread over, the fewest of them
     std::vector<WorldHost*> worlds;
     DevBuf dev_worlds;
     int cu_count = 256;
@@ -358,6 +359,17 @@ static int convert_world(ppt_scene* sc, const uint8_t*& p, const uint8_t* end, W
             ok = false;
         if (ok && b.type == MAT_EMITTER && b.emit_slot < 0) ok = false;
         if (!ok) return fail(PPT_EINVAL, msg);
+        // the addresses that the material's reads of a slot spread over: a map's texels, one for a constant
+        auto cells = [&](int32_t slot, int64_t n) {
+            if (slot >= 0) sc->slot_cells[slot] = std::min(sc->slot_cells[slot], std::max<int64_t>(n, 1));
+        };
+        const bool alb = b.type == MAT_LAMBERT || b.type == MAT_BLEND;
+        const bool eta = b.type == MAT_DIELECTRIC || b.type == MAT_GGX_DIELECTRIC || b.type == MAT_GGX_CONDUCTOR || b.type == MAT_BLEND;
+        if (alb) cells(b.alb_slot, (int64_t)b.alb_tw * b.alb_th);
+        if (eta) cells(b.eta_slot, 1);
+        if (eta && b.type != MAT_DIELECTRIC) cells(b.alpha_slot, (int64_t)b.alpha_tw * b.alpha_th);
+        if (b.type == MAT_GGX_CONDUCTOR) cells(b.kap_slot, 1);
+        cells(b.emit_slot, 1);
         if (b.type != MAT_GGX_CONDUCTOR) m.kap_slot = -1;
         if (b.nrm_slot >= 0 || b.spec_slot >= 0 || b.emit_circ != 0.0f) sc->has_ext = true;
     }
@@ -378,6 +390,7 @@ static int convert_world(ppt_scene* sc, const uint8_t*& p, const uint8_t* end, W
         }
         L.area = (float)a;
         L.le_slot = b.le_slot; L.le_off = (int32_t)b.le_off;
+        sc->slot_cells[b.le_slot] = 1;
         L.circ = b.circ;
         if (b.circ != 0.0f) sc->has_ext = true;
     }
@@ -508,6 +521,7 @@ struct WsLayout {
     size_t table, stats, counts, gacc, total;
     int lds_nd = 0, lds_nf = 0;
     bool lds_stage = false;  // a requested gradient has no workgroup accumulator
+    int64_t stage_cells = 0;  // the fewest addresses that the reads of such a gradient's slot spread over
     size_t ray, shd, acc, vtx, row, dq, cache, hits, ckpt, q0, q1, sq, hq, hf, nv;
     size_t ray2, shd2, acc2, q0_2, q1_2, sq2, hq2, hf2, counts2;  // P-RB sub-path state
     int64_t gacc_n;
@@ -617,6 +631,7 @@ int ppt_scene_create(const void* blob, size_t nbytes, ppt_scene** out) {
         uint32_t n;
         std::memcpy(&n, p, 4); p += 4;
         sc->slot_numel.push_back(n);
+        sc->slot_cells.push_back(MANY_CELLS);
     }
     // validate every world on the host before any device work
     const uint8_t* body = p;
@@ -809,7 +824,7 @@ static bool small_call(const ppt_plan* p, int32_t Q) {
     return std::min<int64_t>(Q, p->num_paths) <= most && !p->scene->has_ext && !p->timing;
 }
 
-static int fill_table(const ppt_plan* p, int32_t Q, const float* const* params, int32_t n_params, float* const* grads,
+static int fill_table(const ppt_plan* p, const float* const* params, int32_t n_params, float* const* grads,
                       WsLayout& L, CallTable& t, int64_t* max_numel) {
     const ppt_scene* sc = p->scene;
     if (!params || n_params != (int32_t)sc->slot_numel.size()) return fail(PPT_EINVAL, "parameter count mismatch");
@@ -825,17 +840,18 @@ static int fill_table(const ppt_plan* p, int32_t Q, const float* const* params, 
         mx = std::max(mx, sc->slot_numel[i]);
     }
     if (max_numel) *max_numel = mx;
-    // workgroup gradient accumulators: small slots in FP64, then textures in FP32 while they fit
-    // (a small call's textures go to the global accumulator: clearing and flushing a texture's copy per
-    // workgroup costs more than its few additions)
-    const bool no_tex = small_call(p, Q) && cached_adjoint(p);
+    // workgroup gradient accumulators: small slots in FP64, then textures in FP32 while they fit (in small
+    // calls too: without them every vertex adds to the global accumulator, and additions to the same few
+    // addresses pass one after the other.  196,608 paths, depth 6: materials packed in slots of 100 to 300
+    // values 1,580 us, 430 with them; a 5 x 5 map 3,290 and 320; a 64 x 64 map, whose additions spread, 420 and 400)
     int nd = 0, nf = 0;
+    L.stage_cells = MANY_CELLS;
     for (int32_t i = 0; i < n_params; ++i) {
         if (t.goff[i] < 0) continue;
         int64_t n = sc->slot_numel[i];
         if (n <= 64 && nd + n <= LDS_GRAD_D) { t.lds_d[i] = nd; nd += (int)n; }
-        else if (!no_tex && nf + n <= LDS_GRAD_F) { t.lds_f[i] = nf; nf += (int)n; }
-        else L.lds_stage = true;
+        else if (nf + n <= LDS_GRAD_F) { t.lds_f[i] = nf; nf += (int)n; }
+        else { L.lds_stage = true; L.stage_cells = std::min(L.stage_cells, sc->slot_cells[i]); }
     }
     L.lds_nd = nd; L.lds_nf = nf;
     return PPT_OK;
@@ -898,7 +914,7 @@ static int render_impl(const ppt_plan* p, const float* const* params, int32_t n_
     if (rc) return rc;
     if (!out && !sig) return fail(PPT_EINVAL, "null output");
     CallTable t;
-    if ((rc = fill_table(p, p->Q, params, n_params, nullptr, L, t, nullptr))) return rc;
+    if ((rc = fill_table(p, params, n_params, nullptr, L, t, nullptr))) return rc;
     hipStream_t s = (hipStream_t)stream;
     WArgs a = make_args(p, seed, ws, L, p->Q);
     a.out = out;
@@ -934,7 +950,7 @@ static int backward_impl(const ppt_plan* p, const float* const* params, int32_t 
     CallTable t;
     int64_t mx = 1;
     int rc;
-    if ((rc = fill_table(p, Q, params, n_params, grads, L, t, &mx))) return rc;
+    if ((rc = fill_table(p, params, n_params, grads, L, t, &mx))) return rc;
     hipStream_t s = (hipStream_t)stream;
     WArgs a = make_args(p, seed, ws, L, Q);
     if (!stats) a.stats = nullptr;
@@ -944,7 +960,11 @@ static int backward_impl(const ppt_plan* p, const float* const* params, int32_t 
     a.lds_nf = L.lds_nf;
     a.lds_stage = L.lds_stage ? 1 : 0;
     a.ckpt = p->ckpt;
-    a.small = a.small && p->adjoint == PPT_ADJOINT_CACHED ? 1 : 0;
+    // (the walk of a small call has fewer of a pixel's samples in a wavefront to add together: where a gradient
+    // without a workgroup accumulator has few addresses for the paths, the launches per bounce stay)
+    const bool shared = cached_adjoint(p) && std::min<int64_t>(Q, p->num_paths) >
+                                                 std::max<int64_t>(SMALL_SHARED, SMALL_PER_CELL * L.stage_cells);
+    a.small = a.small && p->adjoint == PPT_ADJOINT_CACHED && !shared ? 1 : 0;
     a.hyb_rule = p->hyb_rule;
     a.hyb_gamma = p->hyb_gamma;
     a.hyb_eps = p->hyb_eps;

@@ -231,6 +231,12 @@ struct WArgs {
 // many bounces, gain further: 921,600 depth-128 paths in chunks of 262,144 59.1 -> 46.2 ms, 460,800 at once
 // 22.2 -> 21.5, 921,600 at once 34.3 -> 39.8.
 constexpr int SMALL_PATHS = 3 << 16, SMALL_PATHS_DEEP = 6 << 16, SMALL_DEPTH = 32;
+// Not so the cached backward of more than SMALL_SHARED paths, nor of more than SMALL_PER_CELL per address, where a
+// gradient goes to the global accumulator without a workgroup one (it has no room) and has few addresses: constants
+// of a 20,000-value slot, depth 2, 1,024 paths 92 us in one launch, 123 per bounce; 16,384 paths 322 and 140; 196,608
+// paths 564 and 313; an 8 x 8 map beside a full accumulator, 16,384 paths 177 and 130; a 16 x 16 map, 32,768 paths
+// 101 and 132, 196,608 paths 279 and 234.
+constexpr int64_t SMALL_SHARED = 2048, SMALL_PER_CELL = 128, MANY_CELLS = (int64_t)1 << 31;
 
 // workgroups per kernel family (extend_st: traversal with work counters); compute units
 struct LaunchGrid { int extend, shade, adjoint, other, cu, extend_st; };
