@@ -997,9 +997,13 @@ int ppt_backward_noalloc(const ppt_plan* p, const float* const* params, int32_t 
                          const float* d_stokes, float* const* grads, void* stream) {
     if (!p) return fail(PPT_EINVAL, "null plan");
     // the largest chunk (a multiple of the wavefront size, at most the plan's) whose records and
-    // the gradient accumulators fit in the fixed scratch
+    // the gradient accumulators fit in the fixed scratch; half a wavefront where the lines that keep the
+    // counters apart take the room that a whole one had
     const size_t cap = NOALLOC_SCRATCH_BYTES;
-    if (ws_layout(p, 1, WAVE, true).total > cap) {
+    const size_t apart = (p->adjoint == PPT_ADJOINT_PRB ? 2 : 1) * (align256(COUNT_INTS * 4) - 256);
+    const bool half = ws_layout(p, 1, WAVE, true).total > cap && ws_layout(p, 1, WAVE, true).total - apart <= cap &&
+                      ws_layout(p, 1, WAVE / 2, true).total <= cap;
+    if (ws_layout(p, 1, WAVE, true).total > cap && !half) {
         char msg[200];
         std::snprintf(msg, sizeof msg,
                       "the fixed scratch (%zu bytes) cannot hold the gradient accumulators and one %d-path chunk "
@@ -1011,7 +1015,7 @@ int ppt_backward_noalloc(const ppt_plan* p, const float* const* params, int32_t 
         const int64_t mid = (lo + hi + 1) / 2;
         if (ws_layout(p, 1, (int32_t)(mid * WAVE), true).total <= cap) lo = mid; else hi = mid - 1;
     }
-    const int32_t Q = (int32_t)(lo * WAVE);
+    const int32_t Q = half ? WAVE / 2 : (int32_t)(lo * WAVE);
     void* ws = nullptr;
     HIP_TRY(noalloc_scratch(&ws), "scratch address lookup");
     WsLayout L = ws_layout(p, 1, Q, true);
