@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <cstdint>
 
+#include "ppt_work.h"
+
 namespace ppt {
 
 constexpr int MAX_SLOTS = 64;   // parameter tensors per scene
@@ -153,7 +155,7 @@ struct LaunchMarker {
 // Queue sizes (the two ray queues, the shadow queue, the replay or reverse-walk queue, the hit queue) and
 // work counters of the persistent kernels: WORK_SHARDS counters for each of WORK_SETS uses, every one in a
 // cache line of its own (additions to one address pass one after the other, some 10 ns apart).
-constexpr int WORK_SHARDS = 16, WORK_LINE = 32, WORK_FIRST = 5 * WORK_LINE;
+constexpr int WORK_LINE = 32, WORK_FIRST = 5 * WORK_LINE;
 __host__ __device__ constexpr int CNT_RAY(int q) { return q * WORK_LINE; }
 constexpr int CNT_SHADOW = 2 * WORK_LINE, CNT_REPLAY = 3 * WORK_LINE, CNT_HIT = 4 * WORK_LINE;
 constexpr int WORK_TRAVERSAL = 0, WORK_REPLAY = 1, WORK_ADJOINT = 2, WORK_SETS = 3;

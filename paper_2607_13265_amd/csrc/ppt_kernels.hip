@@ -88,7 +88,8 @@ DEV void sig_add(uint64_t& h, uint32_t x) {
 // [w * s, (w + 1) * s) with s = n / active wavefronts rounded up and kept in [FETCH_MIN, batch];
 // positions beyond all static batches are handed out in batches through one atomic on a counter that an earlier
 // kernel cleared, one of WORK_SHARDS: wavefront w takes from counter w mod WORK_SHARDS, whose t-th ticket is
-// batch t WORK_SHARDS + (w + t) mod WORK_SHARDS, so that no counter's batches keep to one part of an image.
+// batch t WORK_SHARDS + (w + t) mod WORK_SHARDS, so that no counter's batches keep to one part of an image.  A
+// wavefront stops at its counter's first ticket beyond the queue; fewer than WORK_SHARDS wavefronts share fewer counters.
 // On a single counter the additions (10 ns each, one after the other) took most of a camera-ray launch and
 // forced batches of 256; with 16 counters and batches of 64 (128 where each wavefront takes many) the
 // camera rays of 4.2M paths take 181 us instead of 340, those of the 128-view batch 6.1 ms a step
@@ -118,23 +119,24 @@ DEV bool fetch_active(int n, int least = 0) { return (int)blockIdx.x < fetch_blo
 DEV int* work_counter(const PathState& S, int set, int shard) {
     return S.counts + WORK_FIRST + (set * WORK_SHARDS + shard) * WORK_LINE;
 }
-// the next ticket of a work counter, wave-uniform (every lane of the wavefront calls it)
-DEV int work_ticket(const PathState& S, int set, int wave) {
-    const int shard = wave & (WORK_SHARDS - 1);
+// the batch of the next ticket of the wavefront's counter, wave-uniform (every lane of the wavefront calls it);
+// waves: the wavefronts that take tickets
+DEV int work_ticket(const PathState& S, int set, int wave, int waves) {
+    const int shards = work_shards(waves), shard = wave & (shards - 1);
     int t = 0;
     if (lane_id() == 0) t = atomicAdd(work_counter(S, set, shard), 1);
-    t = __builtin_amdgcn_readfirstlane(t);
-    return t * WORK_SHARDS + ((shard + t) & (WORK_SHARDS - 1));
+    return work_batch(__builtin_amdgcn_readfirstlane(t), shard, shards);
 }
 DEV int wave_number() { return blockIdx.x * (BLOCK / WAVE) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE)); }
 struct WaveFetch {
     int c, cend;    // the wavefront's current batch [c, cend)
     int stat;       // positions covered by the static batches
     int batch;      // positions per ticket
+    int waves;      // wavefronts that take part
     bool exhausted;
     DEV explicit WaveFetch(int n, int least = 0, bool replay = false) {
         const int smin = fetch_min(n, least);
-        const int waves = fetch_blocks(n, smin) * (BLOCK / WAVE);
+        waves = fetch_blocks(n, smin) * (BLOCK / WAVE);
         const int w = wave_number();  // (known uniform: the fetch state stays in scalar registers)
         batch = replay ? FETCH_REPLAY : max(FETCH_MIN, min(FETCH_BATCH, n / (FETCH_SHARE * waves)));
         int sb = (n + waves - 1) / waves;
@@ -149,7 +151,7 @@ struct WaveFetch {
         const int k = (int)__popcll(m), rank = (int)__popcll(m & ((1ull << lane_id()) - 1ull));
         const int rem = cend - c;
         int nb = -1;
-        if (k > rem && !exhausted) nb = stat + work_ticket(S, set, wave_number()) * batch;
+        if (k > rem && !exhausted) nb = stat + work_ticket(S, set, wave_number(), waves) * batch;
         int idx = -1;
         if (need) {
             if (rank < rem) idx = c + rank;
@@ -1953,7 +1955,7 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint_first(WArgs A) {
     float gtheta = 0.0f, C2 = 1.0f, S2 = 0.0f;
     int tkey = -1, angle_of = -1;
     while (true) {
-        const int r0 = work_ticket(S, WORK_ADJOINT, wave_number()) * run;
+        const int r0 = work_ticket(S, WORK_ADJOINT, wave_number(), waves) * run;
         if (r0 >= n) break;
         for (int base = r0; base < min(r0 + run, n); base += WAVE) {
             const int i = base + lane_id();
