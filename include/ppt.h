@@ -245,8 +245,10 @@ int ppt_read_stats(const void* ws, int64_t* out, void* stream);
 int ppt_read_hybrid_stats(const void* ws, int64_t* out, void* stream);
 
 /* Per-kernel event timing (diagnostics).  While enabled, every render/backward call on the plan
- * records a HIP event on its stream before each kernel launch and one after its last launch (and
- * launches per bounce also where a chunk of few paths otherwise runs all its bounces in one launch).
+ * records a HIP event on its stream before each kernel launch and one after its last launch.
+ * enabled = 1 launches per bounce also where a chunk of few paths otherwise runs all its bounces in one
+ * launch; enabled = 2 keeps the launches of an untimed call (such a launch is counted as family 1, the
+ * one that walks its paths back as family 6).
  * ppt_plan_kernel_times waits for the most recent such call of `op` (0 render, 1 backward) and
  * writes, for kernel family k < n, the summed time between an event and the next (ms[k], in
  * milliseconds) and the number of launches (launches[k]).  Families: 0 camera rays launched

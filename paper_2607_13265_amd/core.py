@@ -117,9 +117,10 @@ class Plan:
         """Enable/disable the in-kernel work counters (on by default)."""
         check(lib().ppt_plan_set_stats(self._h, 1 if enabled else 0))
 
-    def set_timing(self, enabled: bool):
-        """Enable/disable per-kernel HIP-event timing of the plan's calls (diagnostics; not under capture)."""
-        check(lib().ppt_plan_set_timing(self._h, 1 if enabled else 0))
+    def set_timing(self, enabled):
+        """Enable/disable per-kernel HIP-event timing of the plan's calls (diagnostics; not under capture).  True launches
+        per bounce also where a small call otherwise runs its paths in one launch; 2 keeps the launches of an untimed call."""
+        check(lib().ppt_plan_set_timing(self._h, 2 if enabled == 2 else 1 if enabled else 0))
 
     def kernel_times(self, op: int):
         """Per kernel family of the most recent timed call of op (0 render, 1 backward):

@@ -269,7 +269,7 @@ struct ppt_plan {
     LaunchGrid grid{1, 1, 1, 1, 0, 1};
     const uint8_t* mask = nullptr;
     bool stats = true;
-    bool timing = false;
+    int32_t timing = 0;         // per-kernel timing: 0 off, 1 launches per bounce, 2 the launches of an untimed call
     int32_t ckpt = 0;           // hybrid replay checkpoint interval, 0 = cached
     int32_t hyb_rule = 0;       // hybrid replay decision rule (Eq. 3) and its thresholds
     float hyb_gamma = 0.0f, hyb_eps = 0.0f;
@@ -817,11 +817,11 @@ int ppt_plan_launch_info(const ppt_plan* p, int64_t* chunk_paths, int32_t* n_chu
     return PPT_OK;
 }
 
-// A small chunk's paths run in one launch (not with the light-stage features; per-kernel timing keeps the
+// A small chunk's paths run in one launch (not with the light-stage features; per-kernel timing 1 keeps the
 // launches per bounce, whose families it tells apart).  Q: paths per chunk.
 static bool small_call(const ppt_plan* p, int32_t Q) {
     const int64_t most = p->max_depth >= SMALL_DEPTH ? SMALL_PATHS_DEEP : SMALL_PATHS;
-    return std::min<int64_t>(Q, p->num_paths) <= most && !p->scene->has_ext && !p->timing;
+    return std::min<int64_t>(Q, p->num_paths) <= most && !p->scene->has_ext && p->timing != 1;
 }
 
 static int fill_table(const ppt_plan* p, const float* const* params, int32_t n_params, float* const* grads,
@@ -1024,7 +1024,7 @@ int ppt_backward_noalloc(const ppt_plan* p, const float* const* params, int32_t 
 
 int ppt_plan_set_timing(ppt_plan* p, int32_t enabled) {
     if (!p) return fail(PPT_EINVAL, "null plan");
-    p->timing = enabled != 0;
+    p->timing = enabled == 2 ? 2 : enabled != 0;
     p->timer[0].begin();
     p->timer[1].begin();
     return PPT_OK;

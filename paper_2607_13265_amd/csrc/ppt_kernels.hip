@@ -2401,16 +2401,19 @@ static void launch_small_paths(const WArgs& a, int mode, hipStream_t s) {
     else if (a.r1adj) launch_paths<6>(a, pw, lds, s);
     else launch_paths<5>(a, pw, lds, s);
 }
-static hipError_t launch_small(const WArgs& a, int mode, const LaunchGrid& G, hipStream_t s) {
+static hipError_t launch_small(const WArgs& a, int mode, const LaunchGrid& G, hipStream_t s, const LaunchMarker& M) {
+    M(KF_EXTEND, s);
     launch_small_paths(a, mode, s);
     if (mode == 0) {
         const int gb = blocks_for(a.n_chunk, G.other);
+        if (a.out) M(KF_ACCUM, s);
         if (a.out && a.r1) hipLaunchKernelGGL(k_accum<true>, dim3(gb), dim3(BLOCK), 0, s, a);
         else if (a.out) hipLaunchKernelGGL(k_accum<false>, dim3(gb), dim3(BLOCK), 0, s, a);
         return hipGetLastError();
     }
     const int aw = small_per_wave(a, SMALL_LEAST_ADJ), per_block = aw * (BLOCK / WAVE);
     const int grid = (a.n_chunk + per_block - 1) / per_block;
+    M(KF_REPLAY, s);
     if (a.r1adj) hipLaunchKernelGGL(k_adjoint_paths<true>, dim3(grid), dim3(BLOCK), grad_lds(a), s, a, aw);
     else hipLaunchKernelGGL(k_adjoint_paths<false>, dim3(grid), dim3(BLOCK), grad_lds(a), s, a, aw);
     return hipGetLastError();
@@ -2426,7 +2429,7 @@ hipError_t launch_chunk(WArgs a, const PathState& S2, int mode, const LaunchGrid
     a.r1adj = a.adj && a.r1 ? 1 : 0;
     if (mode != 0 || !a.S.nv) a.r1 = 0;  // (the rank-one record is the render's, with its vertex flags)
     size_t lds = (size_t)a.stack_cap * BLOCK * sizeof(int);
-    if (a.small && (mode == 0 || a.adj)) return launch_small(a, mode, G, s);
+    if (a.small && (mode == 0 || a.adj)) return launch_small(a, mode, G, s, M);
     if (a.g0 > 0) {  // (the first chunk's counts were cleared with the call's other memory)
         M(KF_OTHER, s);
         hipLaunchKernelGGL(k_reset_counts, dim3(1), dim3(BLOCK), 0, s, a.S.counts);
@@ -2436,10 +2439,10 @@ hipError_t launch_chunk(WArgs a, const PathState& S2, int mode, const LaunchGrid
     const int xg = blocks_for((int64_t)a.n_chunk * (WAVE / SPREAD_DEEP), a.stats ? G.extend_st : G.extend);
     a.qin = 0;
     a.first = 1;
+    M(KF_EXTEND, s);
     if (a.small) {  // (the hybrid replay's forward pass)
         launch_small_paths(a, mode, s);
     } else {
-        M(KF_EXTEND, s);
         launch_extend<-2>(a, xg, lds, s);  // (camera rays generated in the launch)
     }
     for (int b = 1; b <= a.max_depth && !a.small; ++b) {
