@@ -266,7 +266,7 @@ struct ppt_plan {
     int64_t image_numel = 0, num_paths = 0;
     int32_t Q = 64;             // paths per chunk (slots of the path state)
     int32_t n_chunks = 1;
-    LaunchGrid grid{1, 1, 1, 1, 0, 1};
+    LaunchGrid grid{1, 1, 1, 0, 1};
     const uint8_t* mask = nullptr;
     bool stats = true;
     int32_t timing = 0;         // per-kernel timing: 0 off, 1 launches per bounce, 2 the launches of an untimed call

@@ -168,8 +168,7 @@ struct PathState {
     float4* acc;    // [Q][ACC_F4] (render)
     uint8_t* nv;    // [Q] vertices of the path: the first traversal writes 0 or 1, the backward's shading
                     // kernels the count; read by the rank-one pixel reduction (has the path a radiance
-                    // record), the fold and the first-vertex kernel, so that none reads a ray record (NULL:
-                    // not kept)
+                    // record), the fold and the first-vertex kernel, so that none reads a ray record
     float4* vtx;    // [max_depth][Q][VTX_F4] vertex records (cached backward)
     float4* row;    // [max_depth - 1][Q][ROW_F4 or ROW1_F4] adjoint rows of the vertices after the first
     int* dqueue;    // paths of two or more vertices (cached backward)
@@ -215,7 +214,7 @@ struct WArgs {
     int32_t r1;             // render by the rank-one record (every view has a linear-polarizer sensor, no ext)
     int32_t adj;            // cached backward (no checkpoints, no comparator)
     int32_t r1adj;          // cached backward of such a batch: adjoint rows in rank-one form
-    int32_t keep_deep;      // this bounce's hit queue is kept (in S.dqueue, its size in counts[3])
+    int32_t keep_deep;      // this bounce's hit queue is kept (in S.dqueue, its size in counts[CNT_REPLAY])
     int32_t small;          // a small call: its paths in one launch (k_paths)
     float* out;             // render output
     const float* dout;      // backward: dL/dStokes
@@ -241,7 +240,7 @@ constexpr int SMALL_PATHS = 3 << 16, SMALL_PATHS_DEEP = 6 << 16, SMALL_DEPTH = 3
 constexpr int64_t SMALL_SHARED = 2048, SMALL_PER_CELL = 128, MANY_CELLS = (int64_t)1 << 31;
 
 // workgroups per kernel family (extend_st: traversal with work counters); compute units
-struct LaunchGrid { int extend, shade, adjoint, other, cu, extend_st; };
+struct LaunchGrid { int extend, shade, other, cu, extend_st; };
 
 constexpr uint32_t FLAG_NO_NEE = 1u;
 

@@ -353,7 +353,7 @@ DEV bool camera_begin(const WArgs& A, const ViewRange& range, int slot, Trav& T,
         ++cnt.c[ST_RAYS];
     } else {
         S.hflag[slot] = 2;
-        if (S.nv) S.nv[slot] = 0;  // (no vertex)
+        S.nv[slot] = 0;  // (no vertex)
     }
     return live;
 }
@@ -379,7 +379,7 @@ DEV void camera_end(const WArgs& A, const ViewRange& range, int slot, const Trav
     }
     S.hflag[slot] = T.h.prim >= 0 ? 1 : 0;
     // whether the path has a vertex (the shading kernels of the backward then count them)
-    if (S.nv) S.nv[slot] = T.h.prim >= 0 ? 1 : 0;
+    S.nv[slot] = T.h.prim >= 0 ? 1 : 0;
 }
 // Next-event ray: the ray and its vertex's info word in one record (no read of the ray record, whose line
 // would be fetched for its 16-byte key word).
@@ -467,9 +467,8 @@ DEV void shadow_end(const WArgs& A, int slot, int info, bool occ) {
 // Closest hits of the rays of one bounce: a persistent kernel in which a lane takes the next queued
 // ray as soon as its own is finished.  SMODE >= 0: the same launch resolves the shadow rays of the
 // previous bounce (positions [0, n_s) of one work list, any hit; SMODE is that bounce's mode: 0
-// render, 1 backward, 2 hybrid replay), so the two kinds of rays share one launch and its tail.
-// SMODE 4: the render's mode for a linear-polarizer sensor (shadow rays and pending radiance in the
-// rank-one record of k_shade<4>).
+// full render, 1 backward with cache records (light stage, comparators), 2 hybrid replay, 3 tape, 4 render with
+// the rank-one record, 5 cached backward), so the two kinds of rays share one launch and its tail.
 // SMODE -1: the first bounce of rays whose records are written (P-RB sub-paths); SMODE -2: the
 // first bounce of a chunk's camera paths, each lane generating the camera ray of the path it takes
 // (no separate ray-generation pass writing records that this launch would read back).
@@ -1340,7 +1339,7 @@ DEV void flush_theta(const WArgs& A, const Call& K, int tkey, float gtheta) {
 // L[b] = E_b + W_b L[b+1] (L[b+1] written over E_b), adds the polarizer-angle term
 // delta^T (dP/dtheta) R_s L[1],
 // and sets up the replay: the adjoint rows a_c = (delta^T A / spp) R_s, the camera ray's direction,
-// the path's keys and vertex count (all in the shadow record's words 0..4) and an entry of the replay queue (queue0, size counts[3]).  Each workgroup folds one
+// the path's keys and vertex count (all in the shadow record's words 0..4) and an entry of the replay queue (queue0, size counts[CNT_REPLAY]).  Each workgroup folds one
 // contiguous range of slots, so its lanes mostly see a single view and keep the angle term in a
 // register until the view changes.
 // PPRB (the noise-regularised comparator of Sec. 4.2): the fold uses W_b + u_b I, keeps the records'
@@ -2367,10 +2366,14 @@ static size_t grad_lds(const WArgs& a) {
            (a.lds_stage ? (size_t)(BLOCK / WAVE) * STAGE_WORDS * sizeof(float) : 0);
 }
 
-// Paths per wavefront of a small call, at least `least` and at most half a wavefront: spread over four wavefronts
-// per SIMD where the tree is deep (a path's rays then differ, and wait for each other), over two where it is
-// shallow and shading, the same for every wavefront, is the larger part (16,384 paths of the 20.5k-triangle scene
-// 361 us against 398, of the 3-sphere scene 128 us against 96).
+// Paths per wavefront of a small call, at least `least` and at most half a wavefront: spread over 4,096 wavefronts
+// (four per SIMD, of which three are resident: all variants but the hybrid replay's without counters hold 130 to 155
+// registers) where the tree is deep (a path's rays then differ, and wait for each other), over 2,048 where it is
+// shallow and shading, the same for every wavefront, is the larger part.  16,384 paths, depth 6, render and backward, 4,096 and
+// 2,048 wavefronts, by stack entries: 5 (three spheres) 112 and 88 us (the backward), 8 (40 triangles) 60 + 118 and
+// 61 + 99, 9 (80 triangles) 98 + 168 and 90 + 131, 20 (20.5k triangles) 140 + 206 and 171 + 214.  In between 12 entries (200
+// triangles) 149 + 235 and 145 + 208, 15 (1,000) 366 + 447 and 387 + 437, at 32,768 paths 453 + 539 and 392 + 446: the
+// line lies where neither form loses below it.
 constexpr int SMALL_LEAST = 2, SMALL_LEAST_ADJ = 4, SMALL_WAVES_DEEP = 4096, SMALL_WAVES_SHALLOW = 2048;
 static int small_per_wave(const WArgs& a, int least) {
     const int waves = a.stack_cap > SHALLOW_STACK ? SMALL_WAVES_DEEP : SMALL_WAVES_SHALLOW;
@@ -2427,7 +2430,7 @@ hipError_t launch_chunk(WArgs a, const PathState& S2, int mode, const LaunchGrid
     // the reverse walk's differs from the replay's in the last bits: one texel moved by 5e-4)
     a.adj = mode == 1 && a.ckpt == 0 && !a.ext && !a.pprb && !a.tape && !a.prb ? 1 : 0;
     a.r1adj = a.adj && a.r1 ? 1 : 0;
-    if (mode != 0 || !a.S.nv) a.r1 = 0;  // (the rank-one record is the render's, with its vertex flags)
+    if (mode != 0) a.r1 = 0;  // (the rank-one record is the render's)
     size_t lds = (size_t)a.stack_cap * BLOCK * sizeof(int);
     if (a.small && (mode == 0 || a.adj)) return launch_small(a, mode, G, s, M);
     if (a.g0 > 0) {  // (the first chunk's counts were cleared with the call's other memory)
@@ -2593,20 +2596,17 @@ hipError_t launch_chunk(WArgs a, const PathState& S2, int mode, const LaunchGrid
 }
 
 hipError_t occupancy_grid(int cu, int stack_cap, LaunchGrid* G) {
-    int e = 0, sh = 0, ad = 0, ot = 0;
+    int e = 0, sh = 0, ot = 0;
     size_t lds = (size_t)stack_cap * BLOCK * sizeof(int);
     hipError_t r;
     if ((r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&e, k_extend<1, false>, BLOCK, lds)) != hipSuccess) return r;
     int es = 0;
     if ((r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&es, k_extend<1, true>, BLOCK, lds)) != hipSuccess) return r;
     if ((r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&sh, k_shade<1, false>, BLOCK, 0)) != hipSuccess) return r;
-    size_t glds = (size_t)LDS_GRAD_D * sizeof(double) + (size_t)LDS_GRAD_F * sizeof(float);
-    if ((r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&ad, k_replay<false, false>, BLOCK, glds)) != hipSuccess) return r;
     if ((r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&ot, k_accum<true>, BLOCK, 0)) != hipSuccess) return r;
     G->extend = (e > 0 ? e : 1) * cu;
     G->extend_st = (es > 0 ? es : 1) * cu;
     G->shade = (sh > 0 ? sh : 1) * cu;
-    G->adjoint = (ad > 0 ? ad : 1) * cu;
     G->cu = cu;
     G->other = (ot > 0 ? ot : 1) * cu;
     return hipSuccess;
