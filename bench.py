@@ -28,7 +28,7 @@ METRIC = "Mpath-vertices/s fwd+PRB adjoint; batched vs per-view launch, grad rel
 
 # Algorithmic FP32 operations (an FMA counts 2) per unit of work, read off the kernel source;
 # the design notes itemise them.
-FLOP_NODE = 51          # one two-box BVH node test: 12 FMA + 24 min/max + 3 compares
+FLOP_NODE = 39          # one two-box BVH node test: 12 FMA + 12 min/max + 3 compares
 FLOP_PRIM = 52          # one Moller-Trumbore triangle test
 FLOP_SHADE = 450        # one vertex in the shading kernel (sampling, Fresnel/GGX weight, next-event setup)
 FLOP_REPLAY = 950       # one vertex of the adjoint replay (re-evaluation + vector-Jacobian products)
@@ -39,7 +39,8 @@ PEAK_HBM_GBS = 8000.0
 # files whose content decides whether stored hardware counters still describe the kernels
 KERNEL_SOURCES = ("paper_2607_13265_amd/csrc/ppt_kernels.hip", "paper_2607_13265_amd/csrc/ppt_kernels_ext.hip",
                   "paper_2607_13265_amd/csrc/ppt_device.h",
-                  "paper_2607_13265_amd/csrc/ppt_internal.h", "paper_2607_13265_amd/csrc/ppt_host.cpp",
+                  "paper_2607_13265_amd/csrc/ppt_internal.h", "paper_2607_13265_amd/csrc/ppt_work.h",
+                  "paper_2607_13265_amd/csrc/ppt_host.cpp",
                   "paper_2607_13265_amd/csrc/ppt_half.h",  # (the host builds the BVH the kernels traverse)
                   "paper_2607_13265_amd/build.py")  # (and the compiler flags)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_{}.md")
@@ -634,7 +635,7 @@ def main():
     else:  # the reverse walk: its later vertices and its first ones, in two families
         work["walk"] = ("alu", FLOP_REPLAY * st_b["vertices"])
         per_step["walk"] = sum(per_step.get(f, 0.0) for f in ("fold", "replay"))
-        launches["walk"] = max(launches.get("fold", 0), launches.get("replay", 1))
+        launches["walk"] = launches.get("fold", 0) + launches.get("replay", 0)
     fams = {}
     for f, (bound, amount) in work.items():
         if f not in per_step:
