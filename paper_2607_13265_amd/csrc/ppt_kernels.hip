@@ -2374,7 +2374,8 @@ static size_t grad_lds(const WArgs& a) {
 // 61 + 99, 9 (80 triangles) 98 + 168 and 90 + 131, 20 (20.5k triangles) 140 + 206 and 171 + 214.  In between 12 entries (200
 // triangles) 149 + 235 and 145 + 208, 15 (1,000) 366 + 447 and 387 + 437, at 32,768 paths 453 + 539 and 392 + 446: the
 // line lies where neither form loses below it.
-constexpr int SMALL_LEAST = 2, SMALL_LEAST_ADJ = 4, SMALL_WAVES_DEEP = 4096, SMALL_WAVES_SHALLOW = 2048;
+constexpr int SMALL_LEAST = 2, SMALL_LEAST_ADJ = 4, SMALL_WAVES_DEEP = 4096, SMALL_WAVES_SHALLOW = 2048, SMALL_WAVES_WALK = 3072,
+              SMALL_SCATTERS = 8192;
 static int small_per_wave(const WArgs& a, int least) {
     const int waves = a.stack_cap > SHALLOW_STACK ? SMALL_WAVES_DEEP : SMALL_WAVES_SHALLOW;
     const int pw = (a.n_chunk + waves - 1) / waves;
@@ -2414,7 +2415,15 @@ static hipError_t launch_small(const WArgs& a, int mode, const LaunchGrid& G, hi
         else if (a.out) hipLaunchKernelGGL(k_accum<false>, dim3(gb), dim3(BLOCK), 0, s, a);
         return hipGetLastError();
     }
-    const int aw = small_per_wave(a, SMALL_LEAST_ADJ), per_block = aw * (BLOCK / WAVE);
+    // (texture scatters: whole wavefronts once three per SIMD are filled.  Fewer, larger wavefronts issue fewer
+    // atomics, and more of a pixel's samples meet: 196,608 paths, depth 6, 256 x 256 maps 400 -> 334 us, two texels of
+    // them in view 2,230 -> 1,830; with fewer paths smaller wavefronts are the faster, 16,384 paths 161 us against 184,
+    // unless the paths are short and little but scatters is left: depth 2, 94 -> 77 us, less than a texel in view 315 -> 122,
+    // depth 3, 110 -> 107 and 404 -> 209, but depth 4, 125 -> 135, and 1,024 paths of depth 3, 106 -> 116)
+    const bool scatters = a.lds_stage && a.max_depth <= 3 && a.n_chunk > SMALL_SCATTERS;
+    const int full = a.lds_stage ? (a.n_chunk + SMALL_WAVES_WALK - 1) / SMALL_WAVES_WALK : 0;
+    const int pw = small_per_wave(a, scatters ? WAVE / 2 : SMALL_LEAST_ADJ), aw = full <= pw ? pw : full < WAVE ? full : WAVE;
+    const int per_block = aw * (BLOCK / WAVE);
     const int grid = (a.n_chunk + per_block - 1) / per_block;
     M(KF_REPLAY, s);
     if (a.r1adj) hipLaunchKernelGGL(k_adjoint_paths<true>, dim3(grid), dim3(BLOCK), grad_lds(a), s, a, aw);

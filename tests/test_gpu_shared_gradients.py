@@ -57,16 +57,19 @@ def _plan(sc, width, height, spp, depth, **kw):
     return plan, [torch.from_numpy(p).cuda() for p in sc.params()], d
 
 
-@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("noalloc,depth", [(False, 4), (True, 4), (False, 3)])
 @pytest.mark.parametrize("kind,size,width,height,spp", [
     ("packed", 65, 31, 33, 1), ("packed", 300, 64, 65, 4), ("packed", 12800, 33, 62, 1), ("packed", 12801, 32, 64, 1),
     ("packed", 12801, 49, 41, 12), ("map", 1, 31, 7, 3), ("map", 5, 64, 48, 12), ("map", 56, 37, 29, 9), ("full", 4, 32, 64, 1),
-    ("full", 8, 64, 64, 2), ("full", 8, 64, 65, 2), ("full", 40, 33, 27, 8), ("map", 100, 41, 23, 8)])
-def test_small_call_gradients_equal_launches_per_bounce(kind, size, width, height, spp, noalloc):
+    ("full", 8, 64, 64, 2), ("full", 8, 64, 65, 2), ("full", 40, 33, 27, 8), ("map", 100, 41, 23, 8),
+    # (wavefronts of 32 paths in a walk of depth 3 and 8,193 paths, larger ones from 98,305 on: 33, 63 and 64 paths)
+    ("map", 100, 1, 8192, 1), ("map", 100, 8193, 1, 1),
+    ("map", 100, 1, 98305, 1), ("map", 100, 293, 11, 60), ("map", 100, 128, 128, 12)])
+def test_small_call_gradients_equal_launches_per_bounce(kind, size, width, height, spp, noalloc, depth):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     sc = _scene(kind, size)
-    plan, params, d = _plan(sc, width, height, spp, 4)
+    plan, params, d = _plan(sc, width, height, spp, depth)
 
     def run(grads):
         return plan.backward_noalloc(params, 5, d, grads) if noalloc else plan.backward(params, 5, d, grads=grads)
