@@ -226,11 +226,11 @@ struct WArgs {
 };
 
 // A chunk of at most this many paths runs each path's bounces in one launch instead of three launches per
-// bounce.  Steps of the 20.5k-triangle scene, depth 6: 131,072 paths 950 -> 551 us, 196,608 paths 1011 -> 687 us,
-// 4.2M paths in chunks of 196,608 16.7 -> 15.4 ms, but in chunks of 262,144 13.0 -> 14.2 ms: from there on the
-// compacted queues fill the GPU better.  Deep plans (SMALL_DEPTH and more), with three launches for each of
-// many bounces, gain further: 921,600 depth-128 paths in chunks of 262,144 59.1 -> 46.2 ms, 460,800 at once
-// 22.2 -> 21.5, 921,600 at once 34.3 -> 39.8.
+// bounce.  Steps of the 20.5k-triangle scene, depth 6: 131,072 paths 942 -> 538 us, 196,608 paths 1011 -> 659 us,
+// 4.2M paths in chunks of 196,608 16.4 -> 13.9 ms, in chunks of 262,144 12.95 -> 12.8 ms: from there on the
+// compacted queues fill the GPU as well.  Deep plans (SMALL_DEPTH and more), with three launches for each of
+// many bounces, gain further: 921,600 depth-128 paths in chunks of 262,144 59.3 -> 45.8 ms, 460,800 at once
+// 22.3 -> 21.2, 921,600 at once 34.4 -> 39.5.
 constexpr int SMALL_PATHS = 3 << 16, SMALL_PATHS_DEEP = 6 << 16, SMALL_DEPTH = 32;
 // Not so the cached backward of more than SMALL_SHARED paths, nor of more than SMALL_PER_CELL per address, where a
 // gradient goes to the global accumulator without a workgroup one (it has no room) and has few addresses: constants
