@@ -264,6 +264,7 @@ struct ppt_plan {
     int32_t max_depth = 1;
     uint32_t flags = 0;
     int64_t image_numel = 0, num_paths = 0;
+    int64_t used_views = 0;     // views with paths
     int32_t Q = 64;             // paths per chunk (slots of the path state)
     int32_t n_chunks = 1;
     LaunchGrid grid{1, 1, 1, 0, 1};
@@ -733,6 +734,7 @@ int ppt_plan_create(const ppt_scene* sc, const ppt_view* views, int32_t n_views,
         D.inv_w = 1.0 / (double)V.width;
         out_off += (int64_t)D.n_analyzers * V.crop_w * V.crop_h * 12;
         path_off += (int64_t)V.crop_w * V.crop_h * V.spp;
+        P->used_views += (int64_t)V.crop_w * V.crop_h > 0 ? 1 : 0;
         P->dviews.push_back(D);
     }
     P->image_numel = out_off;
@@ -875,6 +877,7 @@ static WArgs make_args(const ppt_plan* p, uint64_t seed, void* ws, const WsLayou
     a.ext = p->scene->has_ext ? 1 : 0;  // kernels with normal/specular maps and circular emitters
     a.r1 = rank_one(p) ? 1 : 0;
     a.small = small_call(p, Q) ? 1 : 0;
+    a.tiny_views = p->num_paths < TINY_VIEW * p->used_views ? 1 : 0;
     if (p->scene->worlds.size() == 1) {
         a.one_world = 1;
         a.world0 = p->scene->worlds[0]->dev;

@@ -216,6 +216,7 @@ struct WArgs {
     int32_t r1adj;          // cached backward of such a batch: adjoint rows in rank-one form
     int32_t keep_deep;      // this bounce's hit queue is kept (in S.dqueue, its size in counts[CNT_REPLAY])
     int32_t small;          // a small call: its paths in one launch (k_paths)
+    int32_t tiny_views;     // views of few paths (TINY_VIEW): a wavefront's paths lie in many of them
     float* out;             // render output
     const float* dout;      // backward: dL/dStokes
     double* gacc;           // backward: FP64 gradient accumulators
@@ -237,6 +238,11 @@ constexpr int SMALL_PATHS = 3 << 16, SMALL_PATHS_DEEP = 6 << 16, SMALL_DEPTH = 3
 // of a 20,000-value slot, depth 2, 1,024 paths 92 us in one launch, 123 per bounce; 16,384 paths 322 and 140; 196,608
 // paths 564 and 313; an 8 x 8 map beside a full accumulator, 16,384 paths 177 and 130; a 16 x 16 map, 32,768 paths
 // 101 and 132, 196,608 paths 279 and 234.
+// Views of fewer paths than this on average: the lanes of the first vertices' kernel look up their views each for
+// itself.  A pass per view of a wavefront's paths took, in the backward of 300,000 views of 1 path 1,350 us (each for itself
+// 666), 500,000 of 4 2,660 (1,570), 200,000 of 16 2,140 (1,920); with 32 paths 1,770 and 1,730 (with large maps 2,850 and
+// 3,090), with 64 1,806 and 1,840.
+constexpr int64_t TINY_VIEW = 32;
 constexpr int64_t SMALL_SHARED = 2048, SMALL_PER_CELL = 128, MANY_CELLS = (int64_t)1 << 31;
 
 // workgroups per kernel family (extend_st: traversal with work counters); compute units

@@ -213,29 +213,41 @@ DEV void view_find(const WArgs& A, ViewRange& R, bool active, int64_t g) {
     const uint64_t m = __ballot(active);
     if (m != 0ull) view_at(A, read_lane64(g, __ffsll((long long)m) - 1), R);
 }
+DEV int lane_view(const WArgs& A, int64_t g) {  // (g of each lane its own)
+    int lo = 0, hi = A.n_views - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (gval(&A.views[mid].path_off, 0) <= g) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+}
 DEV DevView view_of(const WArgs& A, const ViewRange& R, int64_t g, int& v) {
     DevView V = cval(A.views, R.v);
     v = R.v;
     if (g < R.lo || g >= R.hi) {
-        int lo = 0, hi = A.n_views - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (gval(&A.views[mid].path_off, 0) <= g) lo = mid; else hi = mid - 1;
-        }
-        v = lo;
-        V = gval(A.views, (size_t)lo);
+        v = lane_view(A, g);
+        V = gval(A.views, (size_t)v);
     }
     return V;
 }
 // f(v, V) for the active lanes, view by view: v and V are the wave-uniform view of the lanes that run it
 // (one pass unless the lanes' paths g span views).  Every lane of the wavefront calls it, so that the
-// range stays in scalar registers.
-template <class F>
+// range stays in scalar registers.  EACH: lanes left after VIEW_PASSES views look theirs up each for itself (a
+// wavefront of 64 views of one path took 64 passes: render of 300,000 such views 245 -> 393 us).
+constexpr int VIEW_PASSES = 4;
+template <bool EACH = true, class F>
 DEV void for_views(const WArgs& A, ViewRange& R, bool active, int64_t g, F f) {
     bool todo = active;
-    while (true) {
+    for (int pass = 0;; ++pass) {
         const uint64_t m = __ballot(todo);
         if (m == 0ull) break;
+        if (EACH && pass == VIEW_PASSES) {
+            if (todo) {
+                const int v = lane_view(A, g);
+                f(v, gval(A.views, (size_t)v));
+            }
+            break;
+        }
         view_at(A, read_lane64(g, __ffsll((long long)m) - 1), R);
         if (todo && g >= R.lo && g < R.hi) {
             const DevView V = cval(A.views, R.v);
@@ -1935,8 +1947,9 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint_deep(WArgs A) {
 // term delta^T (dP/dtheta) R_s L[1].  A wavefront takes runs of ADJ_RUN paths from a counter (a fixed
 // stride walks the same part of every view of a batch of equal views, and the wavefronts on its
 // objects end last: 5.2 ms against 2.7 ms on the 128-view batch), long enough that its lanes seldom change
-// view and keep the angle term in a register until they do.
+// view and keep the angle term in a register until they do.  TINY: a view's lanes are few, and each looks up its own.
 constexpr int ADJ_RUN = 8 * WAVE;
+template <bool TINY>
 __global__ void __launch_bounds__(BLOCK) k_adjoint_first(WArgs A) {
     extern __shared__ double lds_grad[];
     PathState& S = A.S;
@@ -1962,7 +1975,7 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint_first(WArgs A) {
             int v = -1;
             float gt = 0.0f;
             bool pol = false;
-            for_views(A, range, B > 0, A.g0 + i, [&](int vw, const DevView& V) {
+            auto first = [&](int vw, const DevView& V) {
                 v = vw;
                 const float4* C = vtx_rec(S, Q, 0, i);
                 const float4 c0 = C[0], c1 = C[1];
@@ -1987,10 +2000,18 @@ __global__ void __launch_bounds__(BLOCK) k_adjoint_first(WArgs A) {
                 rot_cs(kc, canon_x(kc), normalize(ld3(V.r) - kc * dot(ld3(V.r), kc)), Cs, Ss);
                 float av[12];
                 sensor_rows(A, V, px_off, C2, S2, Cs, Ss, av);
-                const DevWorld W = A.one_world ? A.world0 : cval(A.worlds, V.world);
+                const DevWorld W = TINY || A.one_world ? world_of(A, V) : cval(A.worlds, V.world);
                 adjoint_vertex(A, K, W, V.view_id, id.pix, id.smp, 1, B == 1, c0, c1, av, L);
                 if (pol) gt = theta_term(A.dout + px_off, 1.0f / (float)V.spp, C2, S2, Cs, Ss, L);
-            });
+            };
+            if constexpr (TINY) {
+                if (B > 0) {
+                    const int vw = lane_view(A, A.g0 + i);
+                    first(vw, gval(A.views, (size_t)vw));
+                }
+            } else {
+                for_views<false>(A, range, B > 0, A.g0 + i, first);
+            }
             if (__any(pol && tkey >= 0 && tkey != v)) {
                 flush_theta(A, KG, tkey, gtheta);
                 tkey = -1;
@@ -2520,8 +2541,10 @@ hipError_t launch_chunk(WArgs a, const PathState& S2, int mode, const LaunchGrid
                 else hipLaunchKernelGGL(k_adjoint_deep<false>, dim3(dg), dim3(BLOCK), glds, s, a);
             }
             M(KF_REPLAY, s);
-            const int fg = resident_grid((const void*)k_adjoint_first, glds, a.n_chunk, G);
-            hipLaunchKernelGGL(k_adjoint_first, dim3(fg), dim3(BLOCK), glds, s, a);
+            const void* first = a.tiny_views ? (const void*)k_adjoint_first<true> : (const void*)k_adjoint_first<false>;
+            const int fg = resident_grid(first, glds, a.n_chunk, G);
+            if (a.tiny_views) hipLaunchKernelGGL(k_adjoint_first<true>, dim3(fg), dim3(BLOCK), glds, s, a);
+            else hipLaunchKernelGGL(k_adjoint_first<false>, dim3(fg), dim3(BLOCK), glds, s, a);
             return hipGetLastError();
         }
         M(KF_FOLD, s);
