@@ -102,14 +102,15 @@ DEV void sig_add(uint64_t& h, uint32_t x) {
 //
 // Traversal spreads a queue that does not fill the GPU (least > 0): with fewer rays than lanes, a launch
 // lasts as long as its slowest wavefront, whose lanes wait for each other's descents and leaves, so
-// a wavefront takes only n / SPREAD_WAVES positions, and at least `least`: 2 in a scene whose tree is deep
-// enough for rays to differ, 8 in a shallow one (fewer cost the 3-sphere scene 3 %).  A 5,917-path preview
-// 304 -> 229 us, a 28,512-path step 1040 -> 873 us, the 3-sphere step 185 -> 180 us; one ray per wavefront
-// gains 2 % more and costs the smallest scene 10 %; from SPREAD_WAVES full wavefronts on, two per SIMD,
-// full wavefronts are the faster.
+// a wavefront takes only n / SPREAD_WAVES positions, and at least `least`, 2, in a scene whose tree is deep
+// enough for rays to differ.  A 5,917-path preview 304 -> 229 us, a 28,512-path step 1040 -> 873 us (launches per
+// bounce); from SPREAD_WAVES full wavefronts on, two per SIMD, full wavefronts are the faster.  Not in a shallow one,
+// whose rays take alike: with 8 rays a wavefront a traversal launch through 20 polarizer sheets took 18.9 us instead of
+// 14.8 (P-RB of 47,616 paths in chunks of 1,024 30.5 ms against 25.5; P-PRB of 2,304 paths through 85 sheets 5.10
+// against 4.91), 16,384 paths among 80 triangles gained 1 to 3 %.
 constexpr int FETCH_MIN = WAVE, FETCH_BATCH = 2 * WAVE, FETCH_REPLAY = 4 * WAVE, FETCH_SHARE = 8;
-constexpr int SPREAD_DEEP = 2, SPREAD_SHALLOW = 8, SPREAD_WAVES = 2048, SHALLOW_STACK = 10;
-DEV int spread_least(const WArgs& A) { return A.stack_cap > SHALLOW_STACK ? SPREAD_DEEP : SPREAD_SHALLOW; }
+constexpr int SPREAD_DEEP = 2, SPREAD_WAVES = 2048, SHALLOW_STACK = 10;
+DEV int spread_least(const WArgs& A) { return A.stack_cap > SHALLOW_STACK ? SPREAD_DEEP : 0; }
 DEV int fetch_min(int n, int least) { return least ? max(least, min(FETCH_MIN, (n + SPREAD_WAVES - 1) / SPREAD_WAVES)) : FETCH_MIN; }
 DEV int fetch_blocks(int n, int per_wave) {
     const int per_block = per_wave * (BLOCK / WAVE);
@@ -2468,8 +2469,9 @@ hipError_t launch_chunk(WArgs a, const PathState& S2, int mode, const LaunchGrid
         hipLaunchKernelGGL(k_reset_counts, dim3(1), dim3(BLOCK), 0, s, a.S.counts);
     }
     const int gb = blocks_for(a.n_chunk, G.other), cg = blocks_for(a.n_chunk, 4 * G.cu);
-    // (traversal's grid: enough workgroups for the most spread queue)
-    const int xg = blocks_for((int64_t)a.n_chunk * (WAVE / SPREAD_DEEP), a.stats ? G.extend_st : G.extend);
+    // (traversal's grid: enough workgroups for a queue of two rays a path, and for the most spread one)
+    const int xg = blocks_for((int64_t)a.n_chunk * (a.stack_cap > SHALLOW_STACK ? WAVE / SPREAD_DEEP : 2),
+                              a.stats ? G.extend_st : G.extend);
     a.qin = 0;
     a.first = 1;
     M(KF_EXTEND, s);
